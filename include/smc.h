@@ -62,7 +62,7 @@ enum {
 };
 
 typedef enum {
-    SMC_PREC_FP64 = 0,        /* plain FP64 arithmetic with device-library exp/log */
+    SMC_PREC_FP64 = 0,        /* FP64 arithmetic throughout */
     SMC_PREC_FP32 = 1,        /* FP32 terms + hardware exp2, per-datum sums multiplied into a
                                  renormalised FP32 product (exponents kept as integers),
                                  FP64 total */
@@ -166,7 +166,10 @@ int smc_set_launch_table(smc_ctx ctx, const smc_launch_rule* rules, int32_t coun
 /* Per-particle log-likelihood (Mixture Modelling section):
  *   loglik[p] = sum_j log sum_i w_i N_d(y_j; mu_{p,i}, sigma2 I).
  * y: [n][d] FP32; theta: [k*d][N] FP64; loglik: [N] FP64 out.
- * prec FP64: plain form (device-library exp and log per datum, plain sum);
+ * prec FP64: for d = 1 the pivot form described below in FP64 (windows of 64
+ * data, exponent differences up to 250, terms below 2^-58 of a factor left out,
+ * one log per slice), windows it refuses in a max-shifted product form; for
+ * d > 1 an exp per term and a log per datum (relative error below 1e-12);
  * FP32: FP32 arithmetic in base 2 with hardware exp2, no per-datum log: each
  * datum's mixture sum is multiplied into a running FP32 product that is
  * renormalised by frexp after every block of 8 or 16 data, its exponents added

@@ -458,10 +458,249 @@ __device__ __forceinline__ double partial_fp32(const float* __restrict__ y, int 
     return msum + static_cast<double>(expo) + static_cast<double>(__builtin_amdgcn_logf(prod));
 }
 
+// 2^t in FP64 for |t| < 2^31 (0 below the FP64 range, NaN for NaN): 2^n 2^f with
+// n the nearest integer and a polynomial of degree 10 in f on [-1/2, 1/2]. Adding
+// 1.5 * 2^52 rounds t to an integer whose low word is n (cheaper here than
+// v_rndne_f64 and v_cvt_i32_f64, which issues at half rate). The coefficients are
+// the least-squares fit of the relative error at Chebyshev nodes with the
+// constant term 1, rounded to FP64 (relative error below 2.5e-16). 14
+// instructions; the device library's exp takes about 45.
+__device__ __forceinline__ double exp2_fp64(double t) {
+    constexpr double kRound = 6755399441055744.0;        // 1.5 * 2^52
+    const double r = t + kRound;
+    const double f = t - (r - kRound);
+    double p = 7.041923263577725e-09;
+    p = fma(p, f, 1.020852183362834e-07);
+    p = fma(p, f, 1.3215629590371928e-06);
+    p = fma(p, f, 1.5252658206764617e-05);
+    p = fma(p, f, 0.0001540353004830873);
+    p = fma(p, f, 0.0013333558228392813);
+    p = fma(p, f, 0.0096181291079336);
+    p = fma(p, f, 0.05550410866446);
+    p = fma(p, f, 0.2402265069590925);
+    p = fma(p, f, 0.6931471805599497);
+    p = fma(p, f, 1.0);
+    return __builtin_amdgcn_ldexp(p, static_cast<int>(__builtin_bit_cast(long long, r)));
+}
+
+// Sum over data j in [ja, jb) of ln sum_i w_i exp(-||y_j - mu_i||^2 / (2 sigma2))
+// in FP64, the general form: each datum's sum is taken relative to its largest
+// term (the maxima added in FP64) and lies in [1, K], so the sums are multiplied
+// into a product that one log finishes (its exponent taken out every 128 data).
+// NaN for a datum or parameter that is not finite in a component of nonzero
+// weight.
+template <int K>
+__device__ __forceinline__ double general_fp64(const float* __restrict__ y, int ja, int jb,
+                                               const double (&mu)[K], const GmmDev& g) {
+    constexpr double kLog2eD = 1.4426950408889634;
+    const double s2 = g.inv2s2 * kLog2eD;
+    double msum = 0.0, prod = 1.0;
+    int expo = 0;
+    for (int j = ja; j < jb; ++j) {
+        double a[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const double t = static_cast<double>(y[j]) - mu[i];
+            a[i] = g.lw[i] * kLog2eD - (t * t) * s2;
+        }
+        double m = a[0];
+#pragma unroll
+        for (int i = 1; i < K; ++i) m = fmax(m, a[i]);
+        double e = 0.0;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const double t = a[i] - m;
+            e += exp2_fp64(t < -4000.0 ? -4000.0 : t);     // keeps a NaN
+        }
+        msum += m;
+        prod *= e;
+        if (((j - ja) & 127) == 127) {
+            expo += __builtin_amdgcn_frexp_exp(prod);
+            prod = __builtin_amdgcn_frexp_mant(prod);
+        }
+    }
+    return kLn2 * (msum + static_cast<double>(expo) + log2(prod));
+}
+
+// Data per window of the FP64 pivot form (one per lane): a wave's staging row
+// holds one window of FP64 offsets (the room of two FP32 windows).
+constexpr int kPivotWin64 = kWave;
+static_assert(kPivotWin64 * sizeof(double) == kPivotRow * sizeof(float), "");
+// Shortest slice that takes the FP64 pivot form: choosing a window's pivots
+// costs about as much as three data of the general form.
+constexpr int kPivotMin64 = 8;
+// Largest exponent difference a window of the FP64 pivot form may hold: a block
+// of 4 factors below 1 + 7 * 2^T times a mantissa below 1 stays below the FP64
+// overflow at 2^1024 ((1 + 7 * 2^250)^4 < 2^1012).
+constexpr double kPivotOver64 = 250.0;
+// A component whose exponent difference to the pivot stays below this over a
+// window is left out there: its term is below 2^-58 of a factor of at least 1,
+// under a sixteenth of the resolution of the product update it would join.
+constexpr double kPivotSkip64 = -58.0;
+
+// The FP64 likelihood of the 1-D slice [j0, j1) in the pivot form (the algebra
+// of the FP32 pivot form above partial_fp32, all of it in FP64): per window of
+// 64 data each particle takes the component with the largest exponent at the
+// window's midpoint as its pivot, whose own terms come in closed form from two
+// sums over the window's data; every other component costs one FMA, one exp2
+// and one add per datum, and the per-datum factors 1 + sum 2^t are multiplied
+// into a product renormalised every 4 data, so no datum takes a log. Each
+// particle orders its other components by the largest exponent difference the
+// window can hold; the wave takes as many of them as its neediest particle
+// needs, and a particle that does not need one of them adds zero for it.
+// Bound by FP64 VALU issue: 16 instructions per datum and evaluated component
+// plus about 270 per window. Windows of 64 data rather than 128: the narrower
+// range needs fewer components, which saves more than the second choice of
+// pivots costs. A window where some particle's bound fails (a datum or parameter
+// not finite, components tens of standard deviations away on both sides of it)
+// goes through the general form.
+// Returns natural-log units.
+template <int K>
+__device__ __forceinline__ double pivot_fp64(const float* __restrict__ y, int j0, int j1,
+                                             const double (&mu)[K], const GmmDev& g,
+                                             const PivotStage& st) {
+    constexpr double kLog2eD = 1.4426950408889634;
+    constexpr int KO = K > 1 ? K - 1 : 1;
+    constexpr int U = 4;
+    const int lane = lane_id();
+    const double s2 = g.inv2s2 * kLog2eD;
+    double* row = reinterpret_cast<double*>(st.row);
+    double prod = 1.0, msum = 0.0, plain = 0.0;
+    int expo = 0;
+    float vnext = st.pre ? st.y0 : (j0 + lane < j1 ? y[j0 + lane] : 0.0f);
+    for (int wb = j0; wb < j1; wb += kPivotWin64) {
+        const int nw = wave_uniform(j1 - wb < kPivotWin64 ? j1 - wb : kPivotWin64);
+        const bool in = lane < nw;
+        const float v = vnext;
+        const int jn = wb + kPivotWin64 + lane;
+        vnext = jn < j1 ? y[jn] : 0.0f;              // in flight over this window
+        // the window's midpoint and half-width
+        const float lo = wave_min_dpp(in ? v : INFINITY);
+        const float hi = wave_max_dpp(in ? v : -INFINITY);
+        const double c = static_cast<double>(0.5f * lo + 0.5f * hi);
+        const double h = fmax(static_cast<double>(hi) - c, c - static_cast<double>(lo));
+        // exponents at the midpoint and the pivot
+        double a[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const double t = c - mu[i];
+            a[i] = g.lw[i] * kLog2eD - s2 * (t * t);
+        }
+        int piv = 0;
+        double best = a[0];
+#pragma unroll
+        for (int i = 1; i < K; ++i) {
+            const bool up = a[i] > best;
+            best = up ? a[i] : best;
+            piv = up ? i : piv;
+        }
+        double mp = mu[0], lwp = g.lw[0];
+#pragma unroll
+        for (int i = 1; i < K; ++i) {
+            mp = piv == i ? mu[i] : mp;
+            lwp = piv == i ? g.lw[i] : lwp;
+        }
+        double dX[KO], dB[KO], ub[KO];
+        bool ok = h <= 3.0e38 && fabs(best) <= 1.0e300;
+#pragma unroll
+        for (int o = 0; o + 1 < K; ++o) {
+            const bool up = o >= piv;
+            dX[o] = (up ? a[o + 1] : a[o]) - best;
+            dB[o] = 2.0 * s2 * ((up ? mu[o + 1] : mu[o]) - mp);
+            ub[o] = fma(fabs(dB[o]), h, dX[o]);
+            // false for NaN; the lower bound keeps t within exp2_fp64's range
+            ok &= ub[o] <= kPivotOver64 && (dX[o] >= -1.0e8 || ub[o] < kPivotSkip64);
+        }
+        if (!__all(ok)) {
+            plain += general_fp64<K>(y, wb, wb + nw, mu, g);
+            continue;
+        }
+        const double d = in ? static_cast<double>(v) - c : 0.0;
+        const double S1 = wave_sum_dpp(d);
+        const double S2 = wave_sum_dpp(d * d);
+        if constexpr (K > 1) {
+            wave_sync();                             // the previous window's reads come first
+            row[lane] = d;
+            // the others in decreasing order of ub (odd-even transposition
+            // network); those a particle does not need become exact zeros
+#pragma unroll
+            for (int r = 0; r < KO; ++r) {
+#pragma unroll
+                for (int o = r & 1; o + 1 < KO; o += 2) {
+                    const bool sw = ub[o + 1] > ub[o];
+                    const double u0 = ub[o], x0 = dX[o], b0 = dB[o];
+                    ub[o] = sw ? ub[o + 1] : u0;
+                    dX[o] = sw ? dX[o + 1] : x0;
+                    dB[o] = sw ? dB[o + 1] : b0;
+                    ub[o + 1] = sw ? u0 : ub[o + 1];
+                    dX[o + 1] = sw ? x0 : dX[o + 1];
+                    dB[o + 1] = sw ? b0 : dB[o + 1];
+                }
+            }
+            int m = 0;
+#pragma unroll
+            for (int o = 0; o < KO; ++o) {
+                const bool need = ub[o] >= kPivotSkip64;
+                dX[o] = need ? dX[o] : -4000.0;
+                dB[o] = need ? dB[o] : 0.0;
+                m = __any(need) ? o + 1 : m;
+            }
+            m = wave_uniform(m);
+            wave_sync();                             // the window is written before it is read
+            if (m > 0) {
+                int u = 0;
+                for (; u + U <= nw; u += U) {
+                    double x[U], e[U];
+#pragma unroll
+                    for (int q = 0; q < U; ++q) x[q] = row[u + q];
+#pragma unroll
+                    for (int q = 0; q < U; ++q) e[q] = exp2_fp64(fma(x[q], dB[0], dX[0]));
+#pragma unroll
+                    for (int o = 1; o < KO; ++o) {
+                        if (o >= m) break;
+#pragma unroll
+                        for (int q = 0; q < U; ++q) e[q] += exp2_fp64(fma(x[q], dB[o], dX[o]));
+                    }
+                    double p = prod;
+#pragma unroll
+                    for (int q = 0; q < U; ++q) p = fma(p, e[q], p);
+                    expo += __builtin_amdgcn_frexp_exp(p);
+                    prod = __builtin_amdgcn_frexp_mant(p);
+                }
+                for (; u < nw; ++u) {
+                    const double x = row[u];
+                    double e = exp2_fp64(fma(x, dB[0], dX[0]));
+#pragma unroll
+                    for (int o = 1; o < KO; ++o) {
+                        if (o >= m) break;
+                        e += exp2_fp64(fma(x, dB[o], dX[o]));
+                    }
+                    const double p = fma(prod, e, prod);
+                    expo += __builtin_amdgcn_frexp_exp(p);
+                    prod = __builtin_amdgcn_frexp_mant(p);
+                }
+            }
+        }
+        // the pivots' own terms over the window
+        const double dc = c - mp;
+        const double nd = static_cast<double>(nw);
+        msum += nd * (lwp * kLog2eD) - s2 * (S2 + dc * (2.0 * S1 + nd * dc));
+    }
+    return kLn2 * (msum + static_cast<double>(expo) + log2(prod)) + plain;
+}
+
 // Sum over data j in [j0, j1) of ln sum_i w_i exp(-||y_j - mu_i||^2 / (2 sigma2)), FP64.
+// 1-D data take the pivot form where the wave has a staging row, else the
+// general form; d > 1 takes the device library's exp per term and log per datum
+// (its k*d means fill the register budget, and the product form measured slower).
 template <int K, int D>
 __device__ __forceinline__ double partial_fp64(const float* __restrict__ y, int j0, int j1,
-                                               const double (&mu)[K * D], const GmmDev& g) {
+                                               const double (&mu)[K * D], const GmmDev& g,
+                                               const PivotStage& st) {
+    if constexpr (D == 1) {
+        if (st.row != nullptr && j1 - j0 >= kPivotMin64) return pivot_fp64<K>(y, j0, j1, mu, g, st);
+        return general_fp64<K>(y, j0, j1, mu, g);
+    }
     double acc = 0.0;
     for (int j = j0; j < j1; ++j) {
         const float* yj = y + (size_t)j * D;
@@ -495,8 +734,8 @@ __device__ __forceinline__ bool near_data(double l, int n, const GmmDev& g) {
 }
 
 // The slice partial of one lane for parameters pr[0..K*D-1] (FP64 values);
-// `near` is the hint of partial_fp32 and `st` the wave's staging for the
-// pivot form; both unused in FP64.
+// `near` is the hint of partial_fp32 (unused in FP64) and `st` the wave's staging
+// for the pivot forms.
 template <int K, int D, int PREC>
 __device__ __forceinline__ double slice_partial(const float* __restrict__ y, int j0, int j1,
                                                 const double (&pr)[K * D], const GmmDev& g,
@@ -505,16 +744,16 @@ __device__ __forceinline__ double slice_partial(const float* __restrict__ y, int
     if constexpr (PREC == SMC_PREC_FP32) {
         return partial_fp32<K, D>(y, j0, j1, pr, g, near, st, form_ctr);
     } else {
-        return partial_fp64<K, D>(y, j0, j1, pr, g);
+        return partial_fp64<K, D>(y, j0, j1, pr, g, st);
     }
 }
 
 // This wave's staging row for the pivot form in a kernel of at most W waves
 // per workgroup (a static LDS array of that kernel), or nullptr where the form
-// does not apply (FP64, d > 1).
+// does not apply (d > 1).
 template <int PREC, int D, int W>
 __device__ __forceinline__ float* pivot_row() {
-    if constexpr (PREC == SMC_PREC_FP32 && D == 1) {
+    if constexpr (D == 1) {
         __shared__ __align__(16) float win[W][kPivotRow];
         return win[wave_id()];
     } else {

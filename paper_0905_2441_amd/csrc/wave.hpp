@@ -92,6 +92,31 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
+// The same scan for FP64 values (the two halves moved by one DPP each).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_add_step(double v) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, ROW_MASK, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, ROW_MASK, 0xf,
+                                               true);
+    const long long o = (static_cast<long long>(hi) << 32) |
+                        static_cast<long long>(static_cast<unsigned>(lo));
+    return v + __builtin_bit_cast(double, o);
+}
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+    v = dpp_add_step<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_add_step<0x112, 0xf>(v);   // row_shr:2
+    v = dpp_add_step<0x114, 0xf>(v);   // row_shr:4
+    v = dpp_add_step<0x118, 0xf>(v);   // row_shr:8
+    v = dpp_add_step<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add_step<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), 63);
+    const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), 63);
+    return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) |
+                                          static_cast<long long>(static_cast<unsigned>(lo)));
+}
+
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));

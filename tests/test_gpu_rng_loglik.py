@@ -306,6 +306,60 @@ def test_loglik_fp32_pivot_form(smc, ctx, case):
         ctx.set_slices(0)
 
 
+@pytest.mark.parametrize("case", ["near", "far", "mixed", "k1", "k2", "k8", "unsorted",
+                                  "refused", "outliers", "zero_weights", "unnormalised",
+                                  "slice_7", "slice_8", "slice_9", "slice_63", "slice_64",
+                                  "slice_65", "slice_67", "slice_127", "slice_129", "one_datum"])
+def test_loglik_fp64_pivot_form(smc, ctx, case):
+    """The FP64 pivot form (1-D data, windows of 64 data in blocks of 4) at 4
+    slices: slices on either side of the shortest it takes (8), of a block and of
+    a window; near and far particles; windows refused because components lie far
+    away on both sides of them ("refused", unordered data, outliers), which take
+    the general form; components of zero weight and weights of total mass above
+    one. A datum's log carries the rounding of its exponents, below 2^-52 times
+    the largest exponent a window may hold (250, 6e-14), so 1e-12 of a
+    log-likelihood of order one per datum covers it."""
+    announce(f"loglik fp64 pivot {case}")
+    mu = np.array([-3.0, 0.0, 3.0, 6.0])
+    g = smc.Gmm.equal_weights(4, 1, 0.55)
+    n, N = 700, 200
+    if case.startswith("slice_"):
+        n = 4 * int(case[6:])
+    elif case == "one_datum":
+        n = 1
+    y = np.sort(make_mixture_data(n, mu, 0.55, seed=53))
+    near = theta_near_posterior(N, mu, seed=52)
+    far = theta_prior_draws(N, 4, 1, seed=54)
+    th = np.where(np.arange(N) % 5 == 3, far, near)
+    if case == "near":
+        th = near
+    elif case == "far":
+        th = far
+    elif case in ("k1", "k2", "k8"):
+        k = int(case[1:])
+        g = smc.Gmm.equal_weights(k, 1, 0.55)
+        th = np.hstack([theta_prior_draws(64, k, 1, seed=55),
+                        0.2 * theta_prior_draws(64, k, 1, seed=56)])
+    elif case == "unsorted":
+        y = make_mixture_data(n, mu, 0.55, seed=53)
+    elif case == "refused":
+        th = np.stack([np.full(N, -900.0), np.full(N, 900.0), np.linspace(-400.0, 400.0, N),
+                       np.full(N, 903.0)])
+    elif case == "outliers":
+        y = y.copy()
+        y[300:340] = 4.0e4
+    elif case == "zero_weights":
+        g = smc.Gmm(k=4, d=1, sigma2=0.55, log_w=(float("-inf"), math.log(0.3), math.log(0.7),
+                                                  float("-inf")))
+    elif case == "unnormalised":
+        g = smc.Gmm(k=4, d=1, sigma2=0.55, log_w=(0.0, 0.0, 0.0, 0.0))
+    ctx.set_slices(4)
+    try:
+        _check_loglik(smc, ctx, g, y, th, "fp64", FP64_TOL)
+    finally:
+        ctx.set_slices(0)
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_loglik_nan_raises_status(smc, ctx, prec):
     announce(f"loglik NaN status {prec}")
