@@ -169,7 +169,9 @@ int smc_set_launch_table(smc_ctx ctx, const smc_launch_rule* rules, int32_t coun
  * prec FP64: for d = 1 the pivot form described below in FP64 (windows of 64
  * data, exponent differences up to 250, terms below 2^-58 of a factor left out,
  * one log per slice), windows it refuses in a max-shifted product form; for
- * d > 1 an exp per term and a log per datum (relative error below 1e-12);
+ * d = 8 the quadratic forms as one FP64 matrix contraction about a centre of
+ * the data (the population-MCMC calls and a move that cannot have its scratch
+ * take an exp per term and a log per datum); relative error below 1e-12;
  * FP32: FP32 arithmetic in base 2 with hardware exp2, no per-datum log: each
  * datum's mixture sum is multiplied into a running FP32 product that is
  * renormalised by frexp after every block of 8 or 16 data, its exponents added

@@ -198,6 +198,16 @@ int choose_dd_slices(const smc_ctx_s* ctx, const GmmDev& g, int64_t n, int64_t N
     return T > 0 ? dd_clamp_slices(n, T) : dd_slices(n, N);
 }
 
+// Slices of the FP64 matrix form: as choose_dd_slices, within the fixed partials
+// (a single slice needs none: its partials share an array of the move).
+constexpr int64_t kDd64PartCap = int64_t{kMaxGroups} * kSplitCap;
+
+int choose_dd64_slices(const smc_ctx_s* ctx, const GmmDev& g, int64_t n, int64_t N) {
+    int64_t T = ctx->slices_override;
+    if (T <= 0) T = table_slices(ctx, g, SMC_PREC_FP64, n, N);
+    return dd64_slices(n, N, T, kDd64PartCap);
+}
+
 int ensure_scratch(smc_ctx ctx, int64_t N, int64_t kd, hipStream_t s) {
     if (ctx->sc.cap >= N && ctx->grow_kd >= kd) return SMC_OK;
     if (capturing(s))
@@ -231,6 +241,16 @@ int ensure_scratch(smc_ctx ctx, int64_t N, int64_t kd, hipStream_t s) {
     ctx->sc.cap = cap;
     ctx->grow_kd = kdc;
     return SMC_OK;
+}
+
+// Whether the scratch of N particles of kd parameters is there or could be had
+// (no growth inside a capture); leaves no error behind.
+bool have_scratch(smc_ctx ctx, int64_t N, int64_t kd, hipStream_t s) {
+    if (ctx->sc.cap >= N && ctx->grow_kd >= kd) return true;
+    if (capturing(s)) return false;
+    if (ensure_scratch(ctx, N, kd, s) == SMC_OK) return true;
+    (void)hipGetLastError();
+    return false;
 }
 
 // Scratch of the MFMA form: data rows [n_pad][64] bf16, particle-component
@@ -434,6 +454,13 @@ int smc_loglik(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n,
         if (e != hipSuccess) return hip_fail(e, "MFMA loglik launch");
         return SMC_OK;
     }
+    if (dd64_takes(g, prec)) {
+        const int S = choose_dd64_slices(ctx, g, n, N);
+        const hipError_t e = launch_dd64_loglik(g, y, n, theta, N, S == 1 ? loglik : ctx->sc.mv_part,
+                                                S, loglik, ctx->sc.status, s);
+        if (e != hipSuccess) return hip_fail(e, "FP64 MFMA loglik launch");
+        return SMC_OK;
+    }
     const hipError_t e = launch_loglik(g, y, n, theta, N, prec, loglik,
                                        choose_slices(ctx, g, prec, n, N), ctx->sc.status, s);
     if (e != hipSuccess) return hip_fail(e, "loglik launch");
@@ -481,6 +508,18 @@ int smc_rwmh_move(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n,
                                n_accept, ctx->sc.mm_cols, ctx->sc.mm_prop, ctx->sc.mm_part,
                                choose_dd_slices(ctx, g, n, N), ctx->sc.status, MoveStep{}, s);
         if (e != hipSuccess) return hip_fail(e, "MFMA rwmh launch");
+        return SMC_OK;
+    }
+    // the FP64 matrix form keeps the proposals in the context scratch: a call that
+    // cannot have it (a capture before it was reserved, no memory) takes the VALU form
+    if (dd64_takes(g, prec) && have_scratch(ctx, N, g.k * g.d, as_stream(stream))) {
+        const int S = choose_dd64_slices(ctx, g, n, N);
+        const hipError_t e = launch_dd64_rwmh(
+            g, y, n, theta, loglik, N, beta_vec, host_src(static_cast<int>(step), beta, 0.0),
+            step_sd, seed, move, n_accept, ctx->sc.theta_tmp,
+            S == 1 ? ctx->sc.l_tmp : ctx->sc.mv_part, S, ctx->sc.status, MoveStep{},
+            as_stream(stream));
+        if (e != hipSuccess) return hip_fail(e, "FP64 MFMA rwmh launch");
         return SMC_OK;
     }
     const hipError_t e = launch_rwmh(g, y, n, theta, loglik, N, beta_vec,
@@ -651,10 +690,11 @@ int smc_step(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n, int64
     }
     int chunk, nchunks;
     cdf_layout(N, &chunk, &nchunks);
-    if (mfma) {
+    const bool mfma64 = dd64_takes(g, prec);
+    if (mfma || mfma64) {
         e = launch_search_gather(ctx->sc, N, ctx->scheme, seed, later, ctx->sc.state, theta_in,
                                  ctx->sc.theta_tmp, kd, loglik_in, ctx->sc.l_tmp, logw, 0, s);
-        if (e == hipSuccess) e = launch_dd_prep(g, y, n, ctx->sc.mm_rows, s);
+        if (mfma && e == hipSuccess) e = launch_dd_prep(g, y, n, ctx->sc.mm_rows, s);
         if (e != hipSuccess) return hip_fail(e, "gather launch");
     }
     const Split sp = choose_split(ctx, g, prec, n, N, true);
@@ -664,7 +704,7 @@ int smc_step(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n, int64
     first.state = ctx->sc.state;
     first.W_out = W;
     first.logw = logw;
-    if (mfma) {
+    if (mfma || mfma64) {
         first.theta_alt = ctx->sc.theta_tmp;
         first.l_alt = ctx->sc.l_tmp;
     } else {
@@ -676,6 +716,20 @@ int smc_step(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n, int64
         first.nchunks = nchunks;
         first.seed = seed;
         first.scheme = ctx->scheme;
+    }
+    if (mfma64) {
+        // the first move goes out of place, its proposals into the output
+        // population; later ones keep theirs in the gather buffer, read no more
+        const int S = choose_dd64_slices(ctx, g, n, N);
+        for (int m = 0; m < n_moves; ++m) {
+            double* part = S > 1 ? ctx->sc.mv_part : m == 0 ? loglik_out : ctx->sc.l_tmp;
+            e = launch_dd64_rwmh(g, y, n, theta_out, loglik_out, N, nullptr, later, step_sd, seed,
+                                 static_cast<uint32_t>(m), n_accept,
+                                 m == 0 ? theta_out : ctx->sc.theta_tmp, part, S, ctx->sc.status,
+                                 m == 0 ? first : MoveStep{}, s);
+            if (e != hipSuccess) return hip_fail(e, "FP64 MFMA rwmh launch");
+        }
+        return SMC_OK;
     }
     if (!mfma) {
         e = launch_rwmh_moves(g, y, n, theta_out, loglik_out, N, later, step_sd, seed, n_moves,
@@ -710,7 +764,8 @@ int smc_steps(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n, int6
     constexpr int64_t kFusedTiles = static_cast<int64_t>(sizeof(double)) * kMaxGroups * kSplitCap /
                                     static_cast<int64_t>(sizeof(RwPartial));
     const Split sp = choose_split(ctx, g, prec, n, N, true);
-    const bool fuse = prec != SMC_PREC_BF16X3 && rwmh_moves_chainable(g, n_moves, sp) &&
+    const bool fuse = prec != SMC_PREC_BF16X3 && !dd64_takes(g, prec) &&
+                      rwmh_moves_chainable(g, n_moves, sp) &&
                       n_steps >= 2 && tiles <= kFusedTiles;
     if (!fuse) {
         for (int32_t i = 0; i < n_steps; ++i) {

@@ -154,6 +154,7 @@ k_dd_build(const double* __restrict__ theta, int N, int K, GmmDev g, double s2, 
 #pragma unroll
         for (int c = 0; c < kDdDim; ++c) theta_prop[static_cast<size_t>(i * kDdDim + c) * N + p] = mu[c];
     }
+    if (B == nullptr) return;              // the FP64 form reads the proposals themselves
     const __bf16 zero = static_cast<__bf16>(0.0f);
     const __bf16 one = static_cast<__bf16>(1.0f);
     bf16x8 sh, sm, sl, s6, s7;
@@ -312,9 +313,257 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
     if (grp == 0 && p < N) part[static_cast<size_t>(slice) * N + p] = v;
 }
 
+// ---------------------------------------------------------------- FP64 form
+//
+// The same contraction on the FP64 matrix instruction (v_mfma_f64_16x16x4_f64),
+// for the d-dimensional FP64 likelihood: with a centre c of the data,
+//   a_{j,i} = u_j . (mu_i - c) + (C_i - Y_j),  u_j = 2 s2 (y_j - c),
+//   C_i = log2 w_i - s2 ||mu_i - c||^2,  Y_j = s2 ||y_j - c||^2,
+// two instructions of K = 4 per component, started from C_i - Y_j. Lane l holds
+// row (l mod 16) of A, column (l mod 16) of B at K element l / 16, and the four
+// results of rows (l / 16) + 4 r of its column; A row a carries data row
+// 4 (a mod 4) + a / 4 of the tile, so that a lane's results are data rows
+// 4 (l / 16) + r. One component's results are consumed (exp2, add) before the
+// next one's need a register, so a wave holds its particles' means (4 VGPRs per
+// component) where the VALU form keeps all k*d of a particle per lane: at
+// k = d = 8 those 128 VGPRs spilled, and the VALU form took 32.7 ms at
+// N = 16384, n = 65536 against 6.1 ms here.
+//
+// Bound by FP64 issue: per (datum, particle) k = 8 components of 8 multiply-adds
+// on the matrix unit and 16 instructions of exp2, its start and its sum (5.7 ms
+// at the 5.8 cycles an FP64 instruction measured). Held to 3 waves per SIMD:
+// 6.1 ms, against 6.6 at the 2 that the compiler's own choice of registers
+// allows and 7.6 at 4 (spills).
+//
+// The expansion loses 2^-53 of Y_j per datum, so the centre (the mean of up to
+// 64 data spread over the array, the same in every workgroup) keeps Y_j small
+// for data far from the origin, and tiles holding a datum with Y_j above
+// kDd64MaxY, a datum that is not finite, or a particle with a mean that is not
+// finite take the difference form (no expansion, plain FP64). Waves with a
+// particle so far away that a datum's sum falls below 2^-1000 take each datum's
+// largest exponent out first.
+constexpr int kDd64Rows = 128;                         // data rows per LDS stage
+constexpr double kDd64MaxY = 4096.0;
+constexpr double kDd64MinC = -1.0e8;
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <int K>
+__global__ void __launch_bounds__(kDdBlock, 3)
+k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmDev g, double s2,
+               int S, double* part) {
+    __shared__ double su[2][kDd64Rows * kDdDim];
+    __shared__ __align__(16) double sy[2][kDd64Rows];
+    __shared__ double cen[kDdDim];
+    const int lane = lane_id();
+    const int w = wave_id();
+    const int kg = lane >> 4;             // K element of the operands, row group of the results
+    const int col = lane & 15;
+    const int p = blockIdx.x * 64 + w * 16 + col;
+    const int pc = p < N ? p : N - 1;
+    const int slice = blockIdx.y;
+    const int ntiles = (n + kTileRows - 1) / kTileRows;
+    const int t0 = static_cast<int>((static_cast<int64_t>(ntiles) * slice) / S);
+    const int t1 = static_cast<int>((static_cast<int64_t>(ntiles) * (slice + 1)) / S);
+
+    // the centre
+    {
+        const float* yr = y + static_cast<size_t>((static_cast<int64_t>(lane) * n) / kWave) * kDdDim;
+#pragma unroll
+        for (int c = 0; c < kDdDim; ++c) {
+            const float v = yr[c];
+            const double sum = wave_sum_dpp(fabsf(v) < 1.0e18f ? static_cast<double>(v) : 0.0);
+            if (threadIdx.x == 0) cen[c] = sum * (1.0 / kWave);
+        }
+    }
+    __syncthreads();
+    // this lane's coordinates of its particle's means about the centre
+    double b1[K], b2[K], C[K];
+    bool fine = true;
+    {
+        const double c1 = cen[kg], c2 = cen[4 + kg];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            b1[i] = th[static_cast<size_t>(i * kDdDim + kg) * N + pc] - c1;
+            b2[i] = th[static_cast<size_t>(i * kDdDim + 4 + kg) * N + pc] - c2;
+            double q = fma(b2[i], b2[i], b1[i] * b1[i]);
+            q += __shfl_xor(q, 16, kWave);
+            q += __shfl_xor(q, 32, kWave);
+            C[i] = -s2 * q;
+            fine &= C[i] >= kDd64MinC;
+            C[i] += g.lw[i] * kLog2e;              // -inf: the component is skipped
+        }
+    }
+    fine = __all(fine);
+
+    // stages: thread t brings half a data row, (t / 2, 4 coordinates)
+    const int half = threadIdx.x & 1;
+    const int srow = threadIdx.x >> 1;
+    double hc[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) hc[q] = cen[half * 4 + q];
+    float yv[4];
+    auto load_stage = [&](int st) {
+        const int row = (t0 * kTileRows) + st * kDd64Rows + srow;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            yv[q] = row < n ? y[static_cast<size_t>(row) * kDdDim + half * 4 + q] : 0.0f;
+    };
+    auto store_stage = [&](int buf) {
+        double ys = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double d = static_cast<double>(yv[q]) - hc[q];
+            ys = fma(d, d, ys);
+            su[buf][srow * kDdDim + half * 4 + q] = 2.0 * s2 * d;
+        }
+        ys += __shfl_xor(ys, 1, kWave);
+        if (half == 0) sy[buf][srow] = s2 * ys;
+    };
+    const int nst = (t1 - t0 + kDd64Rows / kTileRows - 1) / (kDd64Rows / kTileRows);
+    if (nst > 0) {
+        load_stage(0);
+        store_stage(0);
+    }
+    __syncthreads();
+
+    double prod = 1.0, msum = 0.0;
+    int expo = 0;
+    bool direct = fine && g.unit_mass != 0;
+    const int arow = 4 * (col & 3) + (col >> 2);
+    for (int st = 0; st < nst; ++st) {
+        const int buf = st & 1;
+        const bool more = st + 1 < nst;
+        if (more) load_stage(st + 1);
+        const int tile0 = t0 + st * (kDd64Rows / kTileRows);
+        const int tiles = min(kDd64Rows / kTileRows, t1 - tile0);
+        for (int tt = 0; tt < tiles; ++tt) {
+            const double* ur = &su[buf][(tt * kTileRows + arow) * kDdDim];
+            const double a1 = ur[kg], a2 = ur[4 + kg];
+            double Y[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Y[r] = sy[buf][tt * kTileRows + 4 * kg + r];
+            const int grow = (tile0 + tt) * kTileRows + 4 * kg;
+            const bool whole = (tile0 + tt + 1) * kTileRows <= n;
+            auto tile_exponents = [&](int i) {
+                f64x4 acc = {C[i] - Y[0], C[i] - Y[1], C[i] - Y[2], C[i] - Y[3]};
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1[i], acc, 0, 0, 0);
+                return __builtin_amdgcn_mfma_f64_16x16x4f64(a2, b2[i], acc, 0, 0, 0);
+            };
+            double e[4] = {0.0, 0.0, 0.0, 0.0};
+            const bool near =
+                __all(fmax(fmax(Y[0], Y[1]), fmax(Y[2], Y[3])) <= kDd64MaxY && Y[0] == Y[0] &&
+                      Y[1] == Y[1] && Y[2] == Y[2] && Y[3] == Y[3]);
+            bool done = false;
+            if (direct && near) {
+                // the next component's products are started before this one's
+                // exponentials; the fences keep the compiler from starting all K
+                f64x4 acc = tile_exponents(0);
+#pragma unroll
+                for (int i = 0; i < K; ++i) {
+                    f64x4 next = acc;
+                    if (i + 1 < K) next = tile_exponents(i + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (g.lw[i] != -INFINITY) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) e[r] += exp2_fp64(acc[r]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc = next;
+                }
+                if (!whole) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) e[r] = grow + r < n ? e[r] : 1.0;
+                }
+                done = __all(e[0] >= 0x1p-1000 && e[1] >= 0x1p-1000 && e[2] >= 0x1p-1000 &&
+                             e[3] >= 0x1p-1000);
+                direct = done;
+            }
+            if (!done) {
+                double m[4];
+                // the empty asm keeps this path's addresses and, across its two
+                // passes, its K results out of the direct path's registers
+                const double* thq = th;
+                int pq = pc;
+                asm volatile("" : "+s"(thq), "+v"(pq));
+                if (fine && near) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        m[r] = -INFINITY;
+                        e[r] = 0.0;
+                    }
+#pragma unroll 1
+                    for (int pass = 0; pass < 2; ++pass) {
+                        asm volatile("" : "+v"(Y[0]), "+v"(Y[1]), "+v"(Y[2]), "+v"(Y[3]));
+#pragma unroll
+                        for (int i = 0; i < K; ++i) {
+                            if (g.lw[i] == -INFINITY) continue;
+                            const f64x4 acc = tile_exponents(i);
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                if (pass == 0) m[r] = fmax(m[r], acc[r]);
+                                else e[r] += exp2_fp64(fmax(acc[r] - m[r], -4000.0));
+                            }
+                        }
+                    }
+                } else {
+#pragma unroll 1
+                    for (int r = 0; r < 4; ++r) {
+                        // by differences, one component at a time
+                        const int j = grow + r < n ? grow + r : n - 1;
+                        const float* yj = y + static_cast<size_t>(j) * kDdDim;
+                        double mr = -INFINITY, er = 0.0;
+#pragma unroll 1
+                        for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+                            for (int i = 0; i < K; ++i) {
+                                double d2 = 0.0;
+#pragma unroll 1
+                                for (int c = 0; c < kDdDim; ++c) {
+                                    const double t =
+                                        static_cast<double>(yj[c]) -
+                                        thq[static_cast<size_t>(i * kDdDim + c) * N + pq];
+                                    d2 = fma(t, t, d2);
+                                }
+                                const double a = g.lw[i] * kLog2e - d2 * s2;
+                                const double t = a - mr;
+                                if (pass == 0) mr = fmax(mr, a);
+                                else er += exp2_fp64(t < -4000.0 ? -4000.0 : t);
+                            }
+                        }
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            m[q] = q == r ? mr : m[q];
+                            e[q] = q == r ? er : e[q];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool in = grow + r < n;
+                    msum += in ? m[r] : 0.0;
+                    e[r] = in ? e[r] : 1.0;
+                }
+            }
+            // each factor may reach down to 2^-1000: renormalise after every one
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double q = prod * e[r];
+                expo += __builtin_amdgcn_frexp_exp(q);
+                prod = __builtin_amdgcn_frexp_mant(q);
+            }
+        }
+        if (more) store_stage(buf ^ 1);
+        __syncthreads();
+    }
+    double v = msum + static_cast<double>(expo) + log2(prod);
+    v += __shfl_xor(v, 16, kWave);
+    v += __shfl_xor(v, 32, kWave);
+    if (kg == 0 && p < N) part[static_cast<size_t>(slice) * N + p] = v;
+}
+
 __global__ void __launch_bounds__(256)
-k_dd_finish(const double* __restrict__ part, int S, int N, int n, GmmDev g,
-            double* __restrict__ out, int* status) {
+k_dd_finish(const double* part, int S, int N, int n, GmmDev g, double* out, int* status) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= N) return;
     double acc = part[p];
@@ -326,8 +575,8 @@ k_dd_finish(const double* __restrict__ part, int S, int N, int n, GmmDev g,
 
 template <int K>
 __global__ void __launch_bounds__(256)
-k_dd_accept(const double* __restrict__ part, int S, int N, int n,
-            const double* __restrict__ theta_prop, double* theta, double* l,
+k_dd_accept(const double* part, int S, int N, int n, const double* theta_prop, double* theta,
+            double* l,
             const double* __restrict__ beta_vec, StepSrc src, uint64_t seed, uint32_t move,
             GmmDev g, unsigned long long* n_acc, int* status, MoveStep ms) {
     constexpr int KD = K * kDdDim;
@@ -367,6 +616,18 @@ int dd_clamp_slices(int64_t n, int64_t S) {
 int dd_slices(int64_t n, int64_t N) {
     const int64_t groups = (N + 63) / 64;
     return dd_clamp_slices(n, (2048 + groups - 1) / groups);
+}
+
+bool dd64_takes(const GmmDev& g, int prec) { return prec == SMC_PREC_FP64 && dd_supported(g.k, g.d); }
+
+int dd64_slices(int64_t n, int64_t N, int64_t want, int64_t part_cap) {
+    const int64_t tiles = dd_padded_rows(n) / kTileRows;
+    const int64_t groups = (N + 63) / 64;
+    int64_t S = want > 0 ? want : (2048 + groups - 1) / groups;
+    if (S > 16) S = 16;
+    if (S > tiles) S = tiles;
+    if (S * N > part_cap) S = part_cap / N;
+    return static_cast<int>(S < 1 ? 1 : S);
 }
 
 bool dd_supported(int k, int d) { return d == kDdDim && (k == 1 || k == 2 || k == 4 || k == 8); }
@@ -429,6 +690,57 @@ hipError_t launch_dd_rwmh(const GmmDev& g, const __bf16* A, int64_t n, double* t
     SMC_DD(1) SMC_DD(2) SMC_DD(4) SMC_DD(8)
 #undef SMC_DD
     return hipErrorInvalidValue;
+}
+
+namespace {
+
+hipError_t launch_dd64_partial(const GmmDev& g, const float* y, int64_t n, const double* theta,
+                               int64_t N, double* part, int S, hipStream_t s) {
+    const dim3 grid(static_cast<unsigned>((N + 63) / 64), static_cast<unsigned>(S));
+#define SMC_DD(KK)                                                                              \
+    if (g.k == KK)                                                                              \
+        hipLaunchKernelGGL((k_dd64_partial<KK>), grid, dim3(kDdBlock), 0, s, y,                  \
+                           static_cast<int>(n), theta, static_cast<int>(N), g, s2_of(g), S, part);
+    SMC_DD(1) SMC_DD(2) SMC_DD(4) SMC_DD(8)
+#undef SMC_DD
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_dd64_loglik(const GmmDev& g, const float* y, int64_t n, const double* theta,
+                              int64_t N, double* part, int S, double* out, int* status,
+                              hipStream_t s) {
+    const hipError_t e = launch_dd64_partial(g, y, n, theta, N, part, S, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_dd_finish, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s,
+                       static_cast<const double*>(part), S, static_cast<int>(N),
+                       static_cast<int>(n), g, out, status);
+    return hipGetLastError();
+}
+
+hipError_t launch_dd64_rwmh(const GmmDev& g, const float* y, int64_t n, double* theta, double* l,
+                            int64_t N, const double* beta_vec, StepSrc src, double sd,
+                            uint64_t seed, uint32_t move, unsigned long long* n_accept,
+                            double* theta_prop, double* part, int S, int* status, MoveStep ms,
+                            hipStream_t s) {
+    const unsigned gb = static_cast<unsigned>((N * g.k + 255) / 256);
+    hipLaunchKernelGGL((k_dd_build<true>), dim3(gb), dim3(256), 0, s, theta, static_cast<int>(N),
+                       g.k, g, s2_of(g), ms, sd, seed, src, move, static_cast<__bf16*>(nullptr),
+                       theta_prop);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = launch_dd64_partial(g, y, n, theta_prop, N, part, S, s);
+    if (e != hipSuccess) return e;
+#define SMC_DD(KK)                                                                              \
+    if (g.k == KK)                                                                              \
+        hipLaunchKernelGGL((k_dd_accept<KK>), dim3(static_cast<unsigned>((N + 255) / 256)),      \
+                           dim3(256), 0, s, static_cast<const double*>(part), S,                 \
+                           static_cast<int>(N), static_cast<int>(n),                             \
+                           static_cast<const double*>(theta_prop), theta, l, beta_vec, src,      \
+                           seed, move, g, n_accept, status, ms);
+    SMC_DD(1) SMC_DD(2) SMC_DD(4) SMC_DD(8)
+#undef SMC_DD
+    return hipGetLastError();
 }
 
 }  // namespace smc

@@ -261,6 +261,22 @@ hipError_t launch_dd_rwmh(const GmmDev& g, const __bf16* A, int64_t n, double* t
                           __bf16* B, double* theta_prop, double* part, int S, int* status,
                           MoveStep ms, hipStream_t s);
 
+// FP64 matrix-instruction form of the d-dimensional likelihood and move: taken
+// where the model is compiled for it; `part` holds S slice partials of N
+// particles (one slice may share the output array). The move writes its
+// proposals to theta_prop, which may be the output population of an out-of-place
+// move (theta itself).
+bool dd64_takes(const GmmDev& g, int prec);
+int dd64_slices(int64_t n, int64_t N, int64_t want, int64_t part_cap);
+hipError_t launch_dd64_loglik(const GmmDev& g, const float* y, int64_t n, const double* theta,
+                              int64_t N, double* part, int S, double* out, int* status,
+                              hipStream_t s);
+hipError_t launch_dd64_rwmh(const GmmDev& g, const float* y, int64_t n, double* theta, double* l,
+                            int64_t N, const double* beta_vec, StepSrc src, double sd,
+                            uint64_t seed, uint32_t move, unsigned long long* n_accept,
+                            double* theta_prop, double* part, int S, int* status, MoveStep ms,
+                            hipStream_t s);
+
 // Reweight pass and its one-block finalisation. With t_dev set (fused step)
 // the finaliser also records t in the step state and advances the counter.
 hipError_t launch_reweight(const Scratch& sc, double* logw, const double* l, int64_t N,

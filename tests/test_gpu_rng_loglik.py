@@ -360,6 +360,89 @@ def test_loglik_fp64_pivot_form(smc, ctx, case):
         ctx.set_slices(0)
 
 
+@pytest.mark.parametrize("case", ["n1", "n15", "n16", "n17", "n127", "n129", "N1", "N17", "N65",
+                                  "far", "outliers", "offset", "infinite_mean", "zero_weight",
+                                  "unnormalised", "slices5"])
+@pytest.mark.parametrize("k", [1, 2, 4, 8])
+def test_loglik_fp64_ddim_matrix_form(smc, ctx, k, case):
+    """The FP64 matrix form (d = 8): partial tiles of 16 data and stages of 128,
+    partial columns of particles, particles far enough that each datum's largest
+    exponent is taken out first, data so far from the centre (or means not
+    finite) that their tiles go by differences, data far from the origin,
+    components of zero weight. A datum's exponent carries 2^-53 of at most 4096
+    about the centre (under 5e-13, of either sign, against a log density of order
+    10 per datum), so 1e-12 relative covers it."""
+    announce(f"loglik fp64 ddim k={k} {case}")
+    rng = np.random.default_rng(61)
+    mu = 3.0 * rng.standard_normal((k, 8))
+    n = int(case[1:]) if case[0] == "n" else 300
+    N = int(case[1:]) if case[0] == "N" else 70
+    y = make_mixture_data(n, mu, 1.0, seed=62)
+    g = smc.Gmm.equal_weights(k, 8, 1.0)
+    th = theta_near_posterior(N, mu, seed=63)
+    if case == "far":
+        th = np.where(np.arange(N) % 4 == 1, 60.0 + theta_prior_draws(N, k, 8, seed=64), th)
+    elif case == "outliers":
+        y = y.copy()
+        y[100:104] += 3000.0
+    elif case == "offset":
+        y = (y + 1024.0).astype(np.float32)
+        th = th + 1024.0
+    elif case == "infinite_mean":
+        if k == 1:
+            pytest.skip("the only component would have density zero")
+        th = th.copy()
+        th[:8, 5] = np.inf
+    elif case == "zero_weight":
+        if k == 1:
+            pytest.skip("one component of weight one")
+        g = smc.Gmm(k=k, d=8, sigma2=1.0,
+                    log_w=(float("-inf"),) + tuple([math.log(1.0 / (k - 1))] * (k - 1)))
+    elif case == "unnormalised":
+        g = smc.Gmm(k=k, d=8, sigma2=1.0, log_w=tuple([0.5] * k))
+    ctx.set_slices(5 if case == "slices5" else 0)
+    try:
+        _check_loglik(smc, ctx, g, y, th, "fp64", FP64_TOL)
+    finally:
+        ctx.set_slices(0)
+
+
+@pytest.mark.parametrize("k,n,N", [(1, 40, 65), (2, 130, 64), (4, 17, 3), (8, 300, 130)])
+def test_rwmh_fp64_ddim_matrix_form(smc, k, n, N):
+    """FP64 moves at d = 8 equal the oracle's; captured on a context without the
+    scratch their proposals need, a move takes the VALU form with the same
+    decisions."""
+    announce(f"rwmh fp64 ddim k={k} n={n} N={N}")
+    rng = np.random.default_rng(71)
+    mu = 3.0 * rng.standard_normal((k, 8))
+    y = make_mixture_data(n, mu, 1.0, seed=72)
+    g = smc.Gmm.equal_weights(k, 8, 1.0)
+    om = oracle_model(g)
+    th = theta_near_posterior(N, mu, seed=73)
+    l = ogmm.loglik(th, y, om)
+    rt, rl, _ = osmc.rwmh_move(th, l, y, om, 0.2, 0.1, 9, 4, 0)
+    yd = torch.as_tensor(y).cuda()
+    for captured in (False, True):
+        c = smc.Context(0)
+        t, ll = torch.as_tensor(th).cuda(), torch.as_tensor(l).cuda()
+        s = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        if captured:
+            from paper_0905_2441_amd.api import Graph
+            graph = Graph(c, s)
+            with graph:
+                smc.smc_rwmh_move(c, g, yd, t, ll, 0.2, 0.1, 9, 4, prec="fp64", stream=s)
+            graph.launch()
+        else:
+            smc.smc_rwmh_move(c, g, yd, t, ll, 0.2, 0.1, 9, 4, prec="fp64", stream=s)
+        s.synchronize()
+        c.check(s)
+        assert np.max(np.abs(t.cpu().numpy() - rt)) <= 1e-11
+        assert np.max(rel_err(ll.cpu().numpy(), rl)) <= FP64_TOL
+        if captured:
+            graph.close()
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_loglik_nan_raises_status(smc, ctx, prec):
     announce(f"loglik NaN status {prec}")
