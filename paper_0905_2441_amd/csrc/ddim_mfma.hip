@@ -39,6 +39,19 @@
 // (16 KB stages, double-buffered, 16-byte slots XOR-swizzled by row to spread
 // the banks) and shared by the 4 waves. Slices of the data go to different
 // workgroups; their partial sums are combined in slice order by a second kernel.
+//
+// Bound by VALU issue (the matrix instructions run beside it): per 16 x 16 tile
+// and k = 8, 32 exp2 at two issue slots, 28 adds and 16 issues of the matrix
+// unit in the direct form, 0.85 ms at N = 16384, n = 65536 (1.26 ms in the
+// shifted form with its maxima and differences). Measured 1.03 and 1.38 ms
+// (1.28 and 1.61 before): the direct form consumes one component's results at a
+// time with the next one's products in flight, so the results stay out of the
+// accumulation registers (32 moves a tile), four exp2 go before their four adds
+// (an exp2 result needs a slot before its use), a whole tile carries no per-row
+// bounds test, and the stages are loaded from memory straight into LDS, which
+// leaves room for 4 waves per SIMD. Recomputing the products in the shifted form
+// instead of holding all k results was slower (1.78 ms), and so was a larger
+// register budget at 3 waves (1.42 ms shifted).
 #include "gmm_common.hpp"
 
 namespace smc {
@@ -186,12 +199,12 @@ k_dd_build(const double* __restrict__ theta, int N, int K, GmmDev g, double s2, 
 }
 
 template <int K>
-__global__ void __launch_bounds__(kDdBlock)
+__global__ void __launch_bounds__(kDdBlock, 4)
 k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __restrict__ B, int N,
              int S, int unit_mass, double* __restrict__ part) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[2][kStageBytes];
     const int lane = lane_id();
-    const int w = wave_id();
+    const int w = wave_uniform(wave_id());
     const int grp = lane >> 4;            // K group of this lane: slots grp and 4 + grp
     const int col = lane & 15;            // particle column within the wave's tile
     const int p = blockIdx.x * 64 + w * 16 + col;
@@ -219,36 +232,30 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
     bool direct = unit_mass != 0;
     constexpr float kFloor = 0x1p-100f;
     const int nst = (t1 - t0 + kStageTiles - 1) / kStageTiles;
-    uint4 regs[4];
-    auto load_stage = [&](int st) {
+    // a stage goes from memory straight into LDS, 16 bytes a lane: each load
+    // fills 64 consecutive slots of LDS, so the swizzle is on the source (slot q
+    // of row q / 8 holds the row's slot (q mod 8) ^ (row mod 8)); rows past the
+    // slice repeat its last one and are not read
+    auto load_stage = [&](int st, int buf) {
         const int row0 = (t0 + st * kStageTiles) * kTileRows;
-        const int rows_avail = min(kStageRows, t1 * kTileRows - row0);
+        const int last = t1 * kTileRows - 1 - row0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int q = threadIdx.x * 4 + k;
-            const int row = q >> 3, sl = q & 7;
-            regs[k] = (row < rows_avail)
-                          ? *reinterpret_cast<const uint4*>(A + static_cast<size_t>(row0 + row) * kRowElems + sl * 8)
-                          : make_uint4(0u, 0u, 0u, 0u);
+            const int q0 = (k * 4 + w) * kWave;
+            const int row = (q0 + lane) >> 3;
+            const int sl = (lane & 7) ^ (row & 7);
+            const __bf16* src =
+                A + static_cast<size_t>(row0 + min(row, last)) * kRowElems + sl * 8;
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)src,
+                (__attribute__((address_space(3))) void*)&lds[buf][q0 * 16], 16, 0, 0);
         }
     };
-    auto store_stage = [&](int buf) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int q = threadIdx.x * 4 + k;
-            const int row = q >> 3, sl = q & 7;
-            *reinterpret_cast<uint4*>(&lds[buf][row * kRowBytes + ((sl ^ (row & 7)) << 4)]) = regs[k];
-        }
-    };
-    if (nst > 0) {
-        load_stage(0);
-        store_stage(0);
-    }
+    if (nst > 0) load_stage(0, 0);
     __syncthreads();
     for (int st = 0; st < nst; ++st) {
         const int buf = st & 1;
-        const bool more = st + 1 < nst;
-        if (more) load_stage(st + 1);
+        if (st + 1 < nst) load_stage(st + 1, buf ^ 1);
         const int tile0 = t0 + st * kStageTiles;
         const int tiles_here = min(kStageTiles, t1 - tile0);
         for (int tt = 0; tt < tiles_here; ++tt) {
@@ -257,26 +264,42 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
                 &lds[buf][row * kRowBytes + ((grp ^ (row & 7)) << 4)]);
             const bf16x8 a2 = *reinterpret_cast<const bf16x8*>(
                 &lds[buf][row * kRowBytes + (((4 + grp) ^ (row & 7)) << 4)]);
-            f32x4 acc[K];
-#pragma unroll
-            for (int i = 0; i < K; ++i) {
-                const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1[i], z, 0, 0, 0);
-                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2, b2[i], acc[i], 0, 0, 0);
-            }
+            const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+            auto exponents = [&](int i) {
+                const f32x4 h = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1[i], z, 0, 0, 0);
+                return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2, b2[i], h, 0, 0, 0);
+            };
             const int grow = (tile0 + tt) * kTileRows + grp * 4;
+            const bool whole = (tile0 + tt + 1) * kTileRows <= n;      // wave-uniform
+            float e[4];
             bool done = false;
             if (direct) {
+                float x[K][4];
+                f32x4 acc = exponents(0);
+#pragma unroll
+                for (int i = 0; i < K; ++i) {
+                    f32x4 next = acc;
+                    if (i + 1 < K) next = exponents(i + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[i][r] = __builtin_amdgcn_exp2f(acc[r]);
+                    if (i > 0) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) e[r] = i == 1 ? x[0][r] + x[1][r] : e[r] + x[i][r];
+                    } else if (K == 1) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) e[r] = x[0][r];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc = next;
+                }
+                if (!whole) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) e[r] = grow + r < n ? e[r] : 1.0f;
+                }
                 float pd = prod;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (grow + r < n) {
-                        float e = __builtin_amdgcn_exp2f(acc[0][r]);
-#pragma unroll
-                        for (int i = 1; i < K; ++i) e += __builtin_amdgcn_exp2f(acc[i][r]);
-                        pd *= e;
-                    }
-                }
+                for (int r = 0; r < 4; ++r) pd *= e[r];
                 if (__all(pd >= kFloor)) {
                     prod = pd;
                     done = true;
@@ -285,27 +308,38 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
                 }
             }
             if (!done) {
+                f32x4 acc[K];
+#pragma unroll
+                for (int i = 0; i < K; ++i) acc[i] = exponents(i);
+                float m[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    m[r] = acc[0][r];
+#pragma unroll
+                    for (int i = 1; i < K; ++i) m[r] = fmaxf(m[r], acc[i][r]);
+                    e[r] = __builtin_amdgcn_exp2f(acc[0][r] - m[r]);
+#pragma unroll
+                    for (int i = 1; i < K; ++i) e[r] += __builtin_amdgcn_exp2f(acc[i][r] - m[r]);
+                }
+                if (!whole) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        m[r] = grow + r < n ? m[r] : 0.0f;
+                        e[r] = grow + r < n ? e[r] : 1.0f;
+                    }
+                }
                 float mblk = 0.0f;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    if (grow + r < n) {
-                        float m = acc[0][r];
-#pragma unroll
-                        for (int i = 1; i < K; ++i) m = fmaxf(m, acc[i][r]);
-                        float e = __builtin_amdgcn_exp2f(acc[0][r] - m);
-#pragma unroll
-                        for (int i = 1; i < K; ++i) e += __builtin_amdgcn_exp2f(acc[i][r] - m);
-                        prod *= e;
-                        mblk += m;
-                    }
+                    prod *= e[r];
+                    mblk += m[r];
                 }
                 msum += static_cast<double>(mblk);
             }
             expo += __builtin_amdgcn_frexp_expf(prod);
             prod = __builtin_amdgcn_frexp_mantf(prod);
         }
-        if (more) store_stage(buf ^ 1);
-        __syncthreads();
+        __syncthreads();                  // the next stage has arrived, this one is read
     }
     double v = msum + static_cast<double>(expo) + log2(static_cast<double>(prod));
     v += __shfl_xor(v, 16, kWave);

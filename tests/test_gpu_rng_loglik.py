@@ -122,6 +122,21 @@ def test_loglik_ddim_mfma_parity(smc, ctx, k, n, N):
     _check_loglik(smc, ctx, g, y, th, "bf16x3", FP32_TOL)
 
 
+@pytest.mark.parametrize("k", [1, 8])
+@pytest.mark.parametrize("n,N", [(1, 17), (15, 64), (16, 65), (17, 63), (127, 1), (128, 130),
+                                 (129, 16), (2049, 80)])
+def test_loglik_ddim_mfma_tile_edges(smc, ctx, k, n, N):
+    """The MFMA form at the edges of its 16-row tiles and 128-row stages and of
+    its 16- and 64-particle columns, near particles (direct form) and far ones
+    (shifted) apart."""
+    announce(f"mfma edges k={k} n={n} N={N}")
+    mu = 3.0 * np.random.default_rng(81).standard_normal((k, 8))
+    y = make_mixture_data(n, mu, 1.0, seed=82)
+    g = smc.Gmm.equal_weights(k, 8, 1.0)
+    for th in (theta_near_posterior(N, mu, seed=83), theta_prior_draws(N, k, 8, seed=84)):
+        _check_loglik(smc, ctx, g, y, th, "bf16x3", FP32_TOL)
+
+
 def test_loglik_ddim_mfma_headline_size_sampled(smc, ctx):
     """d = 8, k = 8 at the full workload size (n = 65536, N = 16384), sampled particles."""
     cfg = CONFIGS["gmm8d_k8_n65536_N16384"]
