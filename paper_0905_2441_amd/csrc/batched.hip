@@ -146,6 +146,7 @@ k_b_move(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ units,
     constexpr int KD = K;
     __shared__ double red[kBatchWaves][kWave];
     __shared__ double prs[kBatchWaves][KD][kWave];
+    __shared__ double lus[kBatchWaves][kWave];
     __shared__ int unit_sh;
     const int lane = lane_id();
     const int w = wave_uniform(threadIdx.x / kWave);
@@ -172,11 +173,12 @@ k_b_move(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ units,
         double* l_run = l + rd.p_off;
         const double* th_src = use_alt ? theta_tmp + static_cast<size_t>(KD) * rd.p_off : th_run;
         const double l_src = use_alt ? l_tmp[rd.p_off + pc] : l_run[pc];
-        // the tile's Box-Muller pairs shared out over its S waves (an idle
-        // wave of a short last unit draws none but meets the barrier)
+        // the tile's Box-Muller pairs and its log u shared out over its S waves (an
+        // idle wave of a short last unit draws none but meets the barrier)
         double pr[KD];
         block_proposals<KD>(rd.seed, static_cast<uint32_t>(pc), step, move, th_src, N, pc, sd,
-                            active ? sl : (KD + 1) / 2, S, prs[grp], pr);
+                            active ? sl : (KD + 1) / 2 + 1, S, prs[grp], pr, nullptr, nullptr,
+                            nullptr, lus[grp]);
         double part = 0.0;
         if (active) {
             int j0, j1;
@@ -189,9 +191,7 @@ k_b_move(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ units,
         if (active && sl == 0) {
             bool acc = false;
             if (p < N) {
-                double tot = red[w][lane];
-                for (int q = 1; q < S; ++q) tot += red[w + q][lane];
-                const double l_prop = finish_loglik<PREC>(tot, n, g);
+                const double l_prop = finish_loglik<PREC>(sum_slices(red + w, S), n, g);
                 MoveStep ms{};
                 if (first) {
                     ms.theta_alt = theta_tmp + static_cast<size_t>(KD) * rd.p_off;
@@ -202,7 +202,8 @@ k_b_move(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ units,
                 }
                 const MoveSource srcs = move_source(ms, th_run, l_run);
                 acc = rwmh_accept<KD>(p, p, N, [&](int c) { return pr[c]; }, l_prop, srcs, th_run,
-                                      l_run, nullptr, src, step, rd.seed, move, g, status, ms);
+                                      l_run, nullptr, src, step, rd.seed, move, g, status, ms,
+                                      nullptr, &lus[grp][lane]);
             }
             const unsigned long long mask = __ballot(acc);
             if (lane == 0 && n_acc != nullptr && mask != 0ull)

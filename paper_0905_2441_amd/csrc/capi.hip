@@ -108,8 +108,7 @@ int check_model(const smc_gmm* m, GmmDev* out) {
     g.prior = m->prior;
     g.pa = m->prior_a;
     g.pb = m->prior_b;
-    g.lp_const = (m->prior == SMC_PRIOR_GAUSS) ? -0.5 * log(2.0 * M_PI * m->prior_b * m->prior_b)
-                                               : 0.0;
+    g.inv2pb2 = m->prior == SMC_PRIOR_GAUSS ? 1.0 / (2.0 * m->prior_b * m->prior_b) : 0.0;
     *out = g;
     return SMC_OK;
 }

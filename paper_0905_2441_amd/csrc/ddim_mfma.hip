@@ -274,22 +274,17 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
             float e[4];
             bool done = false;
             if (direct) {
-                float x[K][4];
                 f32x4 acc = exponents(0);
 #pragma unroll
                 for (int i = 0; i < K; ++i) {
                     f32x4 next = acc;
                     if (i + 1 < K) next = exponents(i + 1);
                     __builtin_amdgcn_sched_barrier(0);
+                    float x[4];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) x[i][r] = __builtin_amdgcn_exp2f(acc[r]);
-                    if (i > 0) {
+                    for (int r = 0; r < 4; ++r) x[r] = __builtin_amdgcn_exp2f(acc[r]);
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) e[r] = i == 1 ? x[0][r] + x[1][r] : e[r] + x[i][r];
-                    } else if (K == 1) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) e[r] = x[0][r];
-                    }
+                    for (int r = 0; r < 4; ++r) e[r] = i == 0 ? x[r] : e[r] + x[r];
                     __builtin_amdgcn_sched_barrier(0);
                     acc = next;
                 }

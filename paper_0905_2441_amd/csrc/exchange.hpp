@@ -100,6 +100,30 @@ __device__ __forceinline__ bool pt_swap_given(double* theta, double* l, const do
     return true;
 }
 
+// pt_swap_given on LDS-resident states of KD coordinates: every value is read
+// before any is written, so the reads do not wait on one another's stores.
+template <int KD>
+__device__ __forceinline__ bool pt_swap_local(double* theta, double* l, const double* beta, int M,
+                                              int a, int b, double log_u) {
+    const double la_ = l[a], lb_ = l[b];
+    const double la = (beta[a] - beta[b]) * (lb_ - la_);
+    if (!(la >= 0.0 || log_u < la)) return false;
+    double xa[KD], xb[KD];
+#pragma unroll
+    for (int c = 0; c < KD; ++c) {
+        xa[c] = theta[c * M + a];
+        xb[c] = theta[c * M + b];
+    }
+    l[a] = lb_;
+    l[b] = la_;
+#pragma unroll
+    for (int c = 0; c < KD; ++c) {
+        theta[c * M + a] = xb[c];
+        theta[c * M + b] = xa[c];
+    }
+    return true;
+}
+
 // The exchange decision of pair (a, b) with the uniform of its own stream.
 __device__ __forceinline__ bool pt_swap(double* theta, double* l, const double* beta, int M,
                                         int kd, int a, int b, uint64_t seed, uint32_t it) {

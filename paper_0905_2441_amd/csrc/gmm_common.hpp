@@ -748,6 +748,25 @@ __device__ __forceinline__ double slice_partial(const float* __restrict__ y, int
     }
 }
 
+// The S slice partials of a lane's particle, added in slice order. Four rows are
+// read before the first is added, so an addition does not wait on an LDS read of
+// its own (a loop of single reads and adds took about 140 cycles a slice on the
+// one wave that decides).
+__device__ __forceinline__ double sum_slices(const double (*red)[kWave], int S) {
+    const int lane = lane_id();
+    double tot = 0.0;
+    for (int q = 0; q < S; q += 4) {
+        double v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = red[q + i < S ? q + i : S - 1][lane];
+        tot = q == 0 ? v[0] : tot + v[0];
+#pragma unroll
+        for (int i = 1; i < 4; ++i)
+            if (q + i < S) tot += v[i];
+    }
+    return tot;
+}
+
 // This wave's staging row for the pivot form in a kernel of at most W waves
 // per workgroup (a static LDS array of that kernel), or nullptr where the form
 // does not apply (d > 1).
@@ -761,6 +780,11 @@ __device__ __forceinline__ float* pivot_row() {
     }
 }
 
+// log u of the acceptance test of particle p, u from stream (p, 0, step, ACC, move).
+__device__ __forceinline__ double rwmh_log_u(uint32_t p, uint32_t step, uint64_t seed, uint32_t move) {
+    return log(u01_open(draw(seed, p, 0, step, kAcc, move).w0));
+}
+
 // Random-walk proposals th_src[:, a] + sd * z for the 64 particles of a
 // workgroup. The ceil(KD/2) Box-Muller pairs of each particle are shared out
 // over the block's nw waves (pair q: Philox block q/2, words 0-1 for even q and
@@ -770,7 +794,9 @@ __device__ __forceinline__ float* pivot_row() {
 // current state is kept in LDS for the decision as well: hold[c] (KD rows of 64
 // doubles) gets th_src[c, a] and hold_l the current log-likelihood l_src[a]
 // (read by the block's last wave), so the decision after the likelihood does
-// not wait on global loads.
+// not wait on global loads. With log_u set, log_u[lane] gets the log u of the
+// move's acceptance test, one more item beside the pairs: the decision then
+// starts from it instead of drawing it on one wave while the others are done.
 template <int KD>
 __device__ __forceinline__ void block_proposals(uint64_t seed, uint32_t index, uint32_t step,
                                                 uint32_t move, const double* th_src, int N,
@@ -778,10 +804,16 @@ __device__ __forceinline__ void block_proposals(uint64_t seed, uint32_t index, u
                                                 double (*prs)[kWave], double (&pr)[KD],
                                                 double (*hold)[kWave] = nullptr,
                                                 const double* l_src = nullptr,
-                                                double* hold_l = nullptr) {
+                                                double* hold_l = nullptr,
+                                                double* log_u = nullptr) {
+    constexpr int NP = (KD + 1) / 2;
     const int lane = lane_id();
     if (hold != nullptr && w == nw - 1) hold_l[lane] = l_src[a];
-    for (int q = w; q < (KD + 1) / 2; q += nw) {
+    for (int q = w; q < NP + (log_u != nullptr ? 1 : 0); q += nw) {
+        if (q == NP) {
+            log_u[lane] = rwmh_log_u(index, step, seed, move);
+            break;
+        }
         const int c = 2 * q;
         const double t0 = th_src[static_cast<size_t>(c) * N + a];
         const double t1 = c + 1 < KD ? th_src[static_cast<size_t>(c + 1) * N + a] : 0.0;
@@ -869,24 +901,24 @@ __device__ __forceinline__ void fused_ancestors(const MoveStep& ms, int N, uint3
 // Metropolis-Hastings log acceptance ratio for particle p of a random-walk
 // move: log alpha = beta (l' - l) + log p0(theta') - log p0(theta).
 // cur_at(c) / pr_at(c) return coordinate c of the current state / proposal;
-// the prior terms are accumulated coordinate by coordinate in index order.
+// the prior's squares are summed in index order.
 template <int KD, class PropAt, class CurAt>
 __device__ __forceinline__ double rwmh_log_alpha(int p, PropAt pr_at, CurAt cur_at, double l_cur,
                                                  double l_prop, const double* beta_vec,
                                                  const StepSrc& src, uint32_t step,
                                                  const GmmDev& g) {
-    double lp_cur, lp_prop;
+    // log p0(theta') - log p0(theta): the normalising constants cancel
+    double lp;
     if (g.prior == SMC_PRIOR_GAUSS) {
-        const double den = 2.0 * g.pb * g.pb;
-        lp_cur = 0.0;
-        lp_prop = 0.0;
+        double sq_cur = 0.0, sq_prop = 0.0;
 #pragma unroll
         for (int c = 0; c < KD; ++c) {
             const double zc = cur_at(c) - g.pa;
             const double zp = pr_at(c) - g.pa;
-            lp_cur += g.lp_const - (zc * zc) / den;
-            lp_prop += g.lp_const - (zp * zp) / den;
+            sq_cur = fma(zc, zc, sq_cur);
+            sq_prop = fma(zp, zp, sq_prop);
         }
+        lp = (sq_cur - sq_prop) * g.inv2pb2;
     } else {
         bool in_cur = true, in_prop = true;
 #pragma unroll
@@ -896,28 +928,24 @@ __device__ __forceinline__ double rwmh_log_alpha(int p, PropAt pr_at, CurAt cur_
             in_cur = in_cur && (xc >= g.pa) && (xc <= g.pb);
             in_prop = in_prop && (xp >= g.pa) && (xp <= g.pb);
         }
-        const double inside = -static_cast<double>(KD) * log(g.pb - g.pa);
-        lp_cur = in_cur ? inside : -INFINITY;
-        lp_prop = in_prop ? inside : -INFINITY;
+        lp = (in_prop ? 0.0 : -INFINITY) - (in_cur ? 0.0 : -INFINITY);
     }
     const double beta = beta_vec ? beta_vec[p]
                                  : (src.beta_dev ? src.beta_dev[step] : src.beta_host);
-    return beta * (l_prop - l_cur) + (lp_prop - lp_cur);
+    return beta * (l_prop - l_cur) + lp;
 }
 
-// log u of the acceptance test of particle p, u from stream (p, 0, step, ACC, move).
-__device__ __forceinline__ double rwmh_log_u(int p, uint32_t step, uint64_t seed, uint32_t move) {
-    return log(u01_open(draw(seed, static_cast<uint32_t>(p), 0, step, kAcc, move).w0));
-}
-
-// Metropolis-Hastings decision: accept iff log alpha >= 0 or log u < log alpha.
+// Metropolis-Hastings decision: accept iff log alpha >= 0 or log u < log alpha
+// (log u drawn here, or already drawn at *log_u).
 template <int KD, class PropAt, class CurAt>
 __device__ __forceinline__ bool rwmh_decide(int p, PropAt pr_at, CurAt cur_at, double l_cur,
                                             double l_prop, const double* beta_vec,
                                             const StepSrc& src, uint32_t step, uint64_t seed,
-                                            uint32_t move, const GmmDev& g) {
+                                            uint32_t move, const GmmDev& g,
+                                            const double* log_u = nullptr) {
     const double la = rwmh_log_alpha<KD>(p, pr_at, cur_at, l_cur, l_prop, beta_vec, src, step, g);
-    return (la >= 0.0) || (rwmh_log_u(p, step, seed, move) < la);
+    if (log_u != nullptr) return (la >= 0.0) || (*log_u < la);
+    return (la >= 0.0) || (rwmh_log_u(static_cast<uint32_t>(p), step, seed, move) < la);
 }
 
 // The step duties of a move's first launch: publish W (1/N after resampling)
@@ -944,9 +972,10 @@ __device__ __forceinline__ bool rwmh_accept_state(int p, int N, PropAt pr_at, Cu
                                                   const double* beta_vec, const StepSrc& src,
                                                   uint32_t step, uint64_t seed, uint32_t move,
                                                   const GmmDev& g, int* status,
-                                                  const MoveStep& ms, double* l_new = nullptr) {
+                                                  const MoveStep& ms, double* l_new = nullptr,
+                                                  const double* log_u = nullptr) {
     const bool acc = rwmh_decide<KD>(p, pr_at, cur_at, l_cur, l_prop, beta_vec, src, step, seed,
-                                     move, g);
+                                     move, g, log_u);
     if (acc) {
 #pragma unroll
         for (int c = 0; c < KD; ++c) theta[static_cast<size_t>(c) * N + p] = pr_at(c);
@@ -970,12 +999,13 @@ __device__ __forceinline__ bool rwmh_accept(int p, int a, int N, PropAt pr_at, d
                                             const double* beta_vec, const StepSrc& src,
                                             uint32_t step, uint64_t seed, uint32_t move,
                                             const GmmDev& g, int* status, const MoveStep& ms,
-                                            double* l_new = nullptr) {
+                                            double* l_new = nullptr,
+                                            const double* log_u = nullptr) {
     const double* th_src = srcs.th;
     return rwmh_accept_state<KD>(
         p, N, pr_at, [&](int c) { return th_src[static_cast<size_t>(c) * N + a]; }, srcs.l[a],
         l_prop, srcs.write_always, theta, l, beta_vec, src, step, seed, move, g, status, ms,
-        l_new);
+        l_new, log_u);
 }
 
 }  // namespace smc

@@ -78,9 +78,7 @@ k_loglik(const float* __restrict__ y, int n, const double* __restrict__ theta, i
     red[w][lane] = slice_partial<K, D, PREC>(y, j0, j1, pr, g, true, PivotStage{row});
     __syncthreads();
     if (w == 0 && p < N) {
-        double acc = red[0][lane];
-        for (int s = 1; s < S; ++s) acc += red[s][lane];
-        const double l = finish_loglik<PREC>(acc, n, g);
+        const double l = finish_loglik<PREC>(sum_slices(red, S), n, g);
         out[p] = l;
         if (l != l) atomicOr(status, kStatusNaN);
     }
@@ -125,6 +123,7 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
     __shared__ double prs[KD][kWave];
     __shared__ double hold[kHold ? KD : 1][kWave];
     __shared__ double hold_l[kWave];
+    __shared__ double lus[kWave];
     // LDS sized by the launch (rwmh_dyn_lds_bytes): for 1-D data the
     // waves' staging rows [S][kPivotRow] floats, then offh, offl [nch] (nch =
     // ms.nchunks when the move can resample, else 0)
@@ -159,7 +158,8 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
 
     double pr[KD];
     block_proposals<KD>(seed, static_cast<uint32_t>(pc), step, move, srcs.th, N, a, sd, w, S, prs,
-                        pr, kHold && G == 1 ? hold : nullptr, srcs.l, hold_l);
+                        pr, kHold && G == 1 ? hold : nullptr, srcs.l, hold_l,
+                        G == 1 ? lus : nullptr);
     red[w][lane] = slice_partial<K, D, PREC>(y, j0, j1, pr, g, near_data(srcs.l[a], n, g),
                                              PivotStage{row, y_first, y_pre}, g_fp32_form_ctr);
     __syncthreads();
@@ -168,9 +168,7 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
     if (G > 1) {
         // this group's share; k_rwmh_accept adds the groups and decides
         if (p < N) {
-            double tot = red[0][lane];
-            for (int s = 1; s < S; ++s) tot += red[s][lane];
-            part[static_cast<size_t>(grp) * N + p] = tot;
+            part[static_cast<size_t>(grp) * N + p] = sum_slices(red, S);
             if (grp == 0 && fused) anc_out[p] = a;
         }
         return;
@@ -181,18 +179,16 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
     bool acc = false;
     double l_new = 0.0;
     if (p < N) {
-        double tot = red[0][lane];
-        for (int s = 1; s < S; ++s) tot += red[s][lane];
-        const double l_prop = finish_loglik<PREC>(tot, n, g);
+        const double l_prop = finish_loglik<PREC>(sum_slices(red, S), n, g);
         if constexpr (kHold) {
             acc = rwmh_accept_state<KD>(
                 p, N, [&](int c) { return pr[c]; }, [&](int c) { return hold[c][lane]; },
                 hold_l[lane], l_prop, srcs.write_always, theta, l, beta_vec, src, step, seed,
-                move, g, status, ms, CHAIN ? &l_new : nullptr);
+                move, g, status, ms, CHAIN ? &l_new : nullptr, &lus[lane]);
         } else {
             acc = rwmh_accept<KD>(p, a, N, [&](int c) { return pr[c]; }, l_prop, srcs, theta, l,
                                   beta_vec, src, step, seed, move, g, status, ms,
-                                  CHAIN ? &l_new : nullptr);
+                                  CHAIN ? &l_new : nullptr, &lus[lane]);
         }
     }
     const unsigned long long mask = __ballot(acc);
@@ -207,31 +203,45 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
 // logw are written once at the end. The moves of a particle use only its own
 // state, so this equals n_moves separate launches bit for bit. CHAIN: as in
 // k_rwmh, the next step's reweight after the last move.
+//
+// The random numbers (the normals and the log u of the acceptance test) do not
+// depend on the state, so none is drawn between a likelihood and its decision.
+// The first S waves hold a data slice each. With further waves (launched while
+// the tiles are too few to fill the chip) those draw move m + 1's numbers while
+// the others evaluate move m, into the other of two LDS buffers (`batch` is 2);
+// without, all S waves draw `batch` moves' numbers at a time.
+// Bound, for few tiles, by the latency of one move: the slice's data on one wave
+// (about 150 cycles each at k = 4), then the decision. N = 8192, n = 100: 35.5 us
+// for a step of ten moves, 44.4 us when each move drew its normals before its
+// likelihood and its log u after it.
 template <int K, int D, int PREC, bool CHAIN>
 __global__ void __launch_bounds__(1024)
 k_rwmh_multi(const float* __restrict__ y, int n, double* theta, double* l, int N, StepSrc src,
-             double sd, uint64_t seed, uint32_t move0, int n_moves, GmmDev g,
+             double sd, uint64_t seed, uint32_t move0, int n_moves, int S, int batch, GmmDev g,
              unsigned long long* n_acc, int* status, MoveStep ms) {
     constexpr int KD = K * D;
+    constexpr int NP = (KD + 1) / 2;            // Box-Muller pairs per particle
     constexpr bool kRows = D == 1;
     __shared__ double red[kMaxSlices][kWave];
     __shared__ int anc[kWave];
-    __shared__ double prs[KD][kWave];
     __shared__ double cur[KD][kWave];
     __shared__ double lcur[kWave];
-    // LDS sized by the launch (rwmh_dyn_lds_bytes), as in k_rwmh
+    // LDS sized by the launch (multi_dyn_lds_bytes): the staging rows and chunk
+    // offsets as in k_rwmh, then the random numbers [batch][KD + 1][64]
     extern __shared__ __align__(16) double lds[];
-    const int S = wave_uniform(blockDim.x / kWave);
+    S = wave_uniform(S);
+    const int nw = wave_uniform(blockDim.x / kWave);
     const int nch = ms.cdf_hi != nullptr ? ms.nchunks : 0;
     double* offh = lds + (kRows ? S * (kPivotRow / 2) : 0);
     double* offl = offh + nch;
+    double* rnd = offl + nch;
     const int lane = lane_id();
     const int w = wave_uniform(threadIdx.x / kWave);
-    float* row = kRows ? reinterpret_cast<float*>(lds) + w * kPivotRow : nullptr;
+    float* row = kRows && w < S ? reinterpret_cast<float*>(lds) + w * kPivotRow : nullptr;
     const int p = static_cast<int>(blockIdx.x) * kWave + lane;
     const int pc = p < N ? p : N - 1;
     int j0, j1;
-    slice_bounds(n, w, S, j0, j1);
+    slice_bounds(n, w < S ? w : 0, S, j0, j1);
     const uint32_t step = static_cast<uint32_t>(step_index(src));
     const bool fused = (ms.cdf_hi != nullptr) && (ms.state != nullptr) && (ms.state->resampled != 0);
     if (fused) fused_ancestors(ms, N, step, pc, anc, offh, offl);
@@ -242,23 +252,48 @@ k_rwmh_multi(const float* __restrict__ y, int n, double* theta, double* l, int N
         for (int c = 0; c < KD; ++c) cur[c][lane] = srcs.th[static_cast<size_t>(c) * N + a];
         lcur[lane] = srcs.l[a];
     }
-    __syncthreads();
+    // item q of a move's numbers: a Box-Muller pair or the log u
+    auto draw_item = [&](int m, int slot, int q) {
+        const uint32_t mv = move0 + static_cast<uint32_t>(m);
+        double* r = rnd + (slot * (KD + 1)) * kWave + lane;
+        if (q == NP) {
+            r[KD * kWave] = rwmh_log_u(static_cast<uint32_t>(pc), step, seed, mv);
+            return;
+        }
+        const Words4 wd = draw(seed, static_cast<uint32_t>(pc), static_cast<uint32_t>(q / 2), step,
+                               kProp, mv);
+        double z0, z1;
+        box_muller((q & 1) ? wd.w2 : wd.w0, (q & 1) ? wd.w3 : wd.w1, z0, z1);
+        r[2 * q * kWave] = z0;
+        if (2 * q + 1 < KD) r[(2 * q + 1) * kWave] = z1;
+    };
+    const int drawers = nw - S;
     unsigned long long accepted = 0;
     for (int m = 0; m < n_moves; ++m) {
-        const uint32_t mv = move0 + static_cast<uint32_t>(m);
+        const int slot = drawers > 0 ? m & 1 : m % batch;
+        if (drawers > 0 ? m == 0 : slot == 0) {
+            const int mb = drawers > 0 ? 1 : n_moves - m < batch ? n_moves - m : batch;
+            for (int it = w; it < mb * (NP + 1); it += nw)
+                draw_item(m + it / (NP + 1), it / (NP + 1), it % (NP + 1));
+            __syncthreads();
+        }
+        const double* r = rnd + (slot * (KD + 1)) * kWave + lane;
         double pr[KD];
-        block_proposals<KD>(seed, static_cast<uint32_t>(pc), step, mv, &cur[0][0], kWave, lane, sd,
-                            w, S, prs, pr);
-        red[w][lane] = slice_partial<K, D, PREC>(y, j0, j1, pr, g, near_data(lcur[lane], n, g),
-                                                 PivotStage{row});
+        if (w < S) {
+#pragma unroll
+            for (int c = 0; c < KD; ++c) pr[c] = cur[c][lane] + sd * r[c * kWave];
+            red[w][lane] = slice_partial<K, D, PREC>(y, j0, j1, pr, g,
+                                                     near_data(lcur[lane], n, g), PivotStage{row});
+        } else if (m + 1 < n_moves) {
+            for (int q = w - S; q < NP + 1; q += drawers) draw_item(m + 1, slot ^ 1, q);
+        }
         __syncthreads();
         if (w == 0) {
-            double tot = red[0][lane];
-            for (int q = 1; q < S; ++q) tot += red[q][lane];
-            const double l_prop = finish_loglik<PREC>(tot, n, g);
+            const double l_prop = finish_loglik<PREC>(sum_slices(red, S), n, g);
             const bool acc = rwmh_decide<KD>(
                 pc, [&](int c) { return pr[c]; }, [&](int c) { return cur[c][lane]; }, lcur[lane],
-                l_prop, nullptr, src, step, seed, mv, g);
+                l_prop, nullptr, src, step, seed, move0 + static_cast<uint32_t>(m), g,
+                r + KD * kWave);
             if (acc) {
 #pragma unroll
                 for (int c = 0; c < KD; ++c) cur[c][lane] = pr[c];
@@ -285,26 +320,40 @@ k_rwmh_multi(const float* __restrict__ y, int n, double* theta, double* l, int N
 
 // Data (floats) the one-launch population-MCMC kernel stages in LDS.
 constexpr int kPtLocalData = 2048;
+// Waves of its form with drawing waves: 12 leave 168 registers a lane, where 16
+// leave 128 and the decisions waited on spilled values (2.98 us per
+// iteration at 32 chains and 96 data, 2.86 with 168).
+constexpr int kPtAheadWaves = 12;
 
 // Several population-MCMC iterations in one launch of one workgroup, for
 // populations small enough that every chain's state fits in LDS. The
-// workgroup's waves are `tiles` 64-chain tiles x S data slices. An iteration
-// has three phases separated by barriers:
-//   1. every wave forms its tile's proposals (state + sd * the normals held in
-//      LDS) and sums its data slice;
+// workgroup's first waves are `tiles` 64-chain tiles x S data slices. An
+// iteration has three phases separated by barriers:
+//   1. every such wave forms its tile's proposals (state + sd * the normals held
+//      in LDS) and sums its data slice;
 //   2. the first wave of each tile adds the slices and decides each chain's
-//      move at its own beta, while the tile's other waves draw the next
-//      iteration's random numbers (normals, log u of the acceptance and
-//      exchange tests, the partition parity) into LDS;
-//   3. the workgroup takes the iteration's exchanges on the LDS states.
+//      move at its own beta;
+//   3. the workgroup takes the iteration's exchanges on the LDS states (with one
+//      tile its first wave does, right after its decisions, between its lanes'
+//      registers and without the barrier between).
+// The next iteration's random numbers (normals, log u of the acceptance and
+// exchange tests, the partition parity) go into the other of two LDS buffers
+// meanwhile: AHEAD, by further waves of the workgroup that do nothing else, the
+// first half of an item (Philox and the log) in phase 1 and the rest in phase 2;
+// else (populations whose LDS has no room for a second buffer of normals, or
+// whose slices take all 16 waves) by the tile's other waves during phase 2.
+// Bound by the latency of one iteration's chain: at the paper's 32 chains and
+// 100 data, cycle counters gave 2400 cycles for a slice of 12-13 data, 1600 for
+// the decisions and 1500 for the exchanges on LDS, and the drawing of 3300 in
+// phase 2 held both up; 2.87 us per iteration now, 3.88 us then.
 // The chains' states, their betas and (when n d <= kPtLocalData) the data
 // stay in LDS for the whole launch.
 // The random numbers are drawn from the same streams and with the same
 // arithmetic as in separate iterations, so the results (bit for bit, for the
 // same slicing) equal those of n_iters pt_iteration calls. The iteration
 // index is read once from the caller's counter, which ends advanced by n_iters.
-template <int K, int D, int PREC, int MAXC>
-__global__ void __launch_bounds__(1024)
+template <int K, int D, int PREC, int MAXC, bool AHEAD>
+__global__ void __launch_bounds__(AHEAD ? kWave * kPtAheadWaves : 1024)
 k_pt_local(const float* __restrict__ y, int n, double* theta, double* l, int M,
            const double* __restrict__ beta, int* it_dev, int n_iters, double sd, uint64_t seed,
            int parity_mode, int wrap, int S, GmmDev g, unsigned long long* n_acc,
@@ -312,97 +361,176 @@ k_pt_local(const float* __restrict__ y, int n, double* theta, double* l, int M,
     constexpr int KD = K * D;
     constexpr int NP = (KD + 1) / 2;            // Box-Muller pairs per chain
     constexpr int NITEM = NP + 2;               // + the acceptance and exchange uniforms
+    constexpr int NZ = AHEAD ? 2 : 1;           // buffers of normals
     __shared__ double red[kMaxSlices][kWave];
     __shared__ double cur[KD][MAXC];
-    __shared__ double zs[KD][MAXC];             // the coming iteration's normals
+    __shared__ double zs[NZ][KD][MAXC];         // the coming iteration's normals
     __shared__ double lcur[MAXC];
     __shared__ double lua[2][MAXC];             // log u of the acceptance tests
     __shared__ double lux[2][MAXC];             // log u of the exchange led by each chain
     __shared__ double lbeta[MAXC];
     __shared__ float ys[kPtLocalData];          // the data, when they fit
     __shared__ int par[2];
+    S = wave_uniform(S);
     const int lane = lane_id();
     const int w = wave_uniform(threadIdx.x / kWave);
-    const int tile = w / S;
-    const int sl = w - tile * S;
+    const int nw = wave_uniform(blockDim.x / kWave);
+    const int tiles = (M + kWave - 1) / kWave;
+    const bool worker = w < tiles * S;            // holds a tile's data slice
+    const int tile = worker ? w / S : 0;
+    const int sl = worker ? w - tile * S : -1;
     const int col = tile * kWave + lane;          // chain held by this lane
     const int cc = col < M ? col : M - 1;
     int j0, j1;
-    slice_bounds(n, sl, S, j0, j1);
-    // random items of chain col for iteration it, items first, first + stride, ...
-    auto draw_items = [&](uint32_t it, int buf, int first, int stride) {
-        for (int i = first; i < NITEM; i += stride) {
-            if (i < NP) {
-                const Words4 wd = draw(seed, static_cast<uint32_t>(cc), static_cast<uint32_t>(i / 2),
-                                       it, kProp, 0);
-                double z0, z1;
-                if (i & 1) box_muller(wd.w2, wd.w3, z0, z1);
-                else box_muller(wd.w0, wd.w1, z0, z1);
-                zs[2 * i][col] = z0;
-                if (2 * i + 1 < KD) zs[2 * i + 1][col] = z1;
-            } else if (i == NP) {
-                lua[buf][col] = rwmh_log_u(cc, it, seed, 0);
-            } else {
-                lux[buf][col] = pt_log_u(cc, seed, it);
-                if (col == 0) par[buf] = pt_parity(parity_mode, 0, seed, it);
-            }
+    slice_bounds(n, worker ? sl : 0, S, j0, j1);
+    // Random item i of the chains of tile tl for iteration it, in two halves: the
+    // words and the log every item needs, then what follows from them.
+    struct Half {
+        double log_u;
+        uint32_t wb;
+    };
+    auto draw_first = [&](int tl, uint32_t it, int i) {
+        const int dc = tl * kWave + lane;
+        const uint32_t chain = static_cast<uint32_t>(dc < M ? dc : M - 1);
+        const uint32_t purpose = i < NP ? kProp : i == NP ? kAcc : kExch;
+        const Words4 wd = draw(seed, chain, i < NP ? static_cast<uint32_t>(i / 2) : 0u, it,
+                               purpose, 0);
+        const bool high = i < NP && (i & 1) != 0;
+        return Half{log(u01_open(high ? wd.w2 : wd.w0)), high ? wd.w3 : wd.w1};
+    };
+    auto draw_rest = [&](int tl, uint32_t it, int buf, int i, const Half& h) {
+        const int dc = tl * kWave + lane;
+        if (i < NP) {
+            double z0, z1;
+            box_muller_log(h.log_u, h.wb, z0, z1);
+            double (*z)[MAXC] = zs[AHEAD ? buf : 0];
+            z[2 * i][dc] = z0;
+            if (2 * i + 1 < KD) z[2 * i + 1][dc] = z1;
+        } else if (i == NP) {
+            lua[buf][dc] = h.log_u;
+        } else {
+            lux[buf][dc] = h.log_u;
+            if (dc == 0) par[buf] = pt_parity(parity_mode, 0, seed, it);
         }
     };
+    auto draw_item = [&](int tl, uint32_t it, int buf, int i) {
+        draw_rest(tl, it, buf, i, draw_first(tl, it, i));
+    };
     const int it0 = *it_dev;
+    double be = 0.0;                              // the lane's chain's beta (first waves)
     if (sl == 0) {
 #pragma unroll
         for (int c = 0; c < KD; ++c) cur[c][col] = theta[static_cast<size_t>(c) * M + cc];
         lcur[col] = l[cc];
-        lbeta[col] = beta[cc];
+        be = beta[cc];
+        lbeta[col] = be;
     }
     const bool stage = static_cast<int64_t>(n) * D <= kPtLocalData;
     if (stage)
         for (int i = threadIdx.x; i < n * D; i += blockDim.x) ys[i] = y[i];
     const float* yl = stage ? ys : y;
-    draw_items(static_cast<uint32_t>(it0), 0, sl, S);
+    for (int i = w; i < tiles * NITEM; i += nw)
+        draw_item(i / NITEM, static_cast<uint32_t>(it0), 0, i % NITEM);
     __syncthreads();
+    // the lane's partner under either parity (itself when single) and which of
+    // the two leads their pair
+    int other0 = lane, other1 = lane, lead0 = 0, lead1 = 0;
+    if (tiles == 1 && sl == 0 && lane < M) {
+        int a = 0, b = 0;
+        if (pt_pair_of(M, 0, wrap, lane, a, b)) {
+            other0 = lane == a ? b : a;
+            lead0 = lane == a;
+        }
+        if (pt_pair_of(M, 1, wrap, lane, a, b)) {
+            other1 = lane == a ? b : a;
+            lead1 = lane == a;
+        }
+    }
+    // a drawing wave's items and the last of them, whose second half falls into
+    // phase 2
+    const int d0 = w - tiles * S, dn = nw - tiles * S;
+    const int last = AHEAD && !worker ? d0 + (tiles * NITEM - 1 - d0) / dn * dn : 0;
     unsigned long long accepted = 0;
     unsigned swaps = 0;
     for (int m = 0; m < n_iters; ++m) {
         const uint32_t it = static_cast<uint32_t>(it0 + m);
         const int buf = m & 1;
-        double pr[KD];
+        const bool draws = m + 1 < n_iters;
+        double pr[KD], cu[KD], lc = 0.0;
+        Half half{};
+        if (worker) {
+            lc = lcur[col];
 #pragma unroll
-        for (int c = 0; c < KD; ++c) pr[c] = cur[c][col] + sd * zs[c][col];
-        // the same per-datum forms as the one-launch-per-iteration path, so the
-        // two agree bit for bit
-        red[w][lane] = slice_partial<K, D, PREC>(yl, j0, j1, pr, g, near_data(lcur[col], n, g),
-                                                 PivotStage{pivot_row<PREC, D, kMaxSlices>()});
+            for (int c = 0; c < KD; ++c) {
+                cu[c] = cur[c][col];
+                pr[c] = cu[c] + sd * zs[AHEAD ? buf : 0][c][col];
+            }
+            // the same per-datum forms as the one-launch-per-iteration path, so the
+            // two agree bit for bit
+            red[w][lane] = slice_partial<K, D, PREC>(
+                yl, j0, j1, pr, g, near_data(lc, n, g),
+                PivotStage{pivot_row<PREC, D, kMaxSlices>()});
+        } else if (draws) {
+            for (int i = d0; i < last; i += dn) draw_item(i / NITEM, it + 1u, buf ^ 1, i % NITEM);
+            half = draw_first(last / NITEM, it + 1u, last % NITEM);
+        }
         __syncthreads();
         if (sl == 0) {
-            double tot = red[w][lane];
-            for (int q = 1; q < S; ++q) tot += red[w + q][lane];
-            const double l_prop = finish_loglik<PREC>(tot, n, g);
+            const double lu = lua[buf][col];
+            const int parity = par[buf];
+            const int other = parity ? other1 : other0;
+            const bool lead = (parity ? lead1 : lead0) != 0;
+            const double lx = lux[buf][lead ? col : other];
+            const double l_prop = finish_loglik<PREC>(sum_slices(red + w, S), n, g);
             const double la = rwmh_log_alpha<KD>(
-                col, [&](int c) { return pr[c]; }, [&](int c) { return cur[c][col]; }, lcur[col],
-                l_prop, lbeta, StepSrc{}, it, g);
-            const bool acc = (la >= 0.0) || (lua[buf][col] < la);
-            if (acc) {
+                0, [&](int c) { return pr[c]; }, [&](int c) { return cu[c]; }, lc, l_prop, &be,
+                StepSrc{}, it, g);
+            const bool acc = (la >= 0.0) || (lu < la);
 #pragma unroll
-                for (int c = 0; c < KD; ++c) cur[c][col] = pr[c];
-                lcur[col] = l_prop;
-            }
+            for (int c = 0; c < KD; ++c) cu[c] = acc ? pr[c] : cu[c];
+            lc = acc ? l_prop : lc;
             if (col < M && l_prop != l_prop) atomicOr(status, kStatusNaN);
             accepted += static_cast<unsigned long long>(__popcll(__ballot(acc && col < M)));
+            if (tiles == 1) {
+                // the exchanges between the lanes of this wave, on registers: both
+                // chains of a pair reach the same decision and each takes the
+                // other's state
+                const double lo = __shfl(lc, other), bo = __shfl(be, other);
+                const double d = ((lead ? be : bo) - (lead ? bo : be)) *
+                                 ((lead ? lo : lc) - (lead ? lc : lo));
+                const bool swap = other != lane && (d >= 0.0 || lx < d);
+#pragma unroll
+                for (int c = 0; c < KD; ++c) {
+                    const double x = __shfl(cu[c], other);
+                    cu[c] = swap ? x : cu[c];
+                }
+                lc = swap ? lo : lc;
+                if (swap && lead) ++swaps;
+            }
+#pragma unroll
+            for (int c = 0; c < KD; ++c) cur[c][col] = cu[c];
+            lcur[col] = lc;
         }
-        if (m + 1 < n_iters) {
-            if (S == 1) draw_items(it + 1u, buf ^ 1, 0, 1);
-            else if (sl > 0) draw_items(it + 1u, buf ^ 1, sl - 1, S - 1);
+        if (draws) {
+            if (AHEAD) {
+                if (!worker) draw_rest(last / NITEM, it + 1u, buf ^ 1, last % NITEM, half);
+            } else if (S == 1) {
+                for (int i = 0; i < NITEM; ++i) draw_item(tile, it + 1u, buf ^ 1, i);
+            } else if (sl > 0) {
+                for (int i = sl - 1; i < NITEM; i += S - 1) draw_item(tile, it + 1u, buf ^ 1, i);
+            }
         }
         __syncthreads();
-        const int parity = par[buf];
-        for (int q = threadIdx.x;; q += blockDim.x) {
-            int a, b;
-            if (!pt_slot(M, parity, wrap, q, a, b)) break;
-            if (b < 0) continue;
-            if (pt_swap_given(&cur[0][0], lcur, lbeta, MAXC, KD, a, b, lux[buf][a])) ++swaps;
+        if (tiles > 1) {
+            const int parity = par[buf];
+            for (int q = threadIdx.x;; q += blockDim.x) {
+                int a, b;
+                if (!pt_slot(M, parity, wrap, q, a, b)) break;
+                if (b < 0) continue;
+                if (pt_swap_local<KD>(&cur[0][0], lcur, lbeta, MAXC, a, b, lux[buf][a])) ++swaps;
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
     if (sl == 0 && col < M) {
 #pragma unroll
@@ -438,6 +566,7 @@ k_pt_deferred(const float* __restrict__ y, int n, const double* __restrict__ th_
     __shared__ double cur[KD][kWave];
     __shared__ double prs[KD][kWave];
     __shared__ double lcur[kWave];
+    __shared__ double lus[kWave];
     // LDS sized by the launch: for 1-D data the waves' staging rows
     // [S][kPivotRow] floats
     extern __shared__ __align__(16) double lds[];
@@ -472,17 +601,15 @@ k_pt_deferred(const float* __restrict__ y, int n, const double* __restrict__ th_
     __syncthreads();
     double pr[KD];
     block_proposals<KD>(seed, static_cast<uint32_t>(pc), it, 0, &cur[0][0], kWave, lane, sd, w, S,
-                        prs, pr);
+                        prs, pr, nullptr, nullptr, nullptr, lus);
     red[w][lane] = slice_partial<K, D, PREC>(y, j0, j1, pr, g, near_data(lcur[lane], n, g),
                                              PivotStage{row});
     __syncthreads();
     if (w != 0) return;
-    double tot = red[0][lane];
-    for (int q = 1; q < S; ++q) tot += red[q][lane];
-    const double l_prop = finish_loglik<PREC>(tot, n, g);
+    const double l_prop = finish_loglik<PREC>(sum_slices(red, S), n, g);
     const bool acc = rwmh_decide<KD>(
         pc, [&](int c) { return pr[c]; }, [&](int c) { return cur[c][lane]; }, lcur[lane], l_prop,
-        beta, StepSrc{}, it, seed, 0, g);
+        beta, StepSrc{}, it, seed, 0, g, &lus[lane]);
     if (p < M) {
 #pragma unroll
         for (int c = 0; c < KD; ++c) th_out[static_cast<size_t>(c) * M + p] = acc ? pr[c] : cur[c][lane];
@@ -680,19 +807,36 @@ __global__ void k_prior(int N, uint64_t seed, GmmDev g, double* __restrict__ the
 
 namespace {
 
-// Largest dynamic LDS a k_rwmh or k_rwmh_multi launch asks for (their static
-// part is at most 8 KB + 64 KB + 768 B).
+// Largest dynamic LDS a k_rwmh launch asks for (its static part is at most
+// 8 KB + 64 KB + 1280 B).
 constexpr size_t kMaxRwmhLds = 24 * 1024;
+
+// Moves whose random numbers a k_rwmh_multi workgroup holds at once: two with
+// drawing waves, else 13 KB of them (five moves at k*d = 4), so that LDS admits as
+// many workgroups per CU as registers do.
+constexpr size_t kMultiRandomBytes = 18 * 1024;
+
+int multi_batch(int kd, int n_moves, bool drawers) {
+    const int fit = static_cast<int>(size_t{13 * 1024} / (sizeof(double) * kWave * (kd + 1)));
+    return drawers ? 2 : std::max(1, std::min(n_moves, fit));
+}
 
 // LDS bytes of the pivot forms' staging rows of `slices` waves (d = 1).
 size_t rows_lds_bytes(int slices, bool rows) {
     return rows ? sizeof(float) * slices * kPivotRow : 0;
 }
 
-// Dynamic LDS bytes of one k_rwmh / k_rwmh_multi workgroup (the layout at the
-// top of k_rwmh).
+// Dynamic LDS bytes of one k_rwmh workgroup (the layout at the top of k_rwmh).
 size_t rwmh_dyn_lds_bytes(int slices, int nchunks, bool rows) {
     return rows_lds_bytes(slices, rows) + sizeof(double) * 2 * static_cast<size_t>(nchunks);
+}
+
+// Dynamic LDS bytes of one k_rwmh_multi workgroup: k_rwmh's, then the random
+// numbers of `batch` moves.
+constexpr size_t kMaxMultiLds = kMaxRwmhLds + kMultiRandomBytes;
+size_t multi_dyn_lds_bytes(int slices, int nchunks, bool rows, int kd, int batch) {
+    return rwmh_dyn_lds_bytes(slices, nchunks, rows) +
+           sizeof(double) * kWave * static_cast<size_t>(kd + 1) * static_cast<size_t>(batch);
 }
 
 }  // namespace
@@ -828,22 +972,30 @@ hipError_t launch_rwmh_moves(const GmmDev& g, const float* y, int64_t n, double*
         }
         return hipSuccess;
     }
-    const dim3 grid(static_cast<unsigned>((N + kWave - 1) / kWave));
-    const dim3 block(static_cast<unsigned>(kWave * sp.slices));
+    const int64_t tiles = (N + kWave - 1) / kWave;
+    const dim3 grid(static_cast<unsigned>(tiles));
+    // with at most two tiles per CU, waves beyond the slices (one per random item)
+    // cost no other tile its place
+    const int items = (g.k * g.d + 1) / 2 + 1;
+    const int waves = tiles <= 512 ? std::min(kMaxSlices, sp.slices + items) : sp.slices;
+    const dim3 block(static_cast<unsigned>(kWave * waves));
     const int nch = ms.cdf_hi != nullptr ? ms.nchunks : 0;
     if (nch < 0 || nch > kMaxChunks) return hipErrorInvalidValue;
 #define SMC_MULTI(K, D, P)                                                                     \
     do {                                                                                       \
-        const size_t lds = rwmh_dyn_lds_bytes(sp.slices, nch, D == 1);   \
-        if (lds > kMaxRwmhLds) return hipErrorInvalidValue;                                    \
+        const int batch = multi_batch(K * D, n_moves, waves > sp.slices);                      \
+        const size_t lds = multi_dyn_lds_bytes(sp.slices, nch, D == 1, K * D, batch);          \
+        if (lds > kMaxMultiLds) return hipErrorInvalidValue;                                   \
         if (ms.lw_next != nullptr)                                                             \
             hipLaunchKernelGGL((k_rwmh_multi<K, D, P, true>), grid, block, lds, s, y,          \
                                static_cast<int>(n), theta, l, static_cast<int>(N), src, sd,    \
-                               seed, 0u, n_moves, g, n_accept, sc.status, ms);                 \
+                               seed, 0u, n_moves, sp.slices, batch, g, n_accept, sc.status,    \
+                               ms);                                                            \
         else                                                                                   \
             hipLaunchKernelGGL((k_rwmh_multi<K, D, P, false>), grid, block, lds, s, y,         \
                                static_cast<int>(n), theta, l, static_cast<int>(N), src, sd,    \
-                               seed, 0u, n_moves, g, n_accept, sc.status, ms);                 \
+                               seed, 0u, n_moves, sp.slices, batch, g, n_accept, sc.status,    \
+                               ms);                                                            \
     } while (0)
 #define SMC_CASE(K, D)                                                                         \
     if constexpr (K * D <= 16) {                                                               \
@@ -866,6 +1018,11 @@ constexpr int kPtLocalCap = 4096;
 constexpr int pt_local_cap(int kd) {
     return kd > 16 ? 0 : ((kPtLocalCap / kd) / kWave * kWave < 1024 ? (kPtLocalCap / kd) / kWave * kWave : 1024);
 }
+
+// Largest population of the form with waves that only draw: its second buffer of
+// normals fits LDS beside the states at every k*d, and it covers the populations
+// the automatic choice takes at n = 100 (pt_local_pays).
+constexpr int kPtAheadChains = 128;
 
 int pt_local_chains(int kd) { return kd < 1 ? 0 : pt_local_cap(kd); }
 
@@ -902,11 +1059,20 @@ hipError_t launch_pt_local(const GmmDev& g, const float* y, int64_t n, double* t
     if (S * tiles > kMaxSlices) S = kMaxSlices / tiles;
     if (S > n) S = static_cast<int>(n);
     if (S < 1) S = 1;
-    const dim3 block(static_cast<unsigned>(kWave * tiles * S));
+    // waves that only draw: one per tile and random item, as far as 16 waves go
+    const bool ahead = M <= kPtAheadChains && tiles * S < kPtAheadWaves;
+    const int items = tiles * ((kd + 1) / 2 + 2);
+    const int drawers = ahead ? std::min(kPtAheadWaves - tiles * S, items) : 0;
+    const dim3 block(static_cast<unsigned>(kWave * (tiles * S + drawers)));
+#define SMC_LOCAL_A(K, D, P, C, A)                                                             \
+    hipLaunchKernelGGL((k_pt_local<K, D, P, C, A>), dim3(1), block, 0, s, y,                   \
+                       static_cast<int>(n), theta, l, static_cast<int>(M), beta, it_dev,       \
+                       n_iters, sd, seed, parity_mode, wrap, S, g, n_accept, n_swap, status)
 #define SMC_LOCAL(K, D, P, C)                                                                  \
-    hipLaunchKernelGGL((k_pt_local<K, D, P, C>), dim3(1), block, 0, s, y, static_cast<int>(n), \
-                       theta, l, static_cast<int>(M), beta, it_dev, n_iters, sd, seed,         \
-                       parity_mode, wrap, S, g, n_accept, n_swap, status)
+    do {                                                                                       \
+        if (ahead) SMC_LOCAL_A(K, D, P, kPtAheadChains, true);                                 \
+        else SMC_LOCAL_A(K, D, P, C, false);                                                   \
+    } while (0)
 #define SMC_CASE(K, D)                                                                         \
     if constexpr (K * D <= 16) {                                                               \
         if (g.k == K && g.d == D) {                                                            \
@@ -919,6 +1085,7 @@ hipError_t launch_pt_local(const GmmDev& g, const float* y, int64_t n, double* t
     SMC_KD_CASES(SMC_CASE)
 #undef SMC_CASE
 #undef SMC_LOCAL
+#undef SMC_LOCAL_A
     return hipErrorInvalidValue;
 }
 

@@ -28,7 +28,7 @@ struct GmmDev {
     double cst;                // per-datum constant -(d/2) ln(2 pi sigma2)
     int prior;                 // SMC_PRIOR_GAUSS or SMC_PRIOR_BOX
     double pa, pb;
-    double lp_const;           // Gaussian prior: -(1/2) ln(2 pi pb^2) per coordinate
+    double inv2pb2;            // Gaussian prior: 1 / (2 pb^2)
     int unit_mass;             // sum_i w_i <= 1 (+1e-6): the FP32 form may skip the max shift
 };
 

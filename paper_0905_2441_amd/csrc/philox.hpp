@@ -129,15 +129,19 @@ __device__ __forceinline__ void sincos_0_2pi(double a, double* s, double* c) {
     *c = (q == 0) ? cx : (q == 1) ? -sx : (q == 2) ? -cx : sx;
 }
 
-// Box & Muller (1958): two independent standard normals from two uniforms.
-__device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, double& z0, double& z1) {
+// Box & Muller (1958): two independent standard normals from two uniforms, the
+// first given by its log.
+__device__ __forceinline__ void box_muller_log(double log_u, uint32_t wb, double& z0, double& z1) {
     constexpr double kTwoPi = 6.283185307179586;
-    const double r = sqrt(-2.0 * log(u01_open(wa)));
+    const double r = sqrt(-2.0 * log_u);
     const double ang = kTwoPi * u01_open(wb);
     double s, c;
     sincos_0_2pi(ang, &s, &c);
     z0 = r * c;
     z1 = r * s;
+}
+__device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, double& z0, double& z1) {
+    box_muller_log(log(u01_open(wa)), wb, z0, z1);
 }
 
 // Standard normal number c of the stream (index, step, purpose, move):

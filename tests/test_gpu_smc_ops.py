@@ -655,6 +655,58 @@ def test_pt_iterations_equal_single_iterations(smc, ctx, k, d, prec, M, slices, 
         assert s1 > 0
 
 
+@pytest.mark.parametrize("k,d,prec,M,slices,parity,wrap,iters", [
+    (4, 1, "fp32", 63, 1, 1, True, 6),       # one tile, more drawing waves than items
+    (4, 1, "fp64", 64, 11, 1, True, 6),      # a full tile, one drawing wave
+    (4, 1, "fp32", 64, 12, 1, True, 6),      # no wave left to draw
+    (8, 1, "fp32", 65, 2, 0, False, 5),      # two tiles
+    (4, 1, "fp32", 128, 5, 1, True, 5),
+    (4, 1, "fp32", 192, 3, 1, False, 5),     # past the form with drawing waves
+    (2, 8, "fp64", 128, 3, 1, True, 4),
+])
+def test_pt_iterations_drawing_waves(smc, ctx, k, d, prec, M, slices, parity, wrap, iters):
+    """The single-workgroup form at the edges of its choice of drawing waves (at
+    most 128 chains and fewer than 12 waves with a slice) and of the exchanges in
+    one wave's registers (at most 64 chains)."""
+    test_pt_iterations_equal_single_iterations(smc, ctx, k, d, prec, M, slices, parity, wrap,
+                                               iters)
+
+
+@pytest.mark.parametrize("k,d,prec,N,slices,moves", [
+    (4, 1, "fp32", 70, 3, 7), (4, 1, "fp64", 32768, 2, 3), (4, 1, "fp32", 32769, 4, 11),
+    (8, 1, "fp32", 100, 16, 3), (2, 8, "fp32", 40000, 1, 4), (1, 1, "fp64", 64, 15, 2)])
+def test_several_moves_in_one_launch_equal_single_moves(smc, ctx, k, d, prec, N, slices, moves):
+    """A step of several moves without resampling leaves the state of as many
+    smc_rwmh_move calls, bit for bit: with waves that only draw (up to 512 tiles of
+    64 particles), with the slices' waves drawing a few moves at a time (more
+    tiles, or 16 slices), and with more moves than one such batch."""
+    announce(f"moves k={k} d={d} {prec} N={N} slices={slices} moves={moves}")
+    rng = np.random.default_rng(N + k)
+    mu = rng.uniform(-4.0, 6.0, size=(k, d)) if d > 1 else np.linspace(-3.0, 6.0, k)
+    y = _cuda(make_mixture_data(90, mu, 0.55, seed=N), torch.float32)
+    g = smc.Gmm.equal_weights(k, d, 0.55)
+    th = _cuda(theta_prior_draws(N, k, d, seed=N + 1))
+    betas = _cuda(np.array([0.0, 0.05, 0.3]))
+    ctx.set_slices(slices)
+    try:
+        l = smc.smc_loglik(ctx, g, y, th, prec)
+        t1, l1 = torch.empty_like(th), torch.empty_like(l)
+        logw, W = torch.zeros_like(l), torch.empty_like(l)
+        t_dev = torch.full((1,), 2, dtype=torch.int32).cuda()
+        stats = torch.zeros(4, dtype=torch.float64).cuda()
+        na = torch.zeros(1, dtype=torch.int64).cuda()
+        smc.smc_step(ctx, g, y, th, l, t1, l1, logw, W, betas, t_dev, 0.4, moves, 77, 0.0, prec,
+                     stats, na)
+        t2, l2, nb = th.clone(), l.clone(), torch.zeros(1, dtype=torch.int64).cuda()
+        for m in range(moves):
+            smc.smc_rwmh_move(ctx, g, y, t2, l2, 0.3, 0.4, 77, 2, m, prec, nb)
+        ctx.check()
+    finally:
+        ctx.set_slices(0)
+    assert torch.equal(t1, t2) and torch.equal(l1, l2)
+    assert na.item() == nb.item() > 0
+
+
 def test_pt_iterations_matches_oracle_and_rejects_bad_count(smc, ctx):
     """Twenty iterations of 300 chains against the oracle's population MCMC
     run (FP64, alternating parity) in each of pt_iterations' forms (one
