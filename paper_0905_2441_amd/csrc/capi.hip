@@ -1257,8 +1257,14 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
         }
     }
     std::vector<BatchRun> rd(R);
-    for (int i = 0; i < R; ++i)
-        rd[i] = BatchRun{runs[i].p_off, runs[i].y_off, runs[i].N, runs[i].n, runs[i].seed};
+    std::vector<BatchChunk> chunks;
+    for (int i = 0; i < R; ++i) {
+        int chunk, nchunks;
+        cdf_layout(runs[i].N, &chunk, &nchunks);
+        rd[i] = BatchRun{runs[i].p_off, runs[i].y_off, runs[i].N, runs[i].n, runs[i].seed,
+                         chunk, nchunks, static_cast<int>(chunks.size())};
+        for (int q = 0; q < nchunks; ++q) chunks.push_back(BatchChunk{i, q});
+    }
     const size_t b_runs = align_up(sizeof(BatchRun) * R);
     const size_t b_u0 = align_up(sizeof(BatchUnit) * units[0].size());
     const size_t b_items = b_u0 + align_up(sizeof(BatchUnit) * units[1].size());
@@ -1267,7 +1273,11 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
     const size_t b_cdf = align_up(sizeof(double) * N_total);
     const size_t b_th = align_up(sizeof(double) * N_total * kd);
     const size_t b_l = align_up(sizeof(double) * N_total);
-    const size_t total = b_runs + b_items + b_work + b_state + b_cdf + b_th + b_l;
+    const size_t b_ch = align_up(sizeof(BatchChunk) * chunks.size());
+    const size_t b_part = align_up(sizeof(RwPartial) * chunks.size());
+    const size_t b_tot = align_up(sizeof(double) * 2 * chunks.size());
+    const size_t total = b_runs + b_items + b_work + b_state + 2 * b_cdf + b_th + b_l + b_ch +
+                         b_part + b_tot;
     void* p = nullptr;
     if (hipMalloc(&p, total) != hipSuccess) return fail(SMC_ERR_NOMEM, "batch allocation failed");
     smc_batch b = new (std::nothrow) smc_batch_s();
@@ -1290,12 +1300,22 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
     d.n_units[1] = static_cast<int>(units[1].size());
     d.work = reinterpret_cast<unsigned*>(c + b_runs + b_items);
     d.state = reinterpret_cast<StepState*>(c + b_runs + b_items + b_work);
-    d.cdf = reinterpret_cast<double*>(c + b_runs + b_items + b_work + b_state);
-    d.theta_tmp = reinterpret_cast<double*>(c + b_runs + b_items + b_work + b_state + b_cdf);
-    d.l_tmp = reinterpret_cast<double*>(c + b_runs + b_items + b_work + b_state + b_cdf + b_th);
+    c += b_runs + b_items + b_work + b_state;
+    d.cdf_hi = reinterpret_cast<double*>(c);
+    d.cdf_lo = reinterpret_cast<double*>(c + b_cdf);
+    d.theta_tmp = reinterpret_cast<double*>(c + 2 * b_cdf);
+    d.l_tmp = reinterpret_cast<double*>(c + 2 * b_cdf + b_th);
+    c += 2 * b_cdf + b_th + b_l;
+    d.chunks = reinterpret_cast<BatchChunk*>(c);
+    d.n_chunks = static_cast<int>(chunks.size());
+    d.part = reinterpret_cast<RwPartial*>(c + b_ch);
+    d.chunk_tot = reinterpret_cast<double*>(c + b_ch + b_part);
     d.move_grid = batch_move_grid();
     hipError_t e = hipMemset(p, 0, total);
     if (e == hipSuccess) e = hipMemcpy(d.runs, rd.data(), sizeof(BatchRun) * R, hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+        e = hipMemcpy(d.chunks, chunks.data(), sizeof(BatchChunk) * chunks.size(),
+                      hipMemcpyHostToDevice);
     for (int pi = 0; pi < 2 && e == hipSuccess; ++pi)
         e = hipMemcpy(d.units[pi], units[pi].data(), sizeof(BatchUnit) * units[pi].size(),
                       hipMemcpyHostToDevice);

@@ -49,7 +49,8 @@ __global__ void __launch_bounds__(kRedBlock)
 k_fsv_weight(FsvDev f, const double* __restrict__ y, int T, const double* __restrict__ x,
              double* __restrict__ x_out, double* __restrict__ logw, int N, StepSrc src,
              uint64_t seed, Scratch sc, double* __restrict__ mom, FsvAnc anc) {
-    __shared__ double offh[kMaxChunks], offl[kMaxChunks];
+    __shared__ double offh[kMaxChunks], offl[kMaxChunks], cend[kMaxChunks];
+    __shared__ double win[kRedBlock / kWave][kCdfWin];
     const uint32_t t = static_cast<uint32_t>(step_index(src));
     // the previous step's resampling (one value for the whole grid), searched
     // exactly as the standalone search-and-gather pass does
@@ -57,7 +58,7 @@ k_fsv_weight(FsvDev f, const double* __restrict__ y, int T, const double* __rest
     uint32_t rs_step = 0;
     double rs_u = 0.0;
     if (rs) {
-        block_cdf_offsets(anc.chunk_tot, anc.nchunks, offh, offl);
+        block_cdf_offsets(anc.chunk_tot, anc.nchunks, offh, offl, cend);
         rs_step = static_cast<uint32_t>(anc.state->t);
         if (anc.scheme == 0) rs_u = u01_left_closed(draw(seed, 0, 0, rs_step, kResamp, 0).w0);
     }
@@ -72,10 +73,20 @@ k_fsv_weight(FsvDev f, const double* __restrict__ y, int T, const double* __rest
 #pragma unroll
     for (int c = 0; c < KF; ++c) mo.sx[c] = mo.sxx[c] = 0.0;
     bool bad = false;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < N; p += gridDim.x * blockDim.x) {
-        const int a = rs ? cdf_search(resample_point(anc.scheme, seed, rs_step, p, N, rs_u), N,
-                                      anc.chunk, anc.cdf_hi, anc.cdf_lo, offh, offl)
-                         : p;
+    const CdfView cdf{N, anc.chunk, anc.nchunks, anc.cdf_hi, anc.cdf_lo, offh, offl, cend};
+    // whole waves stay in the loop while their first particle is one (a wave's
+    // points are sorted for its search); lanes past the end drop out after it
+    for (int p0 = blockIdx.x * blockDim.x + wave_id() * kWave; p0 < N;
+         p0 += gridDim.x * blockDim.x) {
+        const int p = p0 + lane_id();
+        int a = p;
+        if (rs) {
+            const double U = resample_point(anc.scheme, seed, rs_step, p < N ? p : N - 1, N, rs_u);
+            a = anc.scheme == SMC_RESAMPLE_MULTINOMIAL
+                    ? cdf_search(U, cdf)
+                    : cdf_search_sorted_wave(U, true, cdf, win[wave_id()]);
+        }
+        if (p >= N) continue;
         double z[KF];
         normals<KF>(seed, static_cast<uint32_t>(p), t, kProp, 0, z);
         double xn[KF], h[KF];

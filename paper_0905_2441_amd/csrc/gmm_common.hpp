@@ -848,15 +848,25 @@ __device__ __forceinline__ MoveSource move_source(const MoveStep& ms, double* th
     return MoveSource{th, ll, th != theta};
 }
 
-// Ancestors of the 64 particles of this workgroup after systematic resampling
+// LDS doubles of fused_ancestors: chunk offsets (two halves) and ends, then the
+// search's window row.
+__host__ __device__ constexpr int ancestor_lds_doubles(int nchunks) {
+    return nchunks > 0 ? 3 * nchunks + kCdfWin : 0;
+}
+
+// Ancestors of the 64 particles of this workgroup after resampling
 // (cooperative: every thread of the block must call it). Wave 0 forms the chunk
-// offsets in LDS (exclusive double-double scan of the chunk totals; offh and
-// offl hold ms.nchunks entries each), then each of its lanes takes the
+// offsets and ends in LDS (exclusive double-double scan of the chunk totals; buf
+// holds ancestor_lds_doubles(ms.nchunks)), then each of its lanes takes the
 // scheme's point U_i for particle i and finds idx = min{j : U < C_j} (or the
 // first j with C_j = C_{N-1}), C_j = offset + within-chunk prefix rounded once.
 __device__ __forceinline__ void fused_ancestors(const MoveStep& ms, int N, uint32_t step, int pc,
-                                                int* anc, double* offh, double* offl) {
+                                                int* anc, double* buf) {
     const int lane = lane_id();
+    double* offh = buf;
+    double* offl = offh + ms.nchunks;
+    double* cend = offl + ms.nchunks;
+    double* win = cend + ms.nchunks;
     if (wave_id() == 0) {
         // two passes over the lane's chunk totals (sum, then running offsets)
         // keep the register footprint of this prologue small
@@ -880,20 +890,19 @@ __device__ __forceinline__ void fused_ancestors(const MoveStep& ms, int N, uint3
                 offh[c] = excl.hi;
                 offl[c] = excl.lo;
                 excl = dd_add(excl, dd{ms.chunk_tot[2 * c], ms.chunk_tot[2 * c + 1]});
+                cend[c] = excl.hi;
             }
         }
-    }
-    __syncthreads();
-    if (wave_id() == 0) {
+        wave_sync();
         const double u = ms.scheme == 0 ? u01_left_closed(draw(ms.seed, 0, 0, step, kResamp, 0).w0)
                                         : 0.0;
         // pc is clamped to N - 1 past the end, so the tile's points are sorted
         // for the systematic and stratified schemes
         const double U = resample_point(ms.scheme, ms.seed, step, pc, N, u);
+        const CdfView cdf{N, ms.chunk, ms.nchunks, ms.cdf_hi, ms.cdf_lo, offh, offl, cend};
         anc[lane] = ms.scheme == SMC_RESAMPLE_MULTINOMIAL
-                        ? cdf_search(U, N, ms.chunk, ms.cdf_hi, ms.cdf_lo, offh, offl)
-                        : cdf_search_sorted_wave(U, true, N, ms.chunk, ms.cdf_hi, ms.cdf_lo, offh,
-                                                 offl);
+                        ? cdf_search(U, cdf)
+                        : cdf_search_sorted_wave(U, true, cdf, win);
     }
     __syncthreads();
 }

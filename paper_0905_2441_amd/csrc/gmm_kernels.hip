@@ -125,13 +125,11 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
     __shared__ double hold_l[kWave];
     __shared__ double lus[kWave];
     // LDS sized by the launch (rwmh_dyn_lds_bytes): for 1-D data the
-    // waves' staging rows [S][kPivotRow] floats, then offh, offl [nch] (nch =
-    // ms.nchunks when the move can resample, else 0)
+    // waves' staging rows [S][kPivotRow] floats, then fused_ancestors' buffer when
+    // the move can resample
     extern __shared__ __align__(16) double lds[];
     const int S = wave_uniform(blockDim.x / kWave);
-    const int nch = ms.cdf_hi != nullptr ? ms.nchunks : 0;
-    double* offh = lds + (kRows ? S * (kPivotRow / 2) : 0);
-    double* offl = offh + nch;
+    double* anc_lds = lds + (kRows ? S * (kPivotRow / 2) : 0);
     const int lane = lane_id();
     const int w = wave_uniform(threadIdx.x / kWave);
     float* row = kRows ? reinterpret_cast<float*>(lds) + w * kPivotRow : nullptr;
@@ -152,7 +150,7 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
     if (ms.t_out != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
         *ms.t_out = static_cast<int>(step);
     const bool fused = (ms.cdf_hi != nullptr) && (ms.state != nullptr) && (ms.state->resampled != 0);
-    if (fused) fused_ancestors(ms, N, step, pc, anc, offh, offl);
+    if (fused) fused_ancestors(ms, N, step, pc, anc, anc_lds);
     const MoveSource srcs = move_source(ms, theta, l);
     const int a = fused ? anc[lane] : pc;
 
@@ -226,15 +224,14 @@ k_rwmh_multi(const float* __restrict__ y, int n, double* theta, double* l, int N
     __shared__ int anc[kWave];
     __shared__ double cur[KD][kWave];
     __shared__ double lcur[kWave];
-    // LDS sized by the launch (multi_dyn_lds_bytes): the staging rows and chunk
-    // offsets as in k_rwmh, then the random numbers [batch][KD + 1][64]
+    // LDS sized by the launch (multi_dyn_lds_bytes): the staging rows and
+    // fused_ancestors' buffer as in k_rwmh, then the random numbers [batch][KD + 1][64]
     extern __shared__ __align__(16) double lds[];
     S = wave_uniform(S);
     const int nw = wave_uniform(blockDim.x / kWave);
     const int nch = ms.cdf_hi != nullptr ? ms.nchunks : 0;
-    double* offh = lds + (kRows ? S * (kPivotRow / 2) : 0);
-    double* offl = offh + nch;
-    double* rnd = offl + nch;
+    double* anc_lds = lds + (kRows ? S * (kPivotRow / 2) : 0);
+    double* rnd = anc_lds + ancestor_lds_doubles(nch);
     const int lane = lane_id();
     const int w = wave_uniform(threadIdx.x / kWave);
     float* row = kRows && w < S ? reinterpret_cast<float*>(lds) + w * kPivotRow : nullptr;
@@ -244,7 +241,7 @@ k_rwmh_multi(const float* __restrict__ y, int n, double* theta, double* l, int N
     slice_bounds(n, w < S ? w : 0, S, j0, j1);
     const uint32_t step = static_cast<uint32_t>(step_index(src));
     const bool fused = (ms.cdf_hi != nullptr) && (ms.state != nullptr) && (ms.state->resampled != 0);
-    if (fused) fused_ancestors(ms, N, step, pc, anc, offh, offl);
+    if (fused) fused_ancestors(ms, N, step, pc, anc, anc_lds);
     const MoveSource srcs = move_source(ms, theta, l);
     if (w == 0) {
         const int a = fused ? anc[lane] : pc;
@@ -809,7 +806,7 @@ namespace {
 
 // Largest dynamic LDS a k_rwmh launch asks for (its static part is at most
 // 8 KB + 64 KB + 1280 B).
-constexpr size_t kMaxRwmhLds = 24 * 1024;
+constexpr size_t kMaxRwmhLds = 34 * 1024;
 
 // Moves whose random numbers a k_rwmh_multi workgroup holds at once: two with
 // drawing waves, else 13 KB of them (five moves at k*d = 4), so that LDS admits as
@@ -828,7 +825,8 @@ size_t rows_lds_bytes(int slices, bool rows) {
 
 // Dynamic LDS bytes of one k_rwmh workgroup (the layout at the top of k_rwmh).
 size_t rwmh_dyn_lds_bytes(int slices, int nchunks, bool rows) {
-    return rows_lds_bytes(slices, rows) + sizeof(double) * 2 * static_cast<size_t>(nchunks);
+    return rows_lds_bytes(slices, rows) +
+           sizeof(double) * static_cast<size_t>(ancestor_lds_doubles(nchunks));
 }
 
 // Dynamic LDS bytes of one k_rwmh_multi workgroup: k_rwmh's, then the random

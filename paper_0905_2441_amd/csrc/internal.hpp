@@ -158,6 +158,12 @@ struct BatchRun {
     int64_t p_off, y_off;      // first particle / observation of the run
     int N, n;
     uint64_t seed;
+    int chunk, nchunks;        // the run's particles in CDF chunks (cdf_layout)
+    int c_off;                 // its first chunk in the batch's list of chunks
+};
+// One chunk of a run's particles: a workgroup of the reweight, scan and gather.
+struct BatchChunk {
+    int run, index;
 };
 constexpr int kBatchWaves = 8;          // waves per workgroup of the persistent batched move
 // Work unit of the persistent batched move: ntiles consecutive 64-particle
@@ -173,7 +179,12 @@ struct BatchDev {
     int n_units[2];
     unsigned* work;            // work-queue counter, zero between launches
     StepState* state;          // [R]
-    double* cdf;               // [N_total]
+    BatchChunk* chunks;        // [n_chunks] every run's chunks, run by run
+    int n_chunks;
+    RwPartial* part;           // [n_chunks] reweight partials
+    double* chunk_tot;         // [2 * n_chunks] CDF chunk totals (hi, lo)
+    double* cdf_hi;            // [N_total] within-chunk CDF prefixes
+    double* cdf_lo;            // [N_total]
     double* theta_tmp;         // [kd * N_total]
     double* l_tmp;             // [N_total]
     int move_grid;             // persistent grid size

@@ -46,6 +46,24 @@ __device__ __forceinline__ Lse3 lse3_merge(Lse3 a, Lse3 b) {
     return Lse3{b.m, b.s1 + a.s1 * r, b.s2 + a.s2 * (r * r)};
 }
 
+// The log-sum-exp of n values of one thread, about their largest: one exp each,
+// independent of one another.
+template <int n>
+__device__ __forceinline__ Lse3 lse3_of(const double (&x)[n]) {
+    double m = x[0];
+#pragma unroll
+    for (int i = 1; i < n; ++i) m = fmax(m, x[i]);
+    Lse3 r{m, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        // a NaN, which the maximum passed over, stays one; no weight at all adds none
+        const double e = m == -INFINITY && x[i] == m ? 0.0 : exp(x[i] - m);
+        r.s1 += e;
+        r.s2 = r.s2 + e * e;
+    }
+    return r;
+}
+
 // Block (kRedBlock threads) log-sum-exp; the result is valid in thread 0.
 // The block maximum is formed first, then every thread rescales its sums to it
 // with one exp and the rescaled sums are added in fixed order: one exp per

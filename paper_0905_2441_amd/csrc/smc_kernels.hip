@@ -24,6 +24,7 @@
 #include "philox.hpp"
 #include "exchange.hpp"
 #include "reduce.hpp"
+#include "cdf_scan.hpp"
 #include "cdf_search.hpp"
 
 namespace smc {
@@ -133,73 +134,6 @@ __device__ __forceinline__ bool should_fire(const ResamplePred& pr) {
 __device__ __forceinline__ double weight_at(const WeightSrc& w, int j) {
     if (w.W) return w.W[j];
     return exp(w.logw[j] - w.state->M) / w.state->S;
-}
-
-// Inclusive prefixes (double-double) of the piece [piece, piece + kRedBlock*PER)
-// clipped to `end`, offset by `carry`, stored rounded in two halves to
-// out_hi/out_lo; returns carry plus the piece's total. Each thread scans PER
-// consecutive elements, but the weights are read and the prefixes written
-// striped across the block (element e*256 + t by thread t: every wave access
-// is 512 contiguous bytes) through LDS, whose rows are padded by one double per
-// PER elements so that the per-thread runs do not fall on the same banks.
-template <int PER, class WeightAt>
-__device__ __forceinline__ dd scan_piece(int piece, int end, dd carry, double* out_hi,
-                                         double* out_lo, WeightAt weight) {
-    constexpr int kPiece = kRedBlock * PER;
-    constexpr int kPadded = kPiece + kPiece / PER;
-    __shared__ double sh_hi[kPadded], sh_lo[kPadded];
-    auto at = [](int j) { return j + j / PER; };
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        const int j = e * kRedBlock + t;
-        sh_hi[at(j)] = piece + j < end ? weight(piece + j) : 0.0;
-    }
-    __syncthreads();
-    const int base = t * PER;
-    dd pre[PER];
-    dd run = dd_zero();
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        if (piece + base + e < end) run = dd_add(run, sh_hi[at(base + e)]);
-        pre[e] = run;
-    }
-    dd total;
-    const dd excl = block_dd_exclusive_scan(run, total);     // ends with a barrier
-    const dd lead = dd_add(carry, excl);
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        const dd c = dd_add(lead, pre[e]);
-        sh_hi[at(base + e)] = c.hi;
-        sh_lo[at(base + e)] = c.lo;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        const int j = e * kRedBlock + t;
-        if (piece + j < end) {
-            out_hi[piece + j] = sh_hi[at(j)];
-            out_lo[piece + j] = sh_lo[at(j)];
-        }
-    }
-    __syncthreads();
-    return dd_add(carry, total);
-}
-
-// Within-chunk inclusive prefixes of chunk b of the fused step's layout (up to
-// kMaxChunks chunks of kScanChunk-element pieces) and the chunk's total.
-template <class WeightAt>
-__device__ __forceinline__ void scan_chunk(int b, int N, int chunk, const Scratch& sc,
-                                           WeightAt weight) {
-    const int begin = b * chunk;
-    const int end = min(N, begin + chunk);
-    dd carry = dd_zero();
-    for (int piece = begin; piece < end; piece += kScanChunk)
-        carry = scan_piece<kScanPerThread>(piece, end, carry, sc.cdf_hi, sc.cdf_lo, weight);
-    if (threadIdx.x == 0) {
-        sc.dd_part[2 * b] = carry.hi;
-        sc.dd_part[2 * b + 1] = carry.lo;
-    }
 }
 
 // Standalone resampling (smc_resample*) in three passes over chunks of
@@ -387,7 +321,8 @@ k_step_mid(int parts, int N, int chunk, StepSrc src, int* t_advance, Scratch sc,
         }
     }
     if (!sh_fire) return;
-    scan_chunk(blockIdx.x, N, chunk, sc, [&](int j) { return exp(logw[j] - M) / S; });
+    scan_chunk(blockIdx.x, N, chunk, sc.cdf_hi, sc.cdf_lo, sc.dd_part,
+               [&](int j) { return exp(logw[j] - M) / S; });
 }
 
 // Publish the normalised weights of a step that made no move.
@@ -418,8 +353,10 @@ k_search_gather(int N, int chunk, int nchunks, Scratch sc, ResamplePred pred, in
         if (l_in && l_out) l_out[i] = l_in[i];
         return;
     }
-    __shared__ double offh[kMaxChunks], offl[kMaxChunks];
-    block_cdf_offsets(sc.dd_part, nchunks, offh, offl);
+    __shared__ double offh[kMaxChunks], offl[kMaxChunks], cend[kMaxChunks];
+    __shared__ double win[kRedBlock / kWave][kCdfWin];
+    block_cdf_offsets(sc.dd_part, nchunks, offh, offl, cend);
+    const CdfView cdf{N, chunk, nchunks, sc.cdf_hi, sc.cdf_lo, offh, offl, cend};
     const uint32_t step = static_cast<uint32_t>(step_index(src));
     double u = 0.0;
     if (scheme == 0)
@@ -429,8 +366,8 @@ k_search_gather(int N, int chunk, int nchunks, Scratch sc, ResamplePred pred, in
     const int ic = i < N ? i : N - 1;
     const double U = resample_point(scheme, seed, step, ic, N, u);
     const int j = scheme == SMC_RESAMPLE_MULTINOMIAL
-                      ? cdf_search(U, N, chunk, sc.cdf_hi, sc.cdf_lo, offh, offl)
-                      : cdf_search_sorted_wave(U, true, N, chunk, sc.cdf_hi, sc.cdf_lo, offh, offl);
+                      ? cdf_search(U, cdf)
+                      : cdf_search_sorted_wave(U, true, cdf, win[wave_id()]);
     if (i >= N) return;
     if (idx_out) idx_out[i] = j;
     if (theta_in && theta_out)
@@ -520,28 +457,13 @@ k_resample_merge(int N, Scratch sc, ResamplePred pred, int scheme, uint64_t seed
     if (scheme == 0)
         u = u_override ? *u_override : u01_left_closed(draw(seed, 0, 0, step, kResamp, 0).w0);
     const double clast = cdf(N - 1);
-    auto pred_c = [&](double uu, double c) -> bool {
-        return uu < clast ? (uu < c) : (c >= clast);
-    };
+    auto pred_c = [&](double uu, double c) -> bool { return cdf_past(uu, c, clast); };
     const int i_last = min(N, i0 + kMergeTile) - 1;
     if (wave_id() == 0) {
         // lanes 0-31 search the ancestor of the tile's first point, 32-63 of its last
         const int lane = lane_id();
-        const int half = lane >> 5, hl = lane & 31;
-        const double us = resample_point(scheme, seed, step, half ? i_last : i0, N, u);
-        int lo_ = 0, hi_ = N - 1;
-        while (__any(hi_ > lo_)) {
-            const int len = hi_ - lo_ + 1;
-            const int stp = (len + 31) >> 5;
-            int q = lo_ + (hl + 1) * stp - 1;
-            q = q < hi_ ? q : hi_;
-            const unsigned long long m = __ballot(pred_c(us, cdf(q)));
-            const unsigned mh = static_cast<unsigned>(half ? (m >> 32) : (m & 0xffffffffull));
-            const int f = __ffs(mh) - 1;
-            const int nhi = lo_ + (f + 1) * stp - 1;
-            lo_ = lo_ + f * stp;
-            hi_ = nhi < hi_ ? nhi : hi_;
-        }
+        const double us = resample_point(scheme, seed, step, lane >> 5 ? i_last : i0, N, u);
+        const int lo_ = first_true_half(0, N - 1, [&](int q) { return pred_c(us, cdf(q)); });
         if (lane == 0) ab[0] = lo_;
         if (lane == 32) ab[1] = lo_;
     }
@@ -616,10 +538,12 @@ k_resample_gather(int N, Scratch sc, ResamplePred pred, int scheme, uint64_t see
     const double* __restrict__ hi = sc.cdf_hi;
     const double* __restrict__ lo = sc.cdf_lo;
     const double* __restrict__ off = sc.res_off;
-    const int j = cdf_search_fn(U, N, [&](int jj) -> double {
+    auto cdf = [&](int jj) -> double {
         const int b = jj / kResChunk;
         return dd_add(dd{off[2 * b], off[2 * b + 1]}, dd{hi[jj], lo[jj]}).hi;
-    });
+    };
+    const double clast = cdf(N - 1);
+    const int j = first_true(0, N - 1, [&](int q) { return cdf_past(U, cdf(q), clast); });
     resample_gather_point(i, j, N, idx_out, theta_in, theta_out, kd, l_in, l_out, logw);
 }
 

@@ -763,3 +763,39 @@ def test_batched_full_workload_fp32_replayed_by_oracle(smc, ctx):
     flips, decisions = _replay_batched(b, states, picked, datas, om, betas, 2 * 10 ** 7)
     assert flips <= max(3, decisions // 1000), (flips, decisions)
     print(f"batched full workload fp32: runs {picked}, flips {flips} of {decisions}")
+
+
+@pytest.mark.parametrize("scheme", ["systematic", "stratified", "multinomial"])
+def test_batched_runs_at_chunk_edges_equal_single_runs(smc, ctx, scheme):
+    """Batched runs whose sizes sit at the edges of the 2048-particle chunks that
+    the reweight, the CDF scan and the gather go by (one particle, a ragged tile,
+    one chunk, one particle more, several chunks) equal the same runs made alone,
+    in FP64: populations, counts and decisions exactly, evidence to 1e-10 (the two
+    group the same sums differently, 2^-53 per addition)."""
+    announce(f"batched chunk edges {scheme}")
+    g = smc.Gmm.equal_weights(4, 1, 0.55)
+    Ns = [1, 63, 2048, 2049, 5000]
+    datas = [make_mixture_data(30 + 20 * i, np.array([-3.0, 0.0, 3.0, 6.0]), 0.55, seed=90 + i)
+             for i in range(len(Ns))]
+    betas = beta_schedule(12, "quadratic")
+    ctx.set_slices(2)
+    ctx.set_launch_table([dict(k=4, d=1, prec="fp64", kind="batch", slices=2, n_lo=1, n_hi=1 << 20,
+                               N_lo=1, N_hi=1 << 20)])
+    try:
+        b = smc.BatchSampler(ctx, g, datas, Ns, [400 + i for i in range(len(Ns))], betas, 0.5, 1,
+                             prec="fp64", scheme=scheme)
+        rb = b.run(graph=True)
+        fired = 0
+        for i, N in enumerate(Ns):
+            s = smc.SMCSampler(ctx, g, datas[i], N, betas, 0.5, 1, 400 + i, prec="fp64",
+                               scheme=scheme)
+            r = s.run(graph=False)
+            assert np.array_equal(rb["theta"][i], r["theta"]), N
+            assert np.array_equal(rb["l"][i], r["l"]), N
+            assert rb["resamples"][i] == r["resamples"], N
+            assert abs(rb["logZ"][i] - r["logZ"]) <= 1e-10 * max(1.0, abs(r["logZ"])), N
+            fired += r["resamples"]
+        assert fired > 0
+    finally:
+        ctx.set_slices(0)
+        ctx.set_launch_table([])
