@@ -74,8 +74,7 @@ k_b_reweight(const BatchRun* __restrict__ runs, const BatchChunk* __restrict__ c
         nw = lse3_merge(nw, lse3_of(ln));
     }
     if (bad) atomicOr(status, kStatusNaN);
-    o = block_lse3(o);
-    nw = block_lse3(nw);
+    block_lse3_pair(o, nw);
     if (threadIdx.x == 0) part[blockIdx.x] = RwPartial{o.m, o.s1, nw.m, nw.s1, nw.s2, 0.0};
 }
 
@@ -98,8 +97,7 @@ k_b_mid(const BatchRun* __restrict__ runs, const BatchChunk* __restrict__ chunks
         o = lse3_merge(o, Lse3{v.mo, v.so, 0.0});
         nw = lse3_merge(nw, Lse3{v.mn, v.s1, v.s2});
     }
-    o = block_lse3(o);
-    nw = block_lse3(nw);
+    block_lse3_pair(o, nw);
     if (threadIdx.x == 0) {
         const double ess = (nw.s1 * nw.s1) / nw.s2;
         const int fire = (ess_frac > 0.0) && (ess < ess_frac * static_cast<double>(rd.N));
@@ -130,7 +128,7 @@ k_b_mid(const BatchRun* __restrict__ runs, const BatchChunk* __restrict__ chunks
     const double* lw = logw + rd.p_off;
     scan_chunk(ch.index, rd.N, rd.chunk, cdf_hi + rd.p_off, cdf_lo + rd.p_off,
                chunk_tot + 2 * static_cast<size_t>(rd.c_off),
-               [&](int j) { return exp(lw[j] - M) / S; });
+               [&](int j) { return exp_fp64(lw[j] - M) / S; });
 }
 
 // A resampling run's ancestors and gather, a chunk of offspring per workgroup;

@@ -537,13 +537,11 @@ int smc_reweight(smc_ctx ctx, double* logw, const double* loglik, int64_t N, dou
     if (!logw || !loglik) return fail(SMC_ERR_INVALID_ARG, "NULL array");
     if (!isfinite(dbeta)) return fail(SMC_ERR_INVALID_ARG, "dbeta must be finite");
     const hipStream_t s = as_stream(stream);
-    hipError_t e = launch_reweight(ctx->sc, logw, loglik, N, host_src(0, 0.0, dbeta), nullptr,
-                                   logZ, ess, 0.0, nullptr, s);
+    const StepSrc src = host_src(0, 0.0, dbeta);
+    const hipError_t e =
+        W ? launch_reweight_weights(ctx->sc, logw, loglik, N, src, logZ, ess, W, s)
+          : launch_reweight(ctx->sc, logw, loglik, N, src, nullptr, logZ, ess, 0.0, nullptr, s);
     if (e != hipSuccess) return hip_fail(e, "reweight launch");
-    if (W) {
-        e = launch_weights(ctx->sc, logw, N, W, s);
-        if (e != hipSuccess) return hip_fail(e, "weights launch");
-    }
     return SMC_OK;
 }
 

@@ -28,7 +28,7 @@ struct CdfView {
     __device__ __forceinline__ double last() const { return cend[nchunks - 1]; }
 };
 
-// Chunk offsets and ends into LDS offh, offl, cend [kMaxChunks]: the exclusive
+// Chunk offsets and ends into LDS offh, offl, cend [nchunks]: the exclusive
 // double-double scan of the chunk totals [2 * nchunks] (hi, lo), formed by every
 // thread of a kRedBlock-thread block (cooperative; ends with a barrier).
 __device__ __forceinline__ void block_cdf_offsets(const double* chunk_tot, int nchunks,
@@ -50,6 +50,7 @@ __device__ __forceinline__ void block_cdf_offsets(const double* chunk_tot, int n
     const dd lead = block_dd_exclusive_scan(run, total);
 #pragma unroll
     for (int q = 0; q < per; ++q) {
+        if (c0 + q >= nchunks) break;
         const dd o = dd_add(lead, loc[q]);
         offh[c0 + q] = o.hi;
         offl[c0 + q] = o.lo;

@@ -401,7 +401,7 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
 #pragma unroll
         for (int c = 0; c < kDdDim; ++c) {
             const float v = yr[c];
-            const double sum = wave_sum_dpp(fabsf(v) < 1.0e18f ? static_cast<double>(v) : 0.0);
+            const double sum = wave_sum(fabsf(v) < 1.0e18f ? static_cast<double>(v) : 0.0);
             if (threadIdx.x == 0) cen[c] = sum * (1.0 / kWave);
         }
     }

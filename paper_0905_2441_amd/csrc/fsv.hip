@@ -31,7 +31,7 @@ template <int KF>
 __device__ __forceinline__ void moments_push(Moments<KF>& a, double lw, const double (&x)[KF]) {
     if (lw == -INFINITY) return;
     const double d = lw - a.m;
-    const double e = exp(-fabs(d));
+    const double e = exp_fp64(-fabs(d));
     const bool up = d > 0.0;
     a.m = up ? lw : a.m;
     a.s = up ? a.s * e + 1.0 : a.s + e;
@@ -141,17 +141,17 @@ k_fsv_weight(FsvDev f, const double* __restrict__ y, int T, const double* __rest
         moments_push<KF>(mo, ln, xn);
     }
     if (bad) atomicOr(sc.status, kStatusNaN);
-    o = block_lse3(o);
-    nw = block_lse3(nw);
+    block_lse3_pair(o, nw);
     // moment sums rescaled to the block maximum of the new log-weights (nw.m,
     // the same in every thread), then added in fixed order
-    const double r = (mo.m == -INFINITY) ? 0.0 : exp(mo.m - nw.m);
+    const double r = (mo.m == -INFINITY) ? 0.0 : exp_fp64(mo.m - nw.m);
     double acc[2 * KF];
 #pragma unroll
     for (int c = 0; c < KF; ++c) {
-        acc[c] = block_sum(mo.sx[c] * r);
-        acc[KF + c] = block_sum(mo.sxx[c] * r);
+        acc[c] = mo.sx[c] * r;
+        acc[KF + c] = mo.sxx[c] * r;
     }
+    block_sum_n<2 * KF>(acc);
     if (threadIdx.x == 0) {
         sc.rw_part[blockIdx.x] = RwPartial{o.m, o.s1, nw.m, nw.s1, nw.s2, 0.0};
 #pragma unroll
@@ -178,12 +178,6 @@ bool fsv_supported(int m, int k) {
     return false;
 }
 
-int fsv_parts(int64_t N) {
-    int64_t g = (N + kRedBlock - 1) / kRedBlock;
-    if (g > kMaxRedBlocks) g = kMaxRedBlocks;
-    return static_cast<int>(g < 1 ? 1 : g);
-}
-
 hipError_t launch_fsv_init(int k, int64_t N, double* x, double* logw, hipStream_t s) {
     hipLaunchKernelGGL(k_fsv_init, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s,
                        k, static_cast<int>(N), x, logw);
@@ -193,7 +187,7 @@ hipError_t launch_fsv_init(int k, int64_t N, double* x, double* logw, hipStream_
 hipError_t launch_fsv_weight(const FsvDev& f, const double* y, int T, const double* x,
                              double* x_out, double* logw, int64_t N, StepSrc src, uint64_t seed,
                              const Scratch& sc, double* mom, hipStream_t s, const FsvAnc& anc) {
-    const dim3 grid(static_cast<unsigned>(fsv_parts(N)));
+    const dim3 grid(static_cast<unsigned>(moment_parts(N)));
 #define SMC_CASE(MO, KF)                                                                      \
     if (f.m == MO && f.k == KF) {                                                             \
         hipLaunchKernelGGL((k_fsv_weight<MO, KF>), grid, dim3(kRedBlock), 0, s, f, y, T, x,   \

@@ -29,8 +29,6 @@ struct FsvAnc {
 };
 
 bool fsv_supported(int m, int k);
-// Number of per-block partials the weight pass writes (as the step's combine expects).
-int fsv_parts(int64_t N);
 hipError_t launch_fsv_init(int k, int64_t N, double* x, double* logw, hipStream_t s);
 // Propagate + weight + reweight partials (sc.rw_part) + moment partials (mom).
 hipError_t launch_fsv_weight(const FsvDev& f, const double* y, int T, const double* x,

@@ -3,6 +3,7 @@
 #include <type_traits>
 
 #include "cdf_search.hpp"
+#include "fp64.hpp"
 #include "internal.hpp"
 #include "philox.hpp"
 #include "wave.hpp"
@@ -458,31 +459,6 @@ __device__ __forceinline__ double partial_fp32(const float* __restrict__ y, int 
     return msum + static_cast<double>(expo) + static_cast<double>(__builtin_amdgcn_logf(prod));
 }
 
-// 2^t in FP64 for |t| < 2^31 (0 below the FP64 range, NaN for NaN): 2^n 2^f with
-// n the nearest integer and a polynomial of degree 10 in f on [-1/2, 1/2]. Adding
-// 1.5 * 2^52 rounds t to an integer whose low word is n (cheaper here than
-// v_rndne_f64 and v_cvt_i32_f64, which issues at half rate). The coefficients are
-// the least-squares fit of the relative error at Chebyshev nodes with the
-// constant term 1, rounded to FP64 (relative error below 2.5e-16). 14
-// instructions; the device library's exp takes about 45.
-__device__ __forceinline__ double exp2_fp64(double t) {
-    constexpr double kRound = 6755399441055744.0;        // 1.5 * 2^52
-    const double r = t + kRound;
-    const double f = t - (r - kRound);
-    double p = 7.041923263577725e-09;
-    p = fma(p, f, 1.020852183362834e-07);
-    p = fma(p, f, 1.3215629590371928e-06);
-    p = fma(p, f, 1.5252658206764617e-05);
-    p = fma(p, f, 0.0001540353004830873);
-    p = fma(p, f, 0.0013333558228392813);
-    p = fma(p, f, 0.0096181291079336);
-    p = fma(p, f, 0.05550410866446);
-    p = fma(p, f, 0.2402265069590925);
-    p = fma(p, f, 0.6931471805599497);
-    p = fma(p, f, 1.0);
-    return __builtin_amdgcn_ldexp(p, static_cast<int>(__builtin_bit_cast(long long, r)));
-}
-
 // Sum over data j in [ja, jb) of ln sum_i w_i exp(-||y_j - mu_i||^2 / (2 sigma2))
 // in FP64, the general form: each datum's sum is taken relative to its largest
 // term (the maxima added in FP64) and lies in [1, K], so the sums are multiplied
@@ -616,8 +592,8 @@ __device__ __forceinline__ double pivot_fp64(const float* __restrict__ y, int j0
             continue;
         }
         const double d = in ? static_cast<double>(v) - c : 0.0;
-        const double S1 = wave_sum_dpp(d);
-        const double S2 = wave_sum_dpp(d * d);
+        const double S1 = wave_sum(d);
+        const double S2 = wave_sum(d * d);
         if constexpr (K > 1) {
             wave_sync();                             // the previous window's reads come first
             row[lane] = d;
@@ -876,12 +852,7 @@ __device__ __forceinline__ void fused_ancestors(const MoveStep& ms, int N, uint3
             const int c = lane * per + q;
             if (c < ms.nchunks) run = dd_add(run, dd{ms.chunk_tot[2 * c], ms.chunk_tot[2 * c + 1]});
         }
-        dd inc = run;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const dd up{__shfl_up(inc.hi, o, kWave), __shfl_up(inc.lo, o, kWave)};
-            if (lane >= o) inc = dd_add(up, inc);
-        }
+        const dd inc = wave_scan(run);
         dd excl{__shfl_up(inc.hi, 1, kWave), __shfl_up(inc.lo, 1, kWave)};
         if (lane == 0) excl = dd_zero();
         for (int q = 0; q < per; ++q) {
@@ -963,7 +934,7 @@ __device__ __forceinline__ void move_duties(int p, int N, const MoveStep& ms) {
     const bool rs = (ms.state != nullptr) && (ms.state->resampled != 0);
     if (ms.W_out) {
         ms.W_out[p] = rs ? 1.0 / static_cast<double>(N)
-                         : exp(ms.logw[p] - ms.state->M) / ms.state->S;
+                         : exp_fp64(ms.logw[p] - ms.state->M) / ms.state->S;
     }
     if (ms.logw_out) ms.logw_out[p] = rs ? 0.0 : ms.logw[p];
     else if (rs && ms.reset_logw) ms.logw[p] = 0.0;

@@ -293,8 +293,10 @@ hipError_t launch_dd64_rwmh(const GmmDev& g, const float* y, int64_t n, double* 
 hipError_t launch_reweight(const Scratch& sc, double* logw, const double* l, int64_t N,
                            StepSrc src, int* t_advance, double* logZ, double* ess,
                            double ess_frac, double* resample_count, hipStream_t s);
-hipError_t launch_weights(const Scratch& sc, const double* logw, int64_t N, double* W,
-                          hipStream_t s);
+// The reweight with its normalised weights W: two launches.
+hipError_t launch_reweight_weights(const Scratch& sc, double* logw, const double* l, int64_t N,
+                                   StepSrc src, double* logZ, double* ess, double* W,
+                                   hipStream_t s);
 hipError_t launch_ess(const Scratch& sc, const double* W, int64_t N, double* ess,
                       hipStream_t s);
 // Resampling (scheme: smc_resampling): CDF of the weights, then search and
@@ -325,6 +327,11 @@ hipError_t launch_step_mid(const Scratch& sc, int64_t N, StepSrc src, int* t_adv
                            const double* mom = nullptr, int mom_k = 0, int mom_stride = 0,
                            double* moments = nullptr, const RwPartial* part = nullptr,
                            int nparts = 0);
+// Workgroups (partials, with moments) of a particle filter's weight pass.
+inline int moment_parts(int64_t N) {
+    const int64_t g = (N + kRedBlock - 1) / kRedBlock;
+    return static_cast<int>(g > kMaxRedBlocks ? kMaxRedBlocks : g < 1 ? 1 : g);
+}
 void cdf_layout(int64_t N, int* chunk, int* nchunks);
 hipError_t launch_search_gather(const Scratch& sc, int64_t N, int scheme, uint64_t seed,
                                 StepSrc src, const StepState* pred_state, const double* theta_in,

@@ -2,6 +2,7 @@
 // (one workgroup = kRedBlock threads). Every combine runs in a fixed lane and
 // wave order, so results are bit-reproducible.
 #pragma once
+#include "fp64.hpp"
 #include "internal.hpp"
 #include "wave.hpp"
 
@@ -20,18 +21,18 @@ __device__ __forceinline__ Lse3 lse3_empty() { return Lse3{-INFINITY, 0.0, 0.0};
 __device__ __forceinline__ Lse3 lse3_push(Lse3 a, double x) {
     if (x == -INFINITY) return a;
     const double d = x - a.m;                   // +inf while the sums are empty
-    const double e = exp(-fabs(d));
+    const double e = exp_fp64(-fabs(d));
     const bool up = d > 0.0;
     return Lse3{up ? x : a.m, up ? a.s1 * e + 1.0 : a.s1 + e,
                 up ? a.s2 * (e * e) + 1.0 : a.s2 + e * e};
 }
 
 // Wave (64 lanes) log-sum-exp, the same value in every lane: the wave maximum
-// first, then each lane's sums rescaled to it with one exp and added by a
-// fixed butterfly.
+// first, then each lane's sums rescaled to it with one exp and added in a
+// fixed order.
 __device__ __forceinline__ Lse3 wave_lse3(Lse3 v) {
     const double m = wave_max(v.m);
-    const double r = (v.m == -INFINITY) ? 0.0 : exp(v.m - m);
+    const double r = (v.m == -INFINITY) ? 0.0 : exp_fp64(v.m - m);
     return Lse3{m, wave_sum(v.s1 * r), wave_sum(v.s2 * (r * r))};
 }
 
@@ -39,10 +40,10 @@ __device__ __forceinline__ Lse3 lse3_merge(Lse3 a, Lse3 b) {
     if (b.m == -INFINITY) return a;
     if (a.m == -INFINITY) return b;
     if (a.m >= b.m) {
-        const double r = exp(b.m - a.m);
+        const double r = exp_fp64(b.m - a.m);
         return Lse3{a.m, a.s1 + b.s1 * r, a.s2 + b.s2 * (r * r)};
     }
-    const double r = exp(a.m - b.m);
+    const double r = exp_fp64(a.m - b.m);
     return Lse3{b.m, b.s1 + a.s1 * r, b.s2 + a.s2 * (r * r)};
 }
 
@@ -57,7 +58,7 @@ __device__ __forceinline__ Lse3 lse3_of(const double (&x)[n]) {
 #pragma unroll
     for (int i = 0; i < n; ++i) {
         // a NaN, which the maximum passed over, stays one; no weight at all adds none
-        const double e = m == -INFINITY && x[i] == m ? 0.0 : exp(x[i] - m);
+        const double e = m == -INFINITY && x[i] == m ? 0.0 : exp_fp64(x[i] - m);
         r.s1 += e;
         r.s2 = r.s2 + e * e;
     }
@@ -76,7 +77,7 @@ __device__ __forceinline__ Lse3 block_lse3(Lse3 v) {
     double M = sm[0];
 #pragma unroll
     for (int w = 1; w < kRedBlock / kWave; ++w) M = fmax(M, sm[w]);
-    const double r = (v.m == -INFINITY) ? 0.0 : exp(v.m - M);
+    const double r = (v.m == -INFINITY) ? 0.0 : exp_fp64(v.m - M);
     const double a = wave_sum(v.s1 * r);
     const double b = wave_sum(v.s2 * (r * r));
     if (lane_id() == 0) {
@@ -93,6 +94,48 @@ __device__ __forceinline__ Lse3 block_lse3(Lse3 v) {
     }
     __syncthreads();
     return out;
+}
+
+// block_lse3 of the old weights' log-sum-exp o (its s2 is not formed) and the new
+// weights' nw together, with the barriers of one. The maxima are valid in every
+// thread, the sums in thread 0.
+__device__ __forceinline__ void block_lse3_pair(Lse3& o, Lse3& nw) {
+    constexpr int kW = kRedBlock / kWave;
+    __shared__ double mo[kW], mn[kW], so[kW], s1[kW], s2[kW];
+    const int w = wave_id();
+    const double wo = wave_max(o.m), wn = wave_max(nw.m);
+    if (lane_id() == 0) {
+        mo[w] = wo;
+        mn[w] = wn;
+    }
+    __syncthreads();
+    double Mo = mo[0], Mn = mn[0];
+#pragma unroll
+    for (int q = 1; q < kW; ++q) {
+        Mo = fmax(Mo, mo[q]);
+        Mn = fmax(Mn, mn[q]);
+    }
+    const double ro = (o.m == -INFINITY) ? 0.0 : exp_fp64(o.m - Mo);
+    const double rn = (nw.m == -INFINITY) ? 0.0 : exp_fp64(nw.m - Mn);
+    const double a = wave_sum(o.s1 * ro);
+    const double b = wave_sum(nw.s1 * rn);
+    const double c = wave_sum(nw.s2 * (rn * rn));
+    if (lane_id() == 0) {
+        so[w] = a;
+        s1[w] = b;
+        s2[w] = c;
+    }
+    __syncthreads();
+    o = Lse3{Mo, 0.0, 0.0};
+    nw = Lse3{Mn, 0.0, 0.0};
+    if (threadIdx.x == 0) {
+        for (int q = 0; q < kW; ++q) {
+            o.s1 += so[q];
+            nw.s1 += s1[q];
+            nw.s2 += s2[q];
+        }
+    }
+    __syncthreads();
 }
 
 // Block (kRedBlock threads) maximum, valid in every thread.
@@ -121,7 +164,7 @@ __device__ __forceinline__ double block_sum(double v) {
 }
 
 // Block (kRedBlock threads) sums of n values per thread, each added as
-// block_sum adds one (wave butterfly, then the waves in order); the results
+// block_sum adds one (the wave's sum, then the waves in order); the results
 // are valid in thread 0.
 template <int n>
 __device__ __forceinline__ void block_sum_n(double (&v)[n]) {
@@ -148,12 +191,7 @@ __device__ __forceinline__ void block_sum_n(double (&v)[n]) {
 __device__ __forceinline__ dd block_dd_exclusive_scan(dd v, dd& total) {
     __shared__ double wh[kRedBlock / kWave], wl[kRedBlock / kWave];
     const int lane = lane_id();
-    dd inc = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const dd up{__shfl_up(inc.hi, o, kWave), __shfl_up(inc.lo, o, kWave)};
-        if (lane >= o) inc = dd_add(up, inc);
-    }
+    const dd inc = wave_scan(v);
     if (lane == kWave - 1) {
         wh[wave_id()] = inc.hi;
         wl[wave_id()] = inc.lo;

@@ -42,34 +42,59 @@ k_reweight_partial(double* __restrict__ logw, const double* __restrict__ l, int 
         const int t = step_index(src);
         dbeta = src.beta_dev[t] - src.beta_dev[t - 1];
     }
+    // kU elements of a thread are loaded together and summed about their own
+    // maximum, so no load waits on an exponential and none of those on another
+    constexpr int kU = 4;
     Lse3 o = lse3_empty(), nw = lse3_empty();
     bool bad = false;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < N; p += gridDim.x * blockDim.x) {
-        const double lo = logw[p];
-        const double ln = lo + dbeta * l[p];
-        logw[p] = ln;
-        bad = bad || (ln != ln) || (ln == INFINITY);
-        o = lse3_push(o, lo);
-        nw = lse3_push(nw, ln);
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kRedBlock;
+    for (int64_t b0 = static_cast<int64_t>(blockIdx.x) * kRedBlock; b0 < N; b0 += kU * stride) {
+        double lo[kU], ln[kU];
+#pragma unroll
+        for (int e = 0; e < kU; ++e) {
+            const int64_t p = b0 + e * stride + threadIdx.x;
+            lo[e] = p < N ? logw[p] : -INFINITY;
+            ln[e] = p < N ? l[p] : 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < kU; ++e) {
+            const int64_t p = b0 + e * stride + threadIdx.x;
+            ln[e] = p < N ? lo[e] + dbeta * ln[e] : -INFINITY;
+            if (p < N) logw[p] = ln[e];
+            bad = bad || (ln[e] != ln[e]) || (ln[e] == INFINITY);
+        }
+        if (b0 + stride < N) {
+            o = lse3_merge(o, lse3_of(lo));
+            nw = lse3_merge(nw, lse3_of(ln));
+        } else {                               // at most one element a thread
+            o = lse3_push(o, lo[0]);
+            nw = lse3_push(nw, ln[0]);
+        }
     }
     if (bad) atomicOr(sc.status, kStatusNaN);
-    o = block_lse3(o);
-    nw = block_lse3(nw);
+    block_lse3_pair(o, nw);
     if (threadIdx.x == 0) sc.rw_part[blockIdx.x] = RwPartial{o.m, o.s1, nw.m, nw.s1, nw.s2, 0.0};
 }
 
-__global__ void __launch_bounds__(kRedBlock)
-k_reweight_final(int parts, int N, StepSrc src, int* t_advance, Scratch sc, double* logZ,
-                 double* ess_out, double ess_frac, double* resample_count) {
-    Lse3 o = lse3_empty(), nw = lse3_empty();
-    for (int b = threadIdx.x; b < parts; b += blockDim.x) {
-        const RwPartial q = sc.rw_part[b];
+// The reweight's partials combined by every thread of a block, in the same order
+// in every block; valid in thread 0 (nw.m in every thread).
+__device__ __forceinline__ void combine_partials(const RwPartial* __restrict__ part, int parts,
+                                                 Lse3& o, Lse3& nw) {
+    o = lse3_empty();
+    nw = lse3_empty();
+    for (int b = threadIdx.x; b < parts; b += kRedBlock) {
+        const RwPartial q = part[b];
         o = lse3_merge(o, Lse3{q.mo, q.so, 0.0});
         nw = lse3_merge(nw, Lse3{q.mn, q.s1, q.s2});
     }
-    o = block_lse3(o);
-    nw = block_lse3(nw);
-    if (threadIdx.x != 0) return;
+    block_lse3_pair(o, nw);
+}
+
+// The sums' results (thread 0 of one block): step state, evidence, ESS.
+__device__ __forceinline__ void publish_reweight(const Lse3& o, const Lse3& nw, int N, StepSrc src,
+                                                 int* t_advance, const Scratch& sc, double* logZ,
+                                                 double* ess_out, double ess_frac,
+                                                 double* resample_count) {
     StepState* st = sc.state;
     st->M = nw.m;
     st->S = nw.s1;
@@ -92,10 +117,61 @@ k_reweight_final(int parts, int N, StepSrc src, int* t_advance, Scratch sc, doub
 }
 
 __global__ void __launch_bounds__(kRedBlock)
+k_reweight_final(int parts, int N, StepSrc src, int* t_advance, Scratch sc, double* logZ,
+                 double* ess_out, double ess_frac, double* resample_count) {
+    Lse3 o, nw;
+    combine_partials(sc.rw_part, parts, o, nw);
+    if (threadIdx.x == 0)
+        publish_reweight(o, nw, N, src, t_advance, sc, logZ, ess_out, ess_frac, resample_count);
+}
+
+__global__ void __launch_bounds__(kRedBlock)
 k_weights(const double* __restrict__ logw, int N, Scratch sc, double* __restrict__ W) {
     const double M = sc.state->M, S = sc.state->S;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < N; p += gridDim.x * blockDim.x)
-        W[p] = exp(logw[p] - M) / S;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kRedBlock;
+    for (int64_t p = static_cast<int64_t>(blockIdx.x) * kRedBlock + threadIdx.x; p < N; p += stride)
+        W[p] = exp_fp64(logw[p] - M) / S;
+}
+
+// The combine and the normalised weights in one launch: every block combines the
+// partials itself (a launch of one block for it took 7.3 us of a reweight of 2^20
+// particles), the first one publishes.
+__global__ void __launch_bounds__(kRedBlock)
+k_reweight_weights(int parts, const double* __restrict__ logw, int N, StepSrc src, Scratch sc,
+                   double* logZ, double* ess_out, double* __restrict__ W) {
+    __shared__ double sh_S;
+    constexpr int kU = 4;
+    const int stride = gridDim.x * kRedBlock;
+    // the first elements come in while the partials are combined
+    double x[kU];
+#pragma unroll
+    for (int e = 0; e < kU; ++e) {
+        const int64_t p = static_cast<int64_t>(blockIdx.x) * kRedBlock + threadIdx.x +
+                          e * static_cast<int64_t>(stride);
+        x[e] = p < N ? logw[p] : 0.0;
+    }
+    Lse3 o, nw;
+    combine_partials(sc.rw_part, parts, o, nw);
+    if (threadIdx.x == 0) {
+        sh_S = nw.s1;
+        if (blockIdx.x == 0)
+            publish_reweight(o, nw, N, src, nullptr, sc, logZ, ess_out, 0.0, nullptr);
+    }
+    __syncthreads();
+    const double M = nw.m, S = sh_S;
+    for (int64_t b0 = static_cast<int64_t>(blockIdx.x) * kRedBlock; b0 < N;
+         b0 += kU * static_cast<int64_t>(stride)) {
+#pragma unroll
+        for (int e = 0; e < kU; ++e) {
+            const int64_t p = b0 + threadIdx.x + e * static_cast<int64_t>(stride);
+            if (p < N) W[p] = exp_fp64(x[e] - M) / S;
+        }
+#pragma unroll
+        for (int e = 0; e < kU; ++e) {
+            const int64_t p = b0 + threadIdx.x + (kU + e) * static_cast<int64_t>(stride);
+            x[e] = p < N ? logw[p] : 0.0;
+        }
+    }
 }
 
 __global__ void __launch_bounds__(kRedBlock)
@@ -133,7 +209,7 @@ __device__ __forceinline__ bool should_fire(const ResamplePred& pr) {
 
 __device__ __forceinline__ double weight_at(const WeightSrc& w, int j) {
     if (w.W) return w.W[j];
-    return exp(w.logw[j] - w.state->M) / w.state->S;
+    return exp_fp64(w.logw[j] - w.state->M) / w.state->S;
 }
 
 // Standalone resampling (smc_resample*) in three passes over chunks of
@@ -157,33 +233,31 @@ k_cdf_chunks(WeightSrc w, int N, Scratch sc, ResamplePred pred) {
     }
 }
 
-// Exclusive double-double scan of the nchunks chunk totals into res_off
-// (one workgroup; kScanPerThread consecutive totals per thread per round).
+// Exclusive double-double scan of the nchunks chunk totals into res_off. Workgroup
+// b writes the offsets of chunks [256 b, 256 b + 256) and sums the totals before
+// them itself, with coalesced independent loads, so no workgroup waits on another
+// (one workgroup for all of them took 29 us at 16384 chunks).
 __global__ void __launch_bounds__(kRedBlock)
 k_cdf_offsets(int nchunks, Scratch sc, ResamplePred pred) {
     if (!should_fire(pred)) return;
-    dd carry = dd_zero();
-    for (int piece = 0; piece < nchunks; piece += kScanChunk) {
-        const int base = piece + threadIdx.x * kScanPerThread;
-        dd loc[kScanPerThread];
-        dd run = dd_zero();
-#pragma unroll
-        for (int e = 0; e < kScanPerThread; ++e) {
-            loc[e] = run;
-            if (base + e < nchunks)
-                run = dd_add(run, dd{sc.res_tot[2 * (base + e)], sc.res_tot[2 * (base + e) + 1]});
-        }
-        dd total;
-        const dd lead = dd_add(carry, block_dd_exclusive_scan(run, total));
-#pragma unroll
-        for (int e = 0; e < kScanPerThread; ++e) {
-            if (base + e < nchunks) {
-                const dd o = dd_add(lead, loc[e]);
-                sc.res_off[2 * (base + e)] = o.hi;
-                sc.res_off[2 * (base + e) + 1] = o.lo;
-            }
-        }
-        carry = dd_add(carry, total);
+    const double2* tot = reinterpret_cast<const double2*>(sc.res_tot);
+    double2* off = reinterpret_cast<double2*>(sc.res_off);
+    const int t = threadIdx.x;
+    const int c0 = blockIdx.x * kRedBlock;
+    dd before = dd_zero();
+#pragma unroll 8
+    for (int c = t; c < c0; c += kRedBlock) {
+        const double2 v = tot[c];
+        before = dd_add(before, dd{v.x, v.y});
+    }
+    const int c = c0 + t;
+    const double2 v = c < nchunks ? tot[c] : double2{0.0, 0.0};
+    dd total, own;
+    (void)block_dd_exclusive_scan(before, total);
+    const dd excl = block_dd_exclusive_scan(dd{v.x, v.y}, own);
+    if (c < nchunks) {
+        const dd o = dd_add(total, excl);
+        off[c] = double2{o.hi, o.lo};
     }
 }
 
@@ -239,12 +313,12 @@ k_step_mid(int parts, int N, int chunk, StepSrc src, int* t_advance, Scratch sc,
             double mr = m;
 #pragma unroll
             for (int u = 0; u < kU; ++u) mr = fmax(mr, vm[u]);
-            const double rr = m == -INFINITY ? 0.0 : exp(m - mr);
+            const double rr = m == -INFINITY ? 0.0 : exp_fp64(m - mr);
             a *= rr;
             c *= rr * rr;
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
-                const double r = vm[u] == -INFINITY ? 0.0 : exp(vm[u] - mr);
+                const double r = vm[u] == -INFINITY ? 0.0 : exp_fp64(vm[u] - mr);
                 a += v1[u] * r;
                 c += v2[u] * (r * r);
             }
@@ -257,8 +331,7 @@ k_step_mid(int parts, int N, int chunk, StepSrc src, int* t_advance, Scratch sc,
             o = lse3_merge(o, Lse3{q.mo, q.so, 0.0});
             nw = lse3_merge(nw, Lse3{q.mn, q.s1, q.s2});
         }
-        o = block_lse3(o);
-        nw = block_lse3(nw);
+        block_lse3_pair(o, nw);
     }
     if (threadIdx.x == 0) {
         const double e = (nw.s1 * nw.s1) / nw.s2;
@@ -300,7 +373,7 @@ k_step_mid(int parts, int N, int chunk, StepSrc src, int* t_advance, Scratch sc,
         for (int c = 0; c < 2 * kMaxMomK; ++c) acc[c] = 0.0;
         for (int q = threadIdx.x; q < parts; q += blockDim.x) {
             const double mb = part[q].mn;
-            const double r = (mb == -INFINITY) ? 0.0 : exp(mb - M);
+            const double r = (mb == -INFINITY) ? 0.0 : exp_fp64(mb - M);
             const double* mq = mom + static_cast<size_t>(q) * mom_stride;
 #pragma unroll
             for (int c = 0; c < kMaxMomK; ++c) {
@@ -322,7 +395,7 @@ k_step_mid(int parts, int N, int chunk, StepSrc src, int* t_advance, Scratch sc,
     }
     if (!sh_fire) return;
     scan_chunk(blockIdx.x, N, chunk, sc.cdf_hi, sc.cdf_lo, sc.dd_part,
-               [&](int j) { return exp(logw[j] - M) / S; });
+               [&](int j) { return exp_fp64(logw[j] - M) / S; });
 }
 
 // Publish the normalised weights of a step that made no move.
@@ -331,7 +404,7 @@ k_publish_w(double* __restrict__ W, const double* __restrict__ logw, int N, Scra
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
     const StepState* st = sc.state;
-    W[i] = st->resampled ? 1.0 / static_cast<double>(N) : exp(logw[i] - st->M) / st->S;
+    W[i] = st->resampled ? 1.0 / static_cast<double>(N) : exp_fp64(logw[i] - st->M) / st->S;
 }
 
 // Phase 2: chunk offsets (exclusive scan of the chunk totals, once per block in
@@ -394,6 +467,7 @@ k_search_gather(int N, int chunk, int nchunks, Scratch sc, ResamplePred pred, in
 // Multinomial points are unsorted: one binary search per point.
 constexpr int kMergePiece = 2048;
 constexpr int64_t kMergeWideN = int64_t{1} << 22;   // PER = 8 from here on
+constexpr int kLdsChunks = 256;
 
 __device__ __forceinline__ void resample_gather_point(int i, int j, int N, int32_t* idx_out,
                                                       const double* __restrict__ theta_in,
@@ -425,7 +499,7 @@ __device__ __forceinline__ bool resample_copy_if_skipped(const ResamplePred& pre
     return true;
 }
 
-template <int PER>
+template <int PER, bool LDSOFF>
 __global__ void __launch_bounds__(kRedBlock)
 k_resample_merge(int N, Scratch sc, ResamplePred pred, int scheme, uint64_t seed, StepSrc src,
                  const double* u_override, int32_t* idx_out,
@@ -448,22 +522,34 @@ k_resample_merge(int N, Scratch sc, ResamplePred pred, int scheme, uint64_t seed
     const double* __restrict__ hi = sc.cdf_hi;
     const double* __restrict__ lo = sc.cdf_lo;
     const double* __restrict__ off = sc.res_off;
+    extern __shared__ double chunk_lds[];              // LDSOFF: offsets and ends [3 nchunks]
+    const int nch = (N + kResChunk - 1) / kResChunk;
+    const CdfView view{N, kResChunk, nch, hi, lo, chunk_lds, chunk_lds + nch, chunk_lds + 2 * nch};
+    if (LDSOFF)
+        block_cdf_offsets(sc.res_tot, nch, chunk_lds, chunk_lds + nch, chunk_lds + 2 * nch);
     auto cdf = [&](int j) -> double {
         const int b = j / kResChunk;
+        if (LDSOFF) return view.at(b, j);
         return dd_add(dd{off[2 * b], off[2 * b + 1]}, dd{hi[j], lo[j]}).hi;
     };
     const uint32_t step = static_cast<uint32_t>(step_index(src));
     double u = 0.0;
     if (scheme == 0)
         u = u_override ? *u_override : u01_left_closed(draw(seed, 0, 0, step, kResamp, 0).w0);
-    const double clast = cdf(N - 1);
+    const double clast = LDSOFF ? view.last() : cdf(N - 1);
     auto pred_c = [&](double uu, double c) -> bool { return cdf_past(uu, c, clast); };
     const int i_last = min(N, i0 + kMergeTile) - 1;
     if (wave_id() == 0) {
         // lanes 0-31 search the ancestor of the tile's first point, 32-63 of its last
         const int lane = lane_id();
         const double us = resample_point(scheme, seed, step, lane >> 5 ? i_last : i0, N, u);
-        const int lo_ = first_true_half(0, N - 1, [&](int q) { return pred_c(us, cdf(q)); });
+        int j0 = 0, j1 = N - 1;
+        if (LDSOFF) {
+            j0 = kResChunk *
+                 first_true_half(0, nch - 1, [&](int q) { return pred_c(us, view.cend[q]); });
+            j1 = min(N, j0 + kResChunk) - 1;
+        }
+        const int lo_ = first_true_half(j0, j1, [&](int q) { return pred_c(us, cdf(q)); });
         if (lane == 0) ab[0] = lo_;
         if (lane == 32) ab[1] = lo_;
     }
@@ -519,32 +605,45 @@ k_resample_merge(int N, Scratch sc, ResamplePred pred, int scheme, uint64_t seed
     }
 }
 
+template <int PER, bool LDSOFF>
 __global__ void __launch_bounds__(kRedBlock)
 k_resample_gather(int N, Scratch sc, ResamplePred pred, int scheme, uint64_t seed, StepSrc src,
                   const double* u_override, int32_t* idx_out,
                   const double* __restrict__ theta_in, double* __restrict__ theta_out, int kd,
                   const double* __restrict__ l_in, double* __restrict__ l_out, double* logw,
                   int copy_when_skipped) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (resample_copy_if_skipped(pred, copy_when_skipped, i, N, idx_out, theta_in, theta_out, kd,
-                                 l_in, l_out))
+    const int i0 = blockIdx.x * kRedBlock * PER + threadIdx.x;
+    if (!should_fire(pred)) {
+        for (int e = 0; e < PER; ++e)
+            resample_copy_if_skipped(pred, copy_when_skipped, i0 + e * kRedBlock, N, idx_out,
+                                     theta_in, theta_out, kd, l_in, l_out);
         return;
-    if (i >= N) return;
+    }
     const uint32_t step = static_cast<uint32_t>(step_index(src));
     double u = 0.0;
     if (scheme == 0)
         u = u_override ? *u_override : u01_left_closed(draw(seed, 0, 0, step, kResamp, 0).w0);
-    const double U = resample_point(scheme, seed, step, i, N, u);
     const double* __restrict__ hi = sc.cdf_hi;
     const double* __restrict__ lo = sc.cdf_lo;
     const double* __restrict__ off = sc.res_off;
+    extern __shared__ double chunk_lds[];
+    const int nch = (N + kResChunk - 1) / kResChunk;
+    const CdfView view{N, kResChunk, nch, hi, lo, chunk_lds, chunk_lds + nch, chunk_lds + 2 * nch};
+    if (LDSOFF)
+        block_cdf_offsets(sc.res_tot, nch, chunk_lds, chunk_lds + nch, chunk_lds + 2 * nch);
     auto cdf = [&](int jj) -> double {
         const int b = jj / kResChunk;
         return dd_add(dd{off[2 * b], off[2 * b + 1]}, dd{hi[jj], lo[jj]}).hi;
     };
-    const double clast = cdf(N - 1);
-    const int j = first_true(0, N - 1, [&](int q) { return cdf_past(U, cdf(q), clast); });
-    resample_gather_point(i, j, N, idx_out, theta_in, theta_out, kd, l_in, l_out, logw);
+    const double clast = LDSOFF ? view.last() : cdf(N - 1);
+    for (int e = 0; e < PER; ++e) {
+        const int i = i0 + e * kRedBlock;
+        if (i >= N) break;
+        const double U = resample_point(scheme, seed, step, i, N, u);
+        const int j = LDSOFF ? cdf_search(U, view)
+                             : first_true(0, N - 1, [&](int q) { return cdf_past(U, cdf(q), clast); });
+        resample_gather_point(i, j, N, idx_out, theta_in, theta_out, kd, l_in, l_out, logw);
+    }
 }
 
 // ---------------------------------------------------------------- exchange
@@ -596,9 +695,13 @@ __global__ void k_rng_normals(uint64_t seed, int64_t count, int per_index, uint3
     }
 }
 
+// Workgroups (and partials) of the reweight pass: 512 where they give a thread at
+// most 16 elements (two partials a thread to combine), 1024 beyond (the pass is
+// bound by memory there: 108 us with 512 at 2^24, 89-94 us with 1024).
 int red_grid(int64_t N) {
     int64_t g = (N + kRedBlock - 1) / kRedBlock;
-    if (g > kMaxRedBlocks) g = kMaxRedBlocks;
+    const int most = N <= int64_t{16} * 512 * kRedBlock ? 512 : kMaxRedBlocks;
+    if (g > most) g = most;
     if (g < 1) g = 1;
     return static_cast<int>(g);
 }
@@ -616,12 +719,10 @@ int cdf_chunk(int64_t N) {
 hipError_t launch_reweight(const Scratch& sc, double* logw, const double* l, int64_t N,
                            StepSrc src, int* t_advance, double* logZ, double* ess,
                            double ess_frac, double* resample_count, hipStream_t s) {
-    const int g = red_grid(N);
-    hipLaunchKernelGGL(k_reweight_partial, dim3(g), dim3(kRedBlock), 0, s, logw, l,
-                       static_cast<int>(N), src, sc);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_reweight_partial(sc, logw, l, N, src, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reweight_final, dim3(1), dim3(kRedBlock), 0, s, g, static_cast<int>(N),
+    hipLaunchKernelGGL(k_reweight_final, dim3(1), dim3(kRedBlock), 0, s, red_grid(N),
+                       static_cast<int>(N),
                        src, t_advance, sc, logZ, ess, ess_frac, resample_count);
     return hipGetLastError();
 }
@@ -633,10 +734,28 @@ hipError_t launch_reweight_partial(const Scratch& sc, double* logw, const double
     return hipGetLastError();
 }
 
-hipError_t launch_weights(const Scratch& sc, const double* logw, int64_t N, double* W,
-                          hipStream_t s) {
-    hipLaunchKernelGGL(k_weights, dim3(red_grid(N)), dim3(kRedBlock), 0, s, logw,
-                       static_cast<int>(N), sc, W);
+// Largest N whose blocks combine the partials themselves: 512 partials. Beyond,
+// with 1024, that costs more than the launch it saves (2^24: 62.6 us against
+// 7.9 + 46.3).
+constexpr int64_t kFusedWeightsN = int64_t{16} * 512 * kRedBlock;
+
+hipError_t launch_reweight_weights(const Scratch& sc, double* logw, const double* l, int64_t N,
+                                   StepSrc src, double* logZ, double* ess, double* W,
+                                   hipStream_t s) {
+    if (N > kFusedWeightsN) {
+        hipError_t e = launch_reweight(sc, logw, l, N, src, nullptr, logZ, ess, 0.0, nullptr, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_weights, dim3(kMaxRedBlocks), dim3(kRedBlock), 0, s,
+                           static_cast<const double*>(logw), static_cast<int>(N), sc, W);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_reweight_partial(sc, logw, l, N, src, s);
+    if (e != hipSuccess) return e;
+    const int64_t blocks = (N + 4 * kRedBlock - 1) / (4 * kRedBlock);
+    hipLaunchKernelGGL(k_reweight_weights,
+                       dim3(static_cast<unsigned>(blocks < kMaxRedBlocks ? blocks : kMaxRedBlocks)),
+                       dim3(kRedBlock), 0, s, red_grid(N), static_cast<const double*>(logw),
+                       static_cast<int>(N), src, sc, logZ, ess, W);
     return hipGetLastError();
 }
 
@@ -662,27 +781,31 @@ hipError_t launch_resample(const Scratch& sc, WeightSrc w, int64_t N, int scheme
                        static_cast<int>(N), sc, pred);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cdf_offsets, dim3(1), dim3(kRedBlock), 0, s, nchunks, sc, pred);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (scheme == SMC_RESAMPLE_MULTINOMIAL) {
-        const int g = static_cast<int>((N + kRedBlock - 1) / kRedBlock);
-        hipLaunchKernelGGL(k_resample_gather, dim3(g), dim3(kRedBlock), 0, s, static_cast<int>(N),
-                           sc, pred, scheme, seed, src, u_override, idx, theta_in, theta_out, kd,
-                           l_in, l_out, logw, copy_when_skipped);
-    } else {
-        if (N >= kMergeWideN) {
-            const int g = static_cast<int>((N + kRedBlock * 8 - 1) / (kRedBlock * 8));
-            hipLaunchKernelGGL(k_resample_merge<8>, dim3(g), dim3(kRedBlock), 0, s,
-                               static_cast<int>(N), sc, pred, scheme, seed, src, u_override, idx,
-                               theta_in, theta_out, kd, l_in, l_out, logw, copy_when_skipped);
-        } else {
-            const int g = static_cast<int>((N + kRedBlock * 2 - 1) / (kRedBlock * 2));
-            hipLaunchKernelGGL(k_resample_merge<2>, dim3(g), dim3(kRedBlock), 0, s,
-                               static_cast<int>(N), sc, pred, scheme, seed, src, u_override, idx,
-                               theta_in, theta_out, kd, l_in, l_out, logw, copy_when_skipped);
-        }
+    const bool lds_off = nchunks <= kLdsChunks;
+    if (!lds_off) {
+        hipLaunchKernelGGL(k_cdf_offsets, dim3((nchunks + kRedBlock - 1) / kRedBlock),
+                           dim3(kRedBlock), 0, s, nchunks, sc, pred);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
+    const size_t lds = lds_off ? sizeof(double) * 3 * static_cast<size_t>(nchunks) : 0;
+#define SMC_RES(KERNEL, PER, LDSOFF)                                                            \
+    hipLaunchKernelGGL((KERNEL<PER, LDSOFF>),                                                   \
+                       dim3(static_cast<unsigned>((N + kRedBlock * PER - 1) / (kRedBlock * PER))), \
+                       dim3(kRedBlock), lds, s, static_cast<int>(N), sc, pred, scheme, seed,     \
+                       src, u_override, idx, theta_in, theta_out, kd, l_in, l_out, logw,         \
+                       copy_when_skipped)
+    if (scheme == SMC_RESAMPLE_MULTINOMIAL) {
+        if (lds_off) SMC_RES(k_resample_gather, 2, true);
+        else SMC_RES(k_resample_gather, 1, false);
+    } else if (lds_off) {
+        SMC_RES(k_resample_merge, 2, true);
+    } else if (N >= kMergeWideN) {
+        SMC_RES(k_resample_merge, 8, false);
+    } else {
+        SMC_RES(k_resample_merge, 2, false);
+    }
+#undef SMC_RES
     return hipGetLastError();
 }
 
@@ -703,7 +826,7 @@ hipError_t launch_step_mid(const Scratch& sc, int64_t N, StepSrc src, int* t_adv
                            const double* mom, int mom_k, int mom_stride, double* moments,
                            const RwPartial* part, int nparts) {
     if (mom != nullptr && (mom_k < 1 || mom_k > kMaxMomK)) return hipErrorInvalidValue;
-    const int parts = part ? nparts : red_grid(N);
+    const int parts = part ? nparts : mom ? moment_parts(N) : red_grid(N);
     const int chunk = cdf_chunk(N);
     const int nchunks = static_cast<int>((N + chunk - 1) / chunk);
     hipLaunchKernelGGL(k_step_mid, dim3(nchunks), dim3(kRedBlock), 0, s, parts, static_cast<int>(N),

@@ -24,18 +24,6 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
-}
-
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-
 // The largest and smallest of the wave's 64 values of v, in every lane, by
 // DPP row shifts and row broadcasts (no LDS round trips). Floats are compared
 // through integer keys that keep their order (a NaN comes out largest or
@@ -92,50 +80,63 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
-// The same scan for FP64 values (the two halves moved by one DPP each).
+// FP64 values through the same DPP moves, two dwords each. A lane whose source is
+// outside its row, or whose row is masked off, gets `id`.
 template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_add_step(double v) {
+__device__ __forceinline__ double dpp_move(double v, double id) {
     const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, ROW_MASK, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, ROW_MASK, 0xf,
-                                               true);
-    const long long o = (static_cast<long long>(hi) << 32) |
-                        static_cast<long long>(static_cast<unsigned>(lo));
-    return v + __builtin_bit_cast(double, o);
+    const long long i = __builtin_bit_cast(long long, id);
+    const int lo = __builtin_amdgcn_update_dpp(static_cast<int>(i), static_cast<int>(b), CTRL,
+                                               ROW_MASK, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(static_cast<int>(i >> 32),
+                                               static_cast<int>(b >> 32), CTRL, ROW_MASK, 0xf,
+                                               false);
+    return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) |
+                                          static_cast<long long>(static_cast<unsigned>(lo)));
 }
-__device__ __forceinline__ double wave_sum_dpp(double v) {
-    v = dpp_add_step<0x111, 0xf>(v);   // row_shr:1
-    v = dpp_add_step<0x112, 0xf>(v);   // row_shr:2
-    v = dpp_add_step<0x114, 0xf>(v);   // row_shr:4
-    v = dpp_add_step<0x118, 0xf>(v);   // row_shr:8
-    v = dpp_add_step<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add_step<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+__device__ __forceinline__ double read_lane(double v, int lane) {
     const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), 63);
-    const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), 63);
+    const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), lane);
+    const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), lane);
     return __builtin_bit_cast(double, (static_cast<long long>(hi) << 32) |
                                           static_cast<long long>(static_cast<unsigned>(lo)));
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-    return v;
+// The wave's sum and maximum in every lane, in the order of an inclusive scan
+// (about 150 cycles; a butterfly of lane shuffles goes through LDS, 12 dependent
+// accesses of about 130 cycles).
+__device__ __forceinline__ double wave_sum(double v) {
+    v += dpp_move<0x111, 0xf>(v, 0.0);   // row_shr:1
+    v += dpp_move<0x112, 0xf>(v, 0.0);   // row_shr:2
+    v += dpp_move<0x114, 0xf>(v, 0.0);   // row_shr:4
+    v += dpp_move<0x118, 0xf>(v, 0.0);   // row_shr:8
+    v += dpp_move<0x142, 0xa>(v, 0.0);   // row_bcast:15 into rows 1 and 3
+    v += dpp_move<0x143, 0xc>(v, 0.0);   // row_bcast:31 into rows 2 and 3
+    return read_lane(v, kWave - 1);
+}
+__device__ __forceinline__ double wave_max(double v) {
+    v = fmax(v, dpp_move<0x111, 0xf>(v, -INFINITY));
+    v = fmax(v, dpp_move<0x112, 0xf>(v, -INFINITY));
+    v = fmax(v, dpp_move<0x114, 0xf>(v, -INFINITY));
+    v = fmax(v, dpp_move<0x118, 0xf>(v, -INFINITY));
+    v = fmax(v, dpp_move<0x142, 0xa>(v, -INFINITY));
+    v = fmax(v, dpp_move<0x143, 0xc>(v, -INFINITY));
+    return read_lane(v, kWave - 1);
 }
 
-__device__ __forceinline__ float wave_min(float v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off, kWave));
-    return v;
+// Inclusive double-double scan over the wave's lanes.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ dd dpp_scan_step(dd v) {
+    const dd up{dpp_move<CTRL, ROW_MASK>(v.hi, 0.0), dpp_move<CTRL, ROW_MASK>(v.lo, 0.0)};
+    return dd_add(up, v);
 }
-
-__device__ __forceinline__ dd wave_sum(dd v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        dd o{__shfl_xor(v.hi, off, kWave), __shfl_xor(v.lo, off, kWave)};
-        v = dd_add(v, o);
-    }
-    return v;
+__device__ __forceinline__ dd wave_scan(dd v) {
+    v = dpp_scan_step<0x111, 0xf>(v);
+    v = dpp_scan_step<0x112, 0xf>(v);
+    v = dpp_scan_step<0x114, 0xf>(v);
+    v = dpp_scan_step<0x118, 0xf>(v);
+    v = dpp_scan_step<0x142, 0xa>(v);
+    return dpp_scan_step<0x143, 0xc>(v);
 }
 
 }  // namespace smc

@@ -152,6 +152,73 @@ def test_resample_schemes_bit_exact(smc, ctx, scheme, N):
         assert np.array_equal(idx.cpu().numpy(), osmc.resample_indices(W, scheme, 21, step))
 
 
+@pytest.mark.parametrize("N", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1])
+@pytest.mark.parametrize("scheme", ["systematic", "stratified", "multinomial"])
+def test_resample_chunk_offsets_in_lds_or_memory(smc, ctx, scheme, N):
+    """Either side of the population (256 chunks of 1024) up to which the search's
+    workgroups form the chunk offsets themselves: spread weights, and weight on a
+    few particles far apart and at chunk ends."""
+    announce(f"resample offsets {scheme} N={N}")
+    sparse = np.zeros(N)
+    sparse[[0, 1023, 1024, 5000, N // 2, N - 1]] = (1.0, 2.0, 3.0, 1.0, 7.0, 0.5)
+    idx = torch.empty(N, dtype=torch.int32).cuda()
+    for W in (osmc.normalise(lognormal_logw(N, seed=N % 89, spread=3.0)), sparse / sparse.sum()):
+        smc.smc_resample(ctx, _cuda(W), scheme, 23, 7, idx=idx)
+        assert np.array_equal(idx.cpu().numpy(), osmc.resample_indices(W, scheme, 23, 7))
+
+
+@pytest.mark.parametrize("moves", [0, 1])
+@pytest.mark.parametrize("scheme", ["systematic", "stratified", "multinomial"])
+def test_step_resampling_of_sparse_weights(smc, ctx, scheme, moves):
+    """A step's ancestors when a wave's points span thousands of particles or sit in
+    one (the search's window in LDS holds 256): weight on every 700th particle, on
+    the last of a chunk of 2048 and the first of the next, and on one particle.
+    Equal log-weights among those with any make the weights exact on both sides."""
+    announce(f"step sparse weights {scheme} moves={moves}")
+    N = 9001
+    g = smc.Gmm.equal_weights(2, 1, 1.0)
+    y = _cuda(np.array([0.5, -1.0, 2.0]), torch.float32)
+    th = theta_prior_draws(N, 2, 1, seed=5)
+    ctx.set_resampling(scheme)
+    try:
+        for keep in (np.arange(N) % 700 == 13, np.isin(np.arange(N), (2047, 2048)),
+                     np.arange(N) == 8999):
+            logw = np.where(keep, 0.0, -np.inf)
+            W = keep / float(keep.sum())
+            ref = osmc.resample_indices(W, scheme, 31, 1)
+            t1, l1 = _cuda(np.zeros_like(th)), _cuda(np.zeros(N))
+            smc.smc_step(ctx, g, y, _cuda(th), _cuda(np.zeros(N)), t1, l1, _cuda(logw),
+                         _cuda(np.zeros(N)), _cuda(np.array([0.0, 0.0, 1.0])),
+                         torch.ones(1, dtype=torch.int32).cuda(), 0.0, moves, 31, 0.5, "fp64",
+                         _cuda(np.zeros(4)))
+            ctx.check()
+            assert np.array_equal(t1.cpu().numpy(), th[:, ref])   # moves of sd 0 stay put
+    finally:
+        ctx.set_resampling("systematic")
+
+
+@pytest.mark.parametrize("N", [1, 255, 257, 131072, 131073, 300001, 1 << 21, (1 << 21) + 1])
+def test_reweight_launch_edges(smc, ctx, N):
+    """The reweight at the edges of its launches (one element a thread, several,
+    combined by the weights' blocks up to 2^21 or by a launch of its own): logw
+    exact, W to 1e-14, ESS and evidence to 1e-12 (sums of N terms of relative error
+    2^-53 each, of one sign)."""
+    announce(f"reweight edges N={N}")
+    rng = np.random.default_rng(N)
+    logw, l = rng.normal(size=N), -50.0 + 3.0 * rng.normal(size=N)
+    logw[rng.integers(0, N)] = -np.inf if N > 1 else 0.25
+    a, W = _cuda(logw), _cuda(np.zeros(N))
+    z, e = _cuda(np.zeros(1)), _cuda(np.zeros(1))
+    smc.smc_reweight(ctx, a, _cuda(l), 0.3, W=W, logZ=z, ess=e)
+    lw = logw + 0.3 * l
+    ref = osmc.normalise(lw)
+    assert np.array_equal(a.cpu().numpy(), lw)
+    assert np.max(np.abs(W.cpu().numpy() - ref)) <= 1e-14
+    inc = osmc.reweight(logw, l, 0.3)[2]
+    assert abs(z.item() - inc) <= 1e-12 * max(1.0, abs(inc))
+    assert abs(e.item() - osmc.ess(ref)) <= 1e-11 * osmc.ess(ref)
+
+
 @pytest.mark.parametrize("scheme", ["systematic", "stratified"])
 def test_resample_sorted_points_large_n_degenerate_gather_predicate(smc, ctx, scheme):
     """Past 2^20 particles (a ragged last chunk of the CDF): equal weights, one
