@@ -124,8 +124,9 @@ const char* smc_last_error(void);
  * whose partial sums for the same 64 particles are formed by separate waves)
  * used by the likelihood kernels; 0 restores the built-in choice. Range 0..128.
  * Up to 16 slices run as the waves of one workgroup; a move with more slices
- * and N <= 32768 spreads them over up to 8 workgroups per 64 particles and
- * completes in a second, per-particle kernel. Other kernels use min(slices, 16).
+ * and N <= 32768 spreads them over up to 16 workgroups of 4 or 8 waves per 64
+ * particles and completes in a second, per-particle kernel. Other kernels use
+ * min(slices, 16).
  * Results depend on the slicing only through the order of FP64 additions and,
  * in FP32, through which of the equivalent per-datum forms (see smc_loglik) a
  * wave's slice takes and, in the pivot form, through its windows. */
@@ -230,8 +231,9 @@ int smc_rwmh_move(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n,
  *   W[p] = exp(logw[p] - m) / sum_q exp(logw[q] - m)   (out, nullable)
  *   *logZ += lse(logw_new) - lse(logw_old)  (device scalar in/out, nullable)
  *   *ess = 1 / sum W^2                      (device scalar out, nullable)
- * All three come out of one pass over (logw, loglik) plus a one-workgroup
- * combine in a fixed order (bit-reproducible). */
+ * All three come out of one pass over (logw, loglik); the workgroups that
+ * write W (one workgroup where W is not asked for or N is above 2^21) combine
+ * its partial sums in a fixed order (bit-reproducible). */
 int smc_reweight(smc_ctx ctx, double* logw, const double* loglik, int64_t N, double dbeta,
                  double* W, double* logZ, double* ess, void* stream);
 
@@ -414,10 +416,10 @@ int smc_batch_destroy(smc_batch b);
 
 /* One tempering step of every run of the batch, graph-replayable like smc_step
  * (t = *t_dev, advanced at the end):
- *   one workgroup per run: reweight, log-sum-exp, ESS and the resampling
- *   decision (ESS < ess_frac * N_r); one workgroup per resampling run:
- *   systematic resampling and gather; then n_moves (>= 1) RW-MH moves as one
- *   persistent launch over the work list (workgroups pull units from a device
+ *   reweight by chunks of each run; log-sum-exp, ESS, the resampling decision
+ *   (ESS < ess_frac * N_r) and the CDF of each run by chunks; systematic
+ *   resampling and gather of the resampling runs by chunks; then n_moves
+ *   (>= 1) RW-MH moves as one persistent launch over the work list (workgroups pull units from a device
  *   counter). run_stats: device FP64 [R][4] = {log Z (accumulated), last ESS,
  *   resample count, unused}. prec: FP32 or FP64. A run's results depend on its
  *   S only through the order of its FP64 slice sums and, in FP32, through which

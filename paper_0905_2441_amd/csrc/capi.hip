@@ -156,9 +156,20 @@ int batch_slices(const smc_ctx_s* ctx, int k, int prec, int64_t n, int64_t N) {
 // Data slices per 64-particle tile: the explicit override, else the launch
 // table, else the built-in choice: enough waves to fill 256 CUs several times
 // over (about 8192), at least 32 observations per slice (24 in FP64), and a grid
-// within 2^32 threads. More than kMaxSlices slices (small N, long data) are spread over up
-// to kMaxGroups workgroups per tile so that every CU receives work; only moves
-// with N <= kSplitCap do that, everything else stays within one workgroup.
+// within 2^32 threads. More than kMaxSlices slices (small N, long data) are
+// spread over several workgroups per tile; only moves with N <= kSplitCap do
+// that, everything else stays within one workgroup.
+//
+// A split move's workgroups have 4 or 8 waves, whichever leaves the busiest CU
+// fewer waves to run (8 on a tie: each workgroup forms the proposals anew), and
+// the last one may have waves without a slice: the slices, and with them every
+// FP32 sum, do not depend on it. Wider workgroups waste a CU's wave slots and
+// leave a long last round (k = 4, n = 3000, ten moves a step, FP32, workgroups
+// of 11 to 16 waves against these: N = 3000 10.5 -> 8.0 ms, 9000 17.9 -> 13.1,
+// 18000 28.9 -> 20.6, 25000 20.2 -> 15.7; 20 PT iterations of 8192 chains,
+// n = 10000, 1002 -> 914 us, of 500 chains, n = 8000, 499 -> 358).
+constexpr int64_t kCus = 256;
+
 Split choose_split(const smc_ctx_s* ctx, const GmmDev& g, int prec, int64_t n, int64_t N,
                    bool allow_groups) {
     const int64_t tiles = (N + kWave - 1) / kWave;
@@ -179,10 +190,18 @@ Split choose_split(const smc_ctx_s* ctx, const GmmDev& g, int prec, int64_t n, i
     if (T > n) T = n;
     if (T < 1) T = 1;
     if (!allow_groups || N > kSplitCap) T = T < kMaxSlices ? T : kMaxSlices;
-    const int64_t G = (T + kMaxSlices - 1) / kMaxSlices;
+    int64_t G = (T + kMaxSlices - 1) / kMaxSlices;
     int64_t S = (T + G - 1) / G;
     while (S > 1 && tiles * kWave * S * G >= (int64_t{1} << 32)) --S;
-    return Split{static_cast<int>(S), static_cast<int>(G)};
+    const int64_t total = S * G;
+    if (G > 1) {
+        const auto load = [&](int64_t W) {  // waves of the busiest CU
+            return (tiles * ((total + W - 1) / W) + kCus - 1) / kCus * W;
+        };
+        S = total <= kMoveGroups * 4 && load(4) < load(8) ? 4 : 8;
+        G = (total + S - 1) / S;
+    }
+    return Split{static_cast<int>(S), static_cast<int>(G), static_cast<int>(total)};
 }
 
 int choose_slices(const smc_ctx_s* ctx, const GmmDev& g, int prec, int64_t n, int64_t N) {
@@ -330,7 +349,7 @@ int smc_create(smc_ctx* out, int device) {
     const size_t b_dd = align_up(sizeof(double) * 2 * kMaxChunks);
     const size_t b_st = align_up(sizeof(int));
     const size_t b_state = align_up(sizeof(StepState));
-    const size_t b_mv = align_up(sizeof(double) * kMaxGroups * kSplitCap);
+    const size_t b_mv = align_up(sizeof(double) * kMoveGroups * kSplitCap);
     const size_t b_anc = align_up(sizeof(int) * kSplitCap);
     const size_t b_fsv = align_up(sizeof(double) * kMaxRedBlocks * 2 * SMC_FSV_KMAX);
     const size_t total = b_part + b_sq + b_dd + b_st + b_state + b_mv + b_anc + b_fsv;

@@ -105,6 +105,27 @@ __device__ __forceinline__ void chain_reweight(const MoveStep& ms, int p, int N,
     if (lane_id() == 0) ms.next_part[tile] = RwPartial{0.0, 0.0, nw.m, nw.s1, nw.s2, 0.0};
 }
 
+// The slices of a split move: n = nsl * q + r divided on the host, so that a
+// wave's bounds cost no 64-bit division (0.8 us at the head of every wave).
+struct SliceMap {
+    int nsl, q, r;
+    float inv;  // 1 / nsl
+};
+
+SliceMap slice_map(int n, int nsl) { return SliceMap{nsl, n / nsl, n % nsl, 1.0f / nsl}; }
+
+// slice_bounds of slice sl, and an empty slice [n, n) for sl >= nsl. r * sl is
+// below 2^14 (nsl <= kMaxSlices * kMaxGroups = 128), and (x + 1/2) / nsl lies at
+// least 1/256 from a whole number, so its FP32 value rounds down to x / nsl.
+__device__ __forceinline__ void move_slice(int n, int sl, const SliceMap& sm, int& j0, int& j1) {
+    const int x0 = sm.r * sl, x1 = x0 + sm.r;
+    const int a = sm.q * sl + static_cast<int>((static_cast<float>(x0) + 0.5f) * sm.inv);
+    const int b = sm.q * (sl + 1) + static_cast<int>((static_cast<float>(x1) + 0.5f) * sm.inv);
+    const bool blocks = sm.q >= 64;
+    j0 = wave_uniform(sl >= sm.nsl ? n : blocks ? a & ~7 : a);
+    j1 = wave_uniform(sl + 1 >= sm.nsl ? n : blocks ? b & ~7 : b);
+}
+
 // CHAIN: the move also makes the next tempering step's reweight (ms.lw_next set,
 // one workgroup per tile); a separate instantiation keeps the plain move's code
 // free of it.
@@ -113,7 +134,7 @@ __global__ void __launch_bounds__(1024)
 k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
        const double* __restrict__ beta_vec, StepSrc src, double sd, uint64_t seed,
        uint32_t move, GmmDev g, unsigned long long* n_acc, int* status, MoveStep ms, int G,
-       double* __restrict__ part, int* __restrict__ anc_out) {
+       SliceMap sm, double* __restrict__ part, int* __restrict__ anc_out) {
     constexpr int KD = K * D;
     constexpr bool kRows = D == 1;
     // the current state held in LDS for the decision (small k*d)
@@ -137,10 +158,9 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
     const int grp = static_cast<int>(blockIdx.x) - tile * G;
     const int p = tile * kWave + lane;
     const int pc = p < N ? p : N - 1;
-    const int nsl = S * G;
     const int sl = grp * S + w;
     int j0, j1;
-    slice_bounds(n, sl, nsl, j0, j1);
+    move_slice(n, sl, sm, j0, j1);
     // the lane's first datum of the slice for the pivot form, loaded ahead
     // of the ancestor search and the proposals (their barriers and Box-Muller
     // work hide its latency)
@@ -645,6 +665,25 @@ k_pt_deferred_exchange(const double* __restrict__ th_in, const double* __restric
     l_out[c] = l_in[src];
 }
 
+// The G groups' partial sums of particle p, added in group order. All are
+// requested at once (beyond G the last one again), before the caller draws its
+// random numbers: one after another they took 0.6 us more a launch at G = 8.
+struct GroupSums {
+    double v[kMoveGroups];
+    __device__ __forceinline__ GroupSums(const double* __restrict__ part, int N, int p, int G) {
+#pragma unroll
+        for (int q = 0; q < kMoveGroups; ++q)
+            v[q] = part[static_cast<size_t>(q < G ? q : G - 1) * N + p];
+    }
+    __device__ __forceinline__ double total(int G) const {
+        double tot = v[0];
+#pragma unroll
+        for (int q = 1; q < kMoveGroups; ++q)
+            if (q < G) tot += v[q];
+        return tot;
+    }
+};
+
 // Second half of a move whose tile data were split over G workgroups, for
 // particle p: add the G partial sums in group order, re-form the same proposal
 // (same counter, same arithmetic) and take the MH decision.
@@ -658,18 +697,20 @@ __device__ __forceinline__ bool complete_split_move(int p, int n, double* theta,
     const bool fused = (ms.cdf_hi != nullptr) && (ms.state != nullptr) && (ms.state->resampled != 0);
     const MoveSource srcs = move_source(ms, theta, l);
     const int a = fused ? anc_in[p] : p;
+    const GroupSums sums(part, N, p, G);
     double pr[KD];
+#pragma unroll
+    for (int c = 0; c < KD; ++c) pr[c] = srcs.th[static_cast<size_t>(c) * N + a];
+    const double lu = rwmh_log_u(static_cast<uint32_t>(p), step, seed, move);
     {
         double z[KD];
         normals<KD>(seed, static_cast<uint32_t>(p), step, kProp, move, z);
 #pragma unroll
-        for (int c = 0; c < KD; ++c) pr[c] = srcs.th[static_cast<size_t>(c) * N + a] + sd * z[c];
+        for (int c = 0; c < KD; ++c) pr[c] += sd * z[c];
     }
-    double tot = part[p];
-    for (int q = 1; q < G; ++q) tot += part[static_cast<size_t>(q) * N + p];
-    const double l_prop = finish_loglik<PREC>(tot, n, g);
+    const double l_prop = finish_loglik<PREC>(sums.total(G), n, g);
     return rwmh_accept<KD>(p, a, N, [&](int c) { return pr[c]; }, l_prop, srcs, theta, l,
-                           beta_vec, src, step, seed, move, g, status, ms);
+                           beta_vec, src, step, seed, move, g, status, ms, nullptr, &lu);
 }
 
 __device__ __forceinline__ void count_accepts(bool acc, unsigned long long* n_acc) {
@@ -680,7 +721,7 @@ __device__ __forceinline__ void count_accepts(bool acc, unsigned long long* n_ac
 
 // One thread per particle completes a split move.
 template <int KD, int PREC>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kWave)
 k_rwmh_accept(int n, double* theta, double* l, int N, const double* __restrict__ beta_vec,
               StepSrc src, double sd, uint64_t seed, uint32_t move, GmmDev g,
               unsigned long long* n_acc, int* status, MoveStep ms, int G,
@@ -705,7 +746,7 @@ k_rwmh_accept(int n, double* theta, double* l, int N, const double* __restrict__
 // the pairs are disjoint. The iteration index comes from the step state
 // recorded by the move; the caller's counter is advanced.
 template <int KD, int PREC>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kWave)
 k_pt_accept_exchange(int n, double* theta, double* l, int M, const double* __restrict__ beta,
                      StepSrc src, double sd, uint64_t seed, GmmDev g, int G,
                      const double* __restrict__ part, int parity_mode, int wrap, int* t_advance,
@@ -725,24 +766,25 @@ k_pt_accept_exchange(int n, double* theta, double* l, int M, const double* __res
     for (int k = 0; k < KD; ++k) th[k] = 0.0;
     double lc = 0.0;
     bool acc = false;
+    double swap_lu = 0.0;
     if (active) {
+        const GroupSums sums(part, M, c, G);
+        const double l_cur = l[c];
         double pr[KD];
+#pragma unroll
+        for (int k = 0; k < KD; ++k) th[k] = theta[static_cast<size_t>(k) * M + c];
+        const double lu = rwmh_log_u(static_cast<uint32_t>(c), it, seed, 0u);
+        swap_lu = pt_log_u(a, seed, it);
         {
             double z[KD];
             normals<KD>(seed, static_cast<uint32_t>(c), it, kProp, 0, z);
 #pragma unroll
-            for (int k = 0; k < KD; ++k) {
-                th[k] = theta[static_cast<size_t>(k) * M + c];
-                pr[k] = th[k] + sd * z[k];
-            }
+            for (int k = 0; k < KD; ++k) pr[k] = th[k] + sd * z[k];
         }
-        double tot = part[c];
-        for (int q = 1; q < G; ++q) tot += part[static_cast<size_t>(q) * M + c];
-        const double l_prop = finish_loglik<PREC>(tot, n, g);
-        const double l_cur = l[c];
+        const double l_prop = finish_loglik<PREC>(sums.total(G), n, g);
         acc = rwmh_decide<KD>(
             c, [&](int k) { return pr[k]; }, [&](int k) { return th[k]; }, l_cur, l_prop, beta,
-            src, it, seed, 0u, g);
+            src, it, seed, 0u, g, &lu);
         if (l_prop != l_prop) atomicOr(status, kStatusNaN);
         lc = acc ? l_prop : l_cur;
         if (acc) {
@@ -760,7 +802,7 @@ k_pt_accept_exchange(int n, double* theta, double* l, int M, const double* __res
         const double l_a = odd ? lp : lc;
         const double l_b = odd ? lc : lp;
         const double la = (beta[a] - beta[b]) * (l_b - l_a);
-        swap = la >= 0.0 || pt_log_u(a, seed, it) < la;
+        swap = la >= 0.0 || swap_lu < la;
     }
     if (active) {
 #pragma unroll
@@ -879,8 +921,9 @@ hipError_t launch_loglik(const GmmDev& g, const float* y, int64_t n, const doubl
 namespace {
 
 bool valid_split(const Split& sp, int64_t N) {
-    return sp.groups >= 1 && sp.groups <= kMaxGroups && sp.slices >= 1 &&
-           sp.slices <= kMaxSlices && (sp.groups == 1 || N <= kSplitCap);
+    return sp.groups >= 1 && sp.groups <= kMoveGroups && sp.slices >= 1 &&
+           sp.slices <= kMaxSlices && (sp.groups == 1 || N <= kSplitCap) && sp.total >= 1 &&
+           sp.total <= sp.slices * sp.groups;
 }
 
 // The likelihood half of a move (with the decision when groups == 1).
@@ -897,14 +940,15 @@ hipError_t launch_move_partials(const float* y, int64_t n, double* theta, double
     if (nch < 0 || nch > kMaxChunks) return hipErrorInvalidValue;
     const size_t lds = rwmh_dyn_lds_bytes(sp.slices, nch, D == 1);
     if (lds > kMaxRwmhLds) return hipErrorInvalidValue;
+    const SliceMap sm = slice_map(static_cast<int>(n), sp.total);
     if (ms.lw_next != nullptr)
         hipLaunchKernelGGL((k_rwmh<K, D, P, true>), grid, block, lds, s, y, static_cast<int>(n),
                            theta, l, static_cast<int>(N), beta_vec, src, sd, seed, move, g,
-                           n_accept, sc.status, ms, sp.groups, sc.mv_part, sc.mv_anc);
+                           n_accept, sc.status, ms, sp.groups, sm, sc.mv_part, sc.mv_anc);
     else
         hipLaunchKernelGGL((k_rwmh<K, D, P, false>), grid, block, lds, s, y, static_cast<int>(n),
                            theta, l, static_cast<int>(N), beta_vec, src, sd, seed, move, g,
-                           n_accept, sc.status, ms, sp.groups, sc.mv_part, sc.mv_anc);
+                           n_accept, sc.status, ms, sp.groups, sm, sc.mv_part, sc.mv_anc);
     return hipSuccess;
 }
 
@@ -916,7 +960,7 @@ hipError_t launch_rwmh(const GmmDev& g, const float* y, int64_t n, double* theta
                        unsigned long long* n_accept, Split sp, const Scratch& sc, MoveStep ms,
                        hipStream_t s) {
     if (!valid_split(sp, N)) return hipErrorInvalidValue;
-    const dim3 agrid(static_cast<unsigned>((N + 255) / 256));
+    const dim3 agrid(static_cast<unsigned>((N + kWave - 1) / kWave));
 #define SMC_MOVE(K, D, P)                                                                      \
     do {                                                                                       \
         const hipError_t e0 = launch_move_partials<K, D, P>(y, n, theta, l, N, beta_vec, src,  \
@@ -924,7 +968,7 @@ hipError_t launch_rwmh(const GmmDev& g, const float* y, int64_t n, double* theta
                                                             sc, ms, s);                        \
         if (e0 != hipSuccess) return e0;                                                       \
         if (sp.groups > 1)                                                                     \
-            hipLaunchKernelGGL((k_rwmh_accept<K * D, P>), agrid, dim3(256), 0, s,              \
+            hipLaunchKernelGGL((k_rwmh_accept<K * D, P>), agrid, dim3(kWave), 0, s,            \
                                static_cast<int>(n), theta, l, static_cast<int>(N), beta_vec,   \
                                src, sd, seed, move, g, n_accept, sc.status, ms, sp.groups,     \
                                static_cast<const double*>(sc.mv_part),                         \
@@ -1102,14 +1146,14 @@ hipError_t launch_pt_iteration(const GmmDev& g, const float* y, int64_t n, doubl
                                t_advance, n_swap, s);
     }
     // slots: at most M/2 pairs plus two singles, two threads each
-    const dim3 xgrid(static_cast<unsigned>((2 * (M / 2 + 2) + 255) / 256));
+    const dim3 xgrid(static_cast<unsigned>((2 * (M / 2 + 2) + kWave - 1) / kWave));
 #define SMC_PT(K, D, P)                                                                        \
     do {                                                                                       \
         const hipError_t e0 = launch_move_partials<K, D, P>(y, n, theta, l, M, beta, src, sd,  \
                                                             seed, 0, g, n_accept, sp, sc, ms,  \
                                                             s);                                \
         if (e0 != hipSuccess) return e0;                                                       \
-        hipLaunchKernelGGL((k_pt_accept_exchange<K * D, P>), xgrid, dim3(256), 0, s,           \
+        hipLaunchKernelGGL((k_pt_accept_exchange<K * D, P>), xgrid, dim3(kWave), 0, s,           \
                            static_cast<int>(n), theta, l, static_cast<int>(M), beta, later,    \
                            sd, seed, g, sp.groups, static_cast<const double*>(sc.mv_part),     \
                            parity_mode, wrap, t_advance, n_accept, n_swap, sc.status);         \

@@ -8,7 +8,8 @@
 namespace smc {
 
 constexpr int kMaxSlices = 16;          // waves per workgroup in the likelihood kernels
-constexpr int kMaxGroups = 8;           // workgroups sharing one 64-particle tile's data
+constexpr int kMaxGroups = 8;           // kMaxSlices * kMaxGroups: most slices of a tile's data
+constexpr int kMoveGroups = 16;         // workgroups a split move's launch may take per tile
 constexpr int kSplitCap = 32768;        // largest N whose move may use several groups
 constexpr int kRedBlock = 256;          // threads per block in the weight/resample kernels
 constexpr int kMaxRedBlocks = 1024;     // grid cap of the grid-stride weight kernels
@@ -70,7 +71,7 @@ struct Scratch {
     double* mm_prop;           // MFMA path: proposals [64][mm_n_cap]
     double* mm_part;           // MFMA path: per-slice partial sums [16][mm_n_cap]
     int64_t mm_rows_cap, mm_n_cap;
-    double* mv_part;           // split move: partial sums [kMaxGroups][kSplitCap]
+    double* mv_part;           // split move: partial sums [kMoveGroups][kSplitCap]
     int* mv_anc;               // split move: ancestors of the fused resampling [kSplitCap]
 };
 
@@ -136,13 +137,14 @@ struct MoveStep {
     int t_max;
 };
 
-// Launch shape of a VALU move for one 64-particle tile: `groups` workgroups of
-// `slices` waves split the observations into groups * slices contiguous slices.
-// With groups > 1 each workgroup writes its partial sums to scratch and a
+// Launch shape of a VALU move for one 64-particle tile: the observations are
+// split into `total` contiguous slices, one per wave of `groups` workgroups of
+// `slices` waves; the last group's waves beyond `total` hold none. With groups > 1 each workgroup writes its partial sums to scratch and a
 // per-particle kernel completes the move.
 struct Split {
     int slices;
     int groups;
+    int total;
 };
 
 // How the CDF kernels obtain the normalised weights: read W, or form

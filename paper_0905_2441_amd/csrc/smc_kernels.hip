@@ -1,8 +1,9 @@
 // Weight, resampling and exchange kernels (FP64) for gfx950.
 //
 // Grid-wide reductions never communicate between workgroups inside a kernel:
-// a streaming kernel writes one partial per workgroup and a one-workgroup
-// kernel combines them in block order. On MI355X a device-scope fence inside a
+// a streaming kernel writes one partial per workgroup and the next launch
+// combines them in block order, in one workgroup or, where that launch streams
+// too, in each of its workgroups. On MI355X a device-scope fence inside a
 // kernel writes back and invalidates the L2 of the issuing XCD, so per-block
 // "last block finishes" tickets cost far more than the kernel boundary they
 // would save. Combining in a fixed order keeps every result bit-reproducible.
@@ -16,8 +17,8 @@
 // Systematic resampling (Sequential Monte Carlo subsection: the empirical CDF
 // of the weights, sampled N times) builds the CDF with a double-double scan:
 // each chunk's workgroup stores within-chunk inclusive prefixes and the chunk
-// total; the search kernel forms the chunk offsets once per workgroup in LDS
-// and rounds offset + prefix once, so every C_j is the correctly rounded
+// total; the search forms the chunk offsets once per workgroup in LDS, or reads
+// those of a launch of their own beyond kLdsChunks chunks, and rounds offset + prefix once, so every C_j is the correctly rounded
 // prefix sum (up to double-double error, about 2^-104 relative). Both kernels
 // can be predicated on the device-side ESS test.
 #include "internal.hpp"
@@ -213,10 +214,10 @@ __device__ __forceinline__ double weight_at(const WeightSrc& w, int j) {
 }
 
 // Standalone resampling (smc_resample*) in three passes over chunks of
-// kResChunk elements: (1) each chunk's within-chunk prefixes and total; (2) one
-// workgroup scans the chunk totals into chunk offsets; (3) search and gather,
-// reading C_j = offset + prefix (rounded once) with the offsets in memory, so
-// no workgroup rescans the totals.
+// kResChunk elements: (1) each chunk's within-chunk prefixes and total; (2) beyond
+// kLdsChunks chunks, the totals scanned into chunk offsets; (3) search and gather
+// with C_j = offset + prefix (rounded once), the offsets from memory or, up to
+// kLdsChunks chunks, scanned by each workgroup into LDS without a second launch.
 constexpr int kResPer = 4;
 constexpr int kResChunk = kRedBlock * kResPer;
 

@@ -332,6 +332,43 @@ def test_rwmh_move_matches_oracle(smc, ctx, prec, slices):
     assert rel_err(got_l[same], l_ref[same]).max() <= tol
 
 
+@pytest.mark.parametrize("slices,N", [(17, 130), (33, 700), (60, 9000), (66, 64), (128, 300),
+                                      (32, 16400)])
+@pytest.mark.parametrize("pt", [False, True])
+def test_split_move_launch_shapes(smc, ctx, slices, N, pt):
+    """Moves and PT iterations spread over workgroups of 4 or 8 waves, some of
+    whose last waves hold no slice, against 16 slices in one workgroup. FP64: 513
+    data summed in another order, so log-likelihoods agree to 513 ulps (1e-13);
+    the decisions are the same."""
+    announce(f"split move slices={slices} N={N} pt={pt}")
+    mu = np.array([-3.0, 0.0, 3.0, 6.0])
+    yd = _cuda(make_mixture_data(513, mu, 0.55, seed=2), torch.float32)
+    g = smc.Gmm.equal_weights(4, 1, 0.55)
+    th0 = _cuda(theta_near_posterior(N, mu, seed=4))
+    out = []
+    for s in (slices, 16):
+        tt, lt = th0.clone(), torch.empty(N, dtype=torch.float64).cuda()
+        acc = torch.zeros(1, dtype=torch.int64).cuda()
+        ctx.set_slices(16)
+        try:
+            smc.smc_loglik(ctx, g, yd, tt, prec="fp64", out=lt)
+            ctx.set_slices(s)
+            if pt:
+                it = torch.zeros(1, dtype=torch.int32).cuda()
+                smc.pt_iteration(ctx, g, yd, tt, lt, _cuda(pt_betas(N, 4)), it, 0.1, 41,
+                                 prec="fp64", n_accept=acc)
+            else:
+                smc.smc_rwmh_move(ctx, g, yd, tt, lt, 0.4, 0.1, seed=11, step=6, move=2,
+                                  prec="fp64", n_accept=acc)
+            ctx.check()
+        finally:
+            ctx.set_slices(0)
+        out.append((tt.cpu().numpy(), lt.cpu().numpy(), acc.item()))
+    assert 0 < out[0][2] == out[1][2]
+    assert np.array_equal(out[0][0], out[1][0])
+    assert rel_err(out[0][1], out[1][1]).max() <= 1.2e-13
+
+
 def test_rwmh_per_chain_beta_and_box_prior(smc, ctx):
     announce("rwmh beta_vec box")
     mu = np.array([-2.0, 2.0])
