@@ -414,13 +414,21 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
                      smc_batch* out);
 int smc_batch_destroy(smc_batch b);
 
+/* The start of every run of the batch: run r's theta_0 from the prior with its
+ * own seed (smc_prior_init) and its log-likelihood (smc_loglik with its own data
+ * slices), each bit for bit what those calls give for the run alone, in two
+ * launches while the slices chosen for the runs are those in force when the
+ * batch was created (else two a run). prec: FP32 or FP64. */
+int smc_batch_init(smc_ctx ctx, smc_batch b, const smc_gmm* model, const float* y, double* theta,
+                   double* loglik, smc_prec prec, void* stream);
+
 /* One tempering step of every run of the batch, graph-replayable like smc_step
  * (t = *t_dev, advanced at the end):
  *   reweight by chunks of each run; log-sum-exp, ESS, the resampling decision
  *   (ESS < ess_frac * N_r) and the CDF of each run by chunks; systematic
  *   resampling and gather of the resampling runs by chunks; then n_moves
- *   (>= 1) RW-MH moves as one persistent launch over the work list (workgroups pull units from a device
- *   counter). run_stats: device FP64 [R][4] = {log Z (accumulated), last ESS,
+ *   (>= 1) RW-MH moves as one persistent launch over the work list (workgroups
+ *   pull units from a device counter). run_stats: device FP64 [R][4] = {log Z (accumulated), last ESS,
  *   resample count, unused}. prec: FP32 or FP64. A run's results depend on its
  *   S only through the order of its FP64 slice sums and, in FP32, through which
  *   of the per-datum forms a wave takes and its data centre (see smc_loglik). */

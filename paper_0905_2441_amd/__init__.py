@@ -30,6 +30,7 @@ from .api import (  # noqa: F401
     smc_sort_data,
     smc_step,
     smc_steps,
+    smc_batch_init,
     smc_step_batched,
 )
 from .samplers import (BatchSampler, FSVFilter, PTSampler, SMCSampler,  # noqa: F401

@@ -113,6 +113,7 @@ SIGNATURES = {
                              c_int32, c_int32, c_int, _P, _P, _P]),
     "smc_batch_create": (c_int, [_P, POINTER(SmcRunDesc), c_int32, c_int32, POINTER(c_void_p)]),
     "smc_batch_destroy": (c_int, [_P]),
+    "smc_batch_init": (c_int, [_P, _P, _GP, _P, _P, _P, c_int, _P]),
     "smc_step_batched": (c_int, [_P, _P, _GP, _P, _P, _P, _P, _P, _P, c_int32, _P, c_double,
                                  c_int32, c_double, c_int, _P, _P, _P]),
     "smc_graph_begin": (c_int, [_P, _P]),

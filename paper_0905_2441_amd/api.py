@@ -431,6 +431,15 @@ class Batch:
             pass
 
 
+def smc_batch_init(ctx: Context, batch: Batch, model: Gmm, y, theta, loglik, prec="fp32",
+                   stream=None):
+    """Prior draws and log-likelihoods of every run of ``batch``."""
+    L.check(ctx._lib.smc_batch_init(
+        ctx.handle, batch.handle, ctypes.byref(model.struct()), _ptr(y, torch.float32, "y"),
+        _ptr(theta, torch.float64, "theta"), _ptr(loglik, torch.float64, "loglik"), _prec(prec),
+        _stream(stream)))
+
+
 def smc_step_batched(ctx: Context, batch: Batch, model: Gmm, y, theta, loglik, logw, W, beta,
                      t_dev, step_sd, n_moves, ess_frac, prec, run_stats, n_accept=None,
                      stream=None):

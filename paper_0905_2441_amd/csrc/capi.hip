@@ -1225,7 +1225,19 @@ int smc_rng_normals(uint64_t seed, int64_t count, int32_t per_index, uint32_t st
 
 // ---------------------------------------------------------------- batched runs
 
+// Data slices of every run's log-likelihood, as a call for the run alone would
+// choose them.
+std::vector<int> init_slices(const smc_ctx_s* ctx, const GmmDev& g, int prec,
+                             const std::vector<smc_run_desc>& runs) {
+    std::vector<int> S(runs.size());
+    for (size_t i = 0; i < runs.size(); ++i)
+        S[i] = choose_slices(ctx, g, prec, runs[i].n, runs[i].N);
+    return S;
+}
+
 struct smc_batch_s {
+    std::vector<smc_run_desc> runs;
+    std::vector<int> slices[2];  // init_slices behind dev.init_units
     int device = 0;
     BatchDev dev{};
     void* mem = nullptr;
@@ -1273,6 +1285,26 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
                 units[pi].push_back(BatchUnit{i, t, std::min(per, tiles - t), S});
         }
     }
+    // units of the first log-likelihood: slices as for the run alone, longest first
+    GmmDev shape{};
+    shape.k = kd;
+    shape.d = 1;
+    const std::vector<smc_run_desc> descs(runs, runs + R);
+    std::vector<int> slices[2];
+    std::vector<BatchUnit> iunits[2];
+    for (int pi = 0; pi < 2; ++pi) {
+        slices[pi] = init_slices(ctx, shape, pi == 1 ? SMC_PREC_FP32 : SMC_PREC_FP64, descs);
+        std::vector<int> by(order);
+        std::stable_sort(by.begin(), by.end(), [&](int a, int b) {
+            return runs[a].n / slices[pi][a] > runs[b].n / slices[pi][b];
+        });
+        for (int i : by) {
+            const int per = kMaxSlices / slices[pi][i];
+            const int tiles = (runs[i].N + 63) / 64;
+            for (int t = 0; t < tiles; t += per)
+                iunits[pi].push_back(BatchUnit{i, t, std::min(per, tiles - t), slices[pi][i]});
+        }
+    }
     std::vector<BatchRun> rd(R);
     std::vector<BatchChunk> chunks;
     for (int i = 0; i < R; ++i) {
@@ -1293,8 +1325,10 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
     const size_t b_ch = align_up(sizeof(BatchChunk) * chunks.size());
     const size_t b_part = align_up(sizeof(RwPartial) * chunks.size());
     const size_t b_tot = align_up(sizeof(double) * 2 * chunks.size());
+    const size_t b_i0 = align_up(sizeof(BatchUnit) * iunits[0].size());
+    const size_t b_i1 = align_up(sizeof(BatchUnit) * iunits[1].size());
     const size_t total = b_runs + b_items + b_work + b_state + 2 * b_cdf + b_th + b_l + b_ch +
-                         b_part + b_tot;
+                         b_part + b_tot + b_i0 + b_i1;
     void* p = nullptr;
     if (hipMalloc(&p, total) != hipSuccess) return fail(SMC_ERR_NOMEM, "batch allocation failed");
     smc_batch b = new (std::nothrow) smc_batch_s();
@@ -1327,15 +1361,25 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
     d.n_chunks = static_cast<int>(chunks.size());
     d.part = reinterpret_cast<RwPartial*>(c + b_ch);
     d.chunk_tot = reinterpret_cast<double*>(c + b_ch + b_part);
+    c += b_ch + b_part + b_tot;
+    d.init_units[0] = reinterpret_cast<BatchUnit*>(c);
+    d.init_units[1] = reinterpret_cast<BatchUnit*>(c + b_i0);
     d.move_grid = batch_move_grid();
     hipError_t e = hipMemset(p, 0, total);
     if (e == hipSuccess) e = hipMemcpy(d.runs, rd.data(), sizeof(BatchRun) * R, hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(d.chunks, chunks.data(), sizeof(BatchChunk) * chunks.size(),
                       hipMemcpyHostToDevice);
-    for (int pi = 0; pi < 2 && e == hipSuccess; ++pi)
+    for (int pi = 0; pi < 2 && e == hipSuccess; ++pi) {
         e = hipMemcpy(d.units[pi], units[pi].data(), sizeof(BatchUnit) * units[pi].size(),
                       hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy(d.init_units[pi], iunits[pi].data(),
+                          sizeof(BatchUnit) * iunits[pi].size(), hipMemcpyHostToDevice);
+        d.n_init_units[pi] = static_cast<int>(iunits[pi].size());
+        b->slices[pi] = slices[pi];
+    }
+    b->runs = descs;
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         (void)hipFree(p);
@@ -1352,6 +1396,35 @@ int smc_batch_destroy(smc_batch b) {
     (void)hipDeviceSynchronize();
     if (b->mem) (void)hipFree(b->mem);
     delete b;
+    return SMC_OK;
+}
+
+int smc_batch_init(smc_ctx ctx, smc_batch b, const smc_gmm* model, const float* y, double* theta,
+                   double* loglik, smc_prec prec, void* stream) {
+    int r = enter(ctx);
+    if (r) return r;
+    if (!b) return fail(SMC_ERR_INVALID_ARG, "batch is NULL");
+    GmmDev g;
+    if ((r = check_model(model, &g))) return r;
+    if (g.d != 1 || g.k * g.d != b->kd)
+        return fail(SMC_ERR_INVALID_ARG, "model does not match the batch (d = 1, k*d = kd)");
+    if (prec != SMC_PREC_FP32 && prec != SMC_PREC_FP64)
+        return fail(SMC_ERR_UNSUPPORTED, "batched runs use FP32 or FP64");
+    if (!y || !theta || !loglik) return fail(SMC_ERR_INVALID_ARG, "NULL array");
+    const hipStream_t s = as_stream(stream);
+    // other slices in force now than at the batch's creation: a launch per run
+    if (init_slices(ctx, g, prec, b->runs) != b->slices[prec == SMC_PREC_FP32 ? 1 : 0]) {
+        for (const smc_run_desc& d : b->runs) {
+            double* th = theta + static_cast<int64_t>(b->kd) * d.p_off;
+            if ((r = smc_prior_init(ctx, model, d.N, d.seed, th, stream))) return r;
+            if ((r = smc_loglik(ctx, model, y + d.y_off, d.n, th, d.N, prec, loglik + d.p_off,
+                                stream)))
+                return r;
+        }
+        return SMC_OK;
+    }
+    const hipError_t e = launch_batch_init(b->dev, g, y, theta, loglik, prec, ctx->sc.status, s);
+    if (e != hipSuccess) return hip_fail(e, "batched initialisation launch");
     return SMC_OK;
 }
 

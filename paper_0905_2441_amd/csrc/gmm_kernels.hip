@@ -819,23 +819,7 @@ template <int KD>
 __global__ void k_prior(int N, uint64_t seed, GmmDev g, double* __restrict__ theta) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= N) return;
-    if (g.prior == SMC_PRIOR_GAUSS) {
-        double z[KD];
-        normals<KD>(seed, static_cast<uint32_t>(p), 0, kPrior, 0, z);
-#pragma unroll
-        for (int c = 0; c < KD; ++c) theta[static_cast<size_t>(c) * N + p] = g.pa + g.pb * z[c];
-    } else {
-        const double width = g.pb - g.pa;
-#pragma unroll
-        for (int b = 0; b < (KD + 3) / 4; ++b) {
-            const Words4 w = draw(seed, static_cast<uint32_t>(p), b, 0, kPrior, 0);
-            const uint32_t ws[4] = {w.w0, w.w1, w.w2, w.w3};
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (4 * b + q < KD)
-                    theta[static_cast<size_t>(4 * b + q) * N + p] = g.pa + width * u01_open(ws[q]);
-        }
-    }
+    prior_draw<KD>(p, N, seed, g, theta);
 }
 
 }  // namespace

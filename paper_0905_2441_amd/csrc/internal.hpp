@@ -179,6 +179,8 @@ struct BatchDev {
     BatchRun* runs;            // [R]
     BatchUnit* units[2];       // work lists of the FP64 [0] and FP32 [1] moves, longest data first
     int n_units[2];
+    BatchUnit* init_units[2];  // tiles of the first log-likelihood, longest slices first
+    int n_init_units[2];
     unsigned* work;            // work-queue counter, zero between launches
     StepState* state;          // [R]
     BatchChunk* chunks;        // [n_chunks] every run's chunks, run by run
@@ -192,6 +194,10 @@ struct BatchDev {
     int move_grid;             // persistent grid size
 };
 int batch_move_grid();
+// Every run's prior draw and log-likelihood, two launches. The units' slices and
+// tiles fill workgroups of kMaxSlices waves.
+hipError_t launch_batch_init(const BatchDev& b, const GmmDev& g, const float* y, double* theta,
+                             double* l, int prec, int* status, hipStream_t s);
 hipError_t launch_batch_step(const BatchDev& b, const GmmDev& g, const float* y, double* theta,
                              double* l, double* logw, double* W, const double* beta, int T,
                              int* t_dev, double sd, int n_moves, double ess_frac, int prec,

@@ -31,8 +31,8 @@ import numpy as np
 import torch
 
 from .api import (Batch, Context, Gmm, Graph, fsv_init, fsv_step, fsv_steps, pt_iteration,
-                  pt_iterations, pt_record, smc_loglik, smc_prior_init, smc_sort_data,
-                  smc_step, smc_step_batched, smc_steps)
+                  pt_iterations, pt_record, smc_batch_init, smc_loglik, smc_prior_init,
+                  smc_sort_data, smc_step, smc_step_batched, smc_steps)
 
 
 def _dev(x, dtype):
@@ -297,12 +297,8 @@ class BatchSampler:
 
     def init(self):
         with torch.cuda.stream(self.stream):
-            for r in range(self.R):
-                smc_prior_init(self.ctx, self.model, self.Ns[r], self.seeds[r],
-                               out=self.theta_of(r), stream=self.stream)
-                a = int(self.y_off[r])
-                smc_loglik(self.ctx, self.model, self.y[a:a + self.ns[r]], self.theta_of(r),
-                           self.prec, out=self._slice(self.loglik, r), stream=self.stream)
+            smc_batch_init(self.ctx, self.batch, self.model, self.y, self.theta, self.loglik,
+                           self.prec, stream=self.stream)
             self.logw.zero_()
             self.t.fill_(1)
             self.stats.zero_()

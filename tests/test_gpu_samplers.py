@@ -765,6 +765,37 @@ def test_batched_full_workload_fp32_replayed_by_oracle(smc, ctx):
     print(f"batched full workload fp32: runs {picked}, flips {flips} of {decisions}")
 
 
+@pytest.mark.parametrize("k,prior", [(4, "gauss"), (1, "box"), (8, "gauss")])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_batch_init_equals_single_calls(smc, ctx, k, prior, prec):
+    """The joint initialisation gives each run the bits of its own prior and
+    log-likelihood calls: one particle, ragged tiles and chunks, 1 to 16 slices
+    (some not dividing 16), and slices changed after the batch was made (3)."""
+    announce(f"batch init k={k} {prior} {prec}")
+    g = smc.Gmm.equal_weights(k, 1, 0.55, prior=prior, prior_a=-8.0 if prior == "box" else 0.0,
+                              prior_b=8.0 if prior == "box" else 4.0)
+    Ns, ns = [1, 63, 2049, 70000, 300, 9000], [5, 2000, 100, 40, 171, 400]
+    datas = [make_mixture_data(n, np.array([-3.0, 3.0]), 0.55, seed=90 + n) for n in ns]
+    seeds = [400 + i for i in range(len(Ns))]
+    b = smc.BatchSampler(ctx, g, datas, Ns, seeds, beta_schedule(4, "linear"), 0.5, 1, prec=prec)
+    for slices in (0, 3):
+        ctx.set_slices(slices)
+        try:
+            b.theta.fill_(-1.0)
+            b.loglik.fill_(-1.0)
+            b.init()
+            ctx.check(b.stream)
+            for r, N in enumerate(Ns):
+                th = smc.smc_prior_init(ctx, g, N, seeds[r])
+                a = int(b.y_off[r])
+                l = smc.smc_loglik(ctx, g, b.y[a:a + ns[r]], th, prec=prec)
+                torch.cuda.synchronize()
+                assert torch.equal(b.theta_of(r), th), (slices, r)
+                assert torch.equal(b.loglik[int(b.p_off[r]):int(b.p_off[r]) + N], l), (slices, r)
+        finally:
+            ctx.set_slices(0)
+
+
 @pytest.mark.parametrize("scheme", ["systematic", "stratified", "multinomial"])
 def test_batched_runs_at_chunk_edges_equal_single_runs(smc, ctx, scheme):
     """Batched runs whose sizes sit at the edges of the 2048-particle chunks that
