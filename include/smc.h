@@ -135,7 +135,7 @@ int smc_set_slices(smc_ctx ctx, int32_t slices);
 /* Which launches a rule of the launch table shapes. */
 enum {
     SMC_RULE_CALL = 0,    /* the likelihood and move kernels of every per-call entry point */
-    SMC_RULE_BATCH = 1    /* the persistent move of smc_step_batched, per run */
+    SMC_RULE_BATCH = 1    /* the move of smc_step_batched, per run */
 };
 
 /* One entry of a context's launch table (the output of the autotuner in the
@@ -144,7 +144,7 @@ enum {
  * (same meaning and range as smc_set_slices; the MFMA form uses
  * min(slices, 16)). kind SMC_RULE_BATCH: in a batch created while the rule is
  * in force, every run whose (n, N) fall in its ranges has each 64-particle tile
- * moved by `slices` waves (1, 2, 4 or 8) of the persistent move's 8-wave
+ * moved by `slices` waves (1, 2, 4 or 8) of that move's 8-wave
  * workgroups, which therefore take 8 / slices tiles of the run at once.
  * k, d = 0 and prec = -1 match anything; ranges are inclusive. */
 typedef struct {
@@ -427,8 +427,8 @@ int smc_batch_init(smc_ctx ctx, smc_batch b, const smc_gmm* model, const float* 
  *   reweight by chunks of each run; log-sum-exp, ESS, the resampling decision
  *   (ESS < ess_frac * N_r) and the CDF of each run by chunks; systematic
  *   resampling and gather of the resampling runs by chunks; then n_moves
- *   (>= 1) RW-MH moves as one persistent launch over the work list (workgroups
- *   pull units from a device counter). run_stats: device FP64 [R][4] = {log Z (accumulated), last ESS,
+ *   (>= 1) RW-MH moves, one launch each over the work list, a workgroup a
+ *   unit. run_stats: device FP64 [R][4] = {log Z (accumulated), last ESS,
  *   resample count, unused}. prec: FP32 or FP64. A run's results depend on its
  *   S only through the order of its FP64 slice sums and, in FP32, through which
  *   of the per-datum forms a wave takes and its data centre (see smc_loglik). */

@@ -9,7 +9,7 @@ candidate on the device, with HIP events on its own stream, and keeps the
 fastest; the result is a list of launch rules for ``Context.set_launch_table``
 (C ABI ``smc_set_launch_table``), which can be saved as JSON and reloaded.
 
-Batched runs (``tune_batched``): the persistent move gives every tile of a run
+Batched runs (``tune_batched``): the move gives every tile of a run
 S of its workgroup's 8 waves (so 8 / S tiles share a workgroup). For each
 power-of-two range of n among the runs, the tuner times graph-replayed batched
 steps of just those runs for S = 1, 2, 4, 8 and keeps the fastest, giving one

@@ -18,17 +18,15 @@
 //   k_b_gather    a resampling run's ancestor search and gather (others exit);
 // One workgroup per run took 144 us for the reweight and 1.34 ms for the
 // resampling of 64 runs of up to 65536 particles; 13, 14 and 42 us now.
-//   k_b_move      persistent: a grid sized to the GPU pulls work units from an
-//                 atomic counter. A unit is 8 / S consecutive 64-particle tiles
+//   k_b_move      a workgroup per work unit. A unit is 8 / S consecutive 64-particle tiles
 //                 of one run, each moved by S of the workgroup's 8 waves
 //                 (proposal + mixture likelihood over the run's n_r
 //                 observations, the S waves splitting the data + accept). S is
 //                 per run (launch table or built-in rule), so short-data runs
 //                 fill the workgroup with several tiles instead of leaving waves
-//                 idle. Units are listed longest data first (LPT), so runs whose
-//                 work differs by 10^3 balance.
-// and a one-thread kernel that advances the step counter and rewinds the work
-// counter for the next replay.
+//                 idle. Units are listed, and so started, longest data first
+//                 (LPT), so runs whose work differs by 10^3 balance.
+// and a one-thread kernel that advances the step counter.
 #include <algorithm>
 
 #include "cdf_scan.hpp"
@@ -227,10 +225,16 @@ k_b_loglik(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ unit
     }
 }
 
+// One move of a unit's tiles. Bound by the likelihood's arithmetic. FP32 up to
+// k = 4 fits 64 registers with its spills outside the loop over the data, four
+// workgroups to a CU; as a persistent loop over a work counter it took 127, since
+// the loop's invariants were held through the likelihood (64 runs of up to 65536
+// particles and 100000 data, k = 4: 5.02 ms so, 4.95 with a workgroup a unit at 91
+// registers, 4.65 at 80, 4.51 at 64).
 template <int K, int PREC>
-__global__ void __launch_bounds__(kBatchBlock, 4)
-k_b_move(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ units, int n_units,
-         unsigned* work, const float* __restrict__ y, double* theta, double* l,
+__global__ void __launch_bounds__(kBatchBlock, PREC == SMC_PREC_FP32 && K <= 4 ? 8 : 4)
+k_b_move(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ units,
+         const float* __restrict__ y, double* theta, double* l,
          const double* __restrict__ logw, double* __restrict__ W,
          const double* __restrict__ theta_tmp, const double* __restrict__ l_tmp,
          const StepState* __restrict__ st, StepSrc src, double sd, uint32_t move, int first,
@@ -239,96 +243,68 @@ k_b_move(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ units,
     __shared__ double red[kBatchWaves][kWave];
     __shared__ double prs[kBatchWaves][KD][kWave];
     __shared__ double lus[kBatchWaves][kWave];
-    __shared__ int unit_sh;
     const int lane = lane_id();
     const int w = wave_uniform(threadIdx.x / kWave);
-    for (;;) {
-        if (threadIdx.x == 0) unit_sh = static_cast<int>(atomicAdd(work, 1u));
-        __syncthreads();
-        const int u = unit_sh;
-        __syncthreads();
-        if (u >= n_units) break;
-        const BatchUnit un = units[u];
-        const BatchRun rd = runs[un.run];
-        const int S = wave_uniform(un.slices);
-        const int grp = w / S;                       // this wave's tile within the unit
-        const int sl = w - grp * S;                  // and its data slice
-        const bool active = grp < un.ntiles;
-        const int N = rd.N;
-        const int n = rd.n;
-        const int p = (un.tile0 + (active ? grp : 0)) * kWave + lane;
-        const int pc = p < N ? p : N - 1;
-        const StepState* sr = st + un.run;
-        const uint32_t step = static_cast<uint32_t>(sr->t);
-        const bool use_alt = first && sr->resampled;
-        double* th_run = theta + static_cast<size_t>(KD) * rd.p_off;
-        double* l_run = l + rd.p_off;
-        const double* th_src = use_alt ? theta_tmp + static_cast<size_t>(KD) * rd.p_off : th_run;
-        const double l_src = use_alt ? l_tmp[rd.p_off + pc] : l_run[pc];
-        // the tile's Box-Muller pairs and its log u shared out over its S waves (an
-        // idle wave of a short last unit draws none but meets the barrier)
-        double pr[KD];
-        block_proposals<KD>(rd.seed, static_cast<uint32_t>(pc), step, move, th_src, N, pc, sd,
-                            active ? sl : (KD + 1) / 2 + 1, S, prs[grp], pr, nullptr, nullptr,
-                            nullptr, lus[grp]);
-        double part = 0.0;
-        if (active) {
-            int j0, j1;
-            slice_bounds(n, sl, S, j0, j1);
-            part = slice_partial<K, 1, PREC>(y + rd.y_off, j0, j1, pr, g, near_data(l_src, n, g),
-                                             PivotStage{pivot_row<PREC, 1, kBatchWaves>()});
-        }
-        red[w][lane] = part;
-        __syncthreads();
-        if (active && sl == 0) {
-            bool acc = false;
-            if (p < N) {
-                const double l_prop = finish_loglik<PREC>(sum_slices(red + w, S), n, g);
-                MoveStep ms{};
-                if (first) {
-                    ms.theta_alt = theta_tmp + static_cast<size_t>(KD) * rd.p_off;
-                    ms.l_alt = l_tmp + rd.p_off;
-                    ms.state = sr;
-                    ms.W_out = W + rd.p_off;
-                    ms.logw = const_cast<double*>(logw) + rd.p_off;
-                }
-                const MoveSource srcs = move_source(ms, th_run, l_run);
-                acc = rwmh_accept<KD>(p, p, N, [&](int c) { return pr[c]; }, l_prop, srcs, th_run,
-                                      l_run, nullptr, src, step, rd.seed, move, g, status, ms,
-                                      nullptr, &lus[grp][lane]);
+    const BatchUnit un = units[blockIdx.x];
+    const BatchRun rd = runs[un.run];
+    const int S = wave_uniform(un.slices);
+    const int grp = w / S;                       // this wave's tile within the unit
+    const int sl = w - grp * S;                  // and its data slice
+    const bool active = grp < un.ntiles;
+    const int N = rd.N;
+    const int n = rd.n;
+    const int p = (un.tile0 + (active ? grp : 0)) * kWave + lane;
+    const int pc = p < N ? p : N - 1;
+    const StepState* sr = st + un.run;
+    const uint32_t step = static_cast<uint32_t>(sr->t);
+    const bool use_alt = first && sr->resampled;
+    double* th_run = theta + static_cast<size_t>(KD) * rd.p_off;
+    double* l_run = l + rd.p_off;
+    const double* th_src = use_alt ? theta_tmp + static_cast<size_t>(KD) * rd.p_off : th_run;
+    const double l_src = use_alt ? l_tmp[rd.p_off + pc] : l_run[pc];
+    // the tile's Box-Muller pairs and its log u shared out over its S waves (an
+    // idle wave of a short last unit draws none but meets the barrier)
+    double pr[KD];
+    block_proposals<KD>(rd.seed, static_cast<uint32_t>(pc), step, move, th_src, N, pc, sd,
+                        active ? sl : (KD + 1) / 2 + 1, S, prs[grp], pr, nullptr, nullptr,
+                        nullptr, lus[grp]);
+    double part = 0.0;
+    if (active) {
+        int j0, j1;
+        slice_bounds(n, sl, S, j0, j1);
+        part = slice_partial<K, 1, PREC>(y + rd.y_off, j0, j1, pr, g, near_data(l_src, n, g),
+                                         PivotStage{pivot_row<PREC, 1, kBatchWaves>()});
+    }
+    red[w][lane] = part;
+    __syncthreads();
+    if (active && sl == 0) {
+        bool acc = false;
+        if (p < N) {
+            const double l_prop = finish_loglik<PREC>(sum_slices(red + w, S), n, g);
+            MoveStep ms{};
+            if (first) {
+                ms.theta_alt = theta_tmp + static_cast<size_t>(KD) * rd.p_off;
+                ms.l_alt = l_tmp + rd.p_off;
+                ms.state = sr;
+                ms.W_out = W + rd.p_off;
+                ms.logw = const_cast<double*>(logw) + rd.p_off;
             }
-            const unsigned long long mask = __ballot(acc);
-            if (lane == 0 && n_acc != nullptr && mask != 0ull)
-                atomicAdd(n_acc, static_cast<unsigned long long>(__popcll(mask)));
+            const MoveSource srcs = move_source(ms, th_run, l_run);
+            acc = rwmh_accept<KD>(p, p, N, [&](int c) { return pr[c]; }, l_prop, srcs, th_run,
+                                  l_run, nullptr, src, step, rd.seed, move, g, status, ms,
+                                  nullptr, &lus[grp][lane]);
         }
-        __syncthreads();
+        const unsigned long long mask = __ballot(acc);
+        if (lane == 0 && n_acc != nullptr && mask != 0ull)
+            atomicAdd(n_acc, static_cast<unsigned long long>(__popcll(mask)));
     }
 }
 
-__global__ void k_b_end(int* t_dev, unsigned* work) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        *t_dev += 1;
-        *work = 0u;
-    }
-}
-
-__global__ void k_b_rewind(unsigned* work) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *work = 0u;
+__global__ void k_b_end(int* t_dev) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) *t_dev += 1;
 }
 
 }  // namespace
-
-int batch_move_grid() {
-    int dev = 0, cus = 256, per_cu = 1;
-    if (hipGetDevice(&dev) == hipSuccess)
-        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void*>(&k_b_move<4, SMC_PREC_FP32>), kBatchBlock, 0) !=
-            hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
-    return cus * per_cu;
-}
 
 hipError_t launch_batch_init(const BatchDev& b, const GmmDev& g, const float* y, double* theta,
                              double* l, int prec, int* status, hipStream_t s) {
@@ -378,34 +354,27 @@ hipError_t launch_batch_step(const BatchDev& b, const GmmDev& g, const float* y,
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int pi = prec == SMC_PREC_FP32 ? 1 : 0;
-    const BatchUnit* units = b.units[pi];
-    const int n_units = b.n_units[pi];
-    const int grid = n_units < b.move_grid ? n_units : b.move_grid;
     for (int m = 0; m < n_moves; ++m) {
-        if (m > 0) {
-            hipLaunchKernelGGL(k_b_rewind, dim3(1), dim3(64), 0, s, b.work);
+        for (int u = 0; u < b.n_units[pi]; u += kMaxUnitGrid) {
+            const dim3 grid(static_cast<unsigned>(std::min(kMaxUnitGrid, b.n_units[pi] - u)));
+            const BatchUnit* units = b.units[pi] + u;
+#define SMC_BM(KK, P)                                                                           \
+            hipLaunchKernelGGL((k_b_move<KK, P>), grid, dim3(kBatchBlock), 0, s, b.runs, units, \
+                               y, theta, l, logw, W, b.theta_tmp, b.l_tmp, b.state, src, sd,    \
+                               static_cast<uint32_t>(m), m == 0 ? 1 : 0, g, n_acc, status)
+#define SMC_BK(KK)                                                                              \
+            if (g.k == KK) {                                                                    \
+                if (prec == SMC_PREC_FP32) SMC_BM(KK, SMC_PREC_FP32);                           \
+                else SMC_BM(KK, SMC_PREC_FP64);                                                 \
+            }
+            SMC_BK(1) SMC_BK(2) SMC_BK(3) SMC_BK(4) SMC_BK(5) SMC_BK(6) SMC_BK(7) SMC_BK(8)
+#undef SMC_BK
+#undef SMC_BM
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-#define SMC_BK(KK)                                                                              \
-        if (g.k == KK) {                                                                        \
-            if (prec == SMC_PREC_FP32)                                                          \
-                hipLaunchKernelGGL((k_b_move<KK, SMC_PREC_FP32>), dim3(grid), dim3(kBatchBlock), 0, s, \
-                                   b.runs, units, n_units, b.work, y, theta, l, logw, W,    \
-                                   b.theta_tmp, b.l_tmp, b.state, src, sd, static_cast<uint32_t>(m), \
-                                   m == 0 ? 1 : 0, g, n_acc, status);                           \
-            else                                                                                \
-                hipLaunchKernelGGL((k_b_move<KK, SMC_PREC_FP64>), dim3(grid), dim3(kBatchBlock), 0, s, \
-                                   b.runs, units, n_units, b.work, y, theta, l, logw, W,    \
-                                   b.theta_tmp, b.l_tmp, b.state, src, sd, static_cast<uint32_t>(m), \
-                                   m == 0 ? 1 : 0, g, n_acc, status);                           \
-        }
-        SMC_BK(1) SMC_BK(2) SMC_BK(3) SMC_BK(4) SMC_BK(5) SMC_BK(6) SMC_BK(7) SMC_BK(8)
-#undef SMC_BK
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_b_end, dim3(1), dim3(64), 0, s, t_dev, b.work);
+    hipLaunchKernelGGL(k_b_end, dim3(1), dim3(64), 0, s, t_dev);
     return hipGetLastError();
 }
 

@@ -1317,7 +1317,6 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
     const size_t b_runs = align_up(sizeof(BatchRun) * R);
     const size_t b_u0 = align_up(sizeof(BatchUnit) * units[0].size());
     const size_t b_items = b_u0 + align_up(sizeof(BatchUnit) * units[1].size());
-    const size_t b_work = align_up(sizeof(unsigned));
     const size_t b_state = align_up(sizeof(StepState) * R);
     const size_t b_cdf = align_up(sizeof(double) * N_total);
     const size_t b_th = align_up(sizeof(double) * N_total * kd);
@@ -1327,7 +1326,7 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
     const size_t b_tot = align_up(sizeof(double) * 2 * chunks.size());
     const size_t b_i0 = align_up(sizeof(BatchUnit) * iunits[0].size());
     const size_t b_i1 = align_up(sizeof(BatchUnit) * iunits[1].size());
-    const size_t total = b_runs + b_items + b_work + b_state + 2 * b_cdf + b_th + b_l + b_ch +
+    const size_t total = b_runs + b_items + b_state + 2 * b_cdf + b_th + b_l + b_ch +
                          b_part + b_tot + b_i0 + b_i1;
     void* p = nullptr;
     if (hipMalloc(&p, total) != hipSuccess) return fail(SMC_ERR_NOMEM, "batch allocation failed");
@@ -1349,9 +1348,8 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
     d.units[1] = reinterpret_cast<BatchUnit*>(c + b_runs + b_u0);
     d.n_units[0] = static_cast<int>(units[0].size());
     d.n_units[1] = static_cast<int>(units[1].size());
-    d.work = reinterpret_cast<unsigned*>(c + b_runs + b_items);
-    d.state = reinterpret_cast<StepState*>(c + b_runs + b_items + b_work);
-    c += b_runs + b_items + b_work + b_state;
+    d.state = reinterpret_cast<StepState*>(c + b_runs + b_items);
+    c += b_runs + b_items + b_state;
     d.cdf_hi = reinterpret_cast<double*>(c);
     d.cdf_lo = reinterpret_cast<double*>(c + b_cdf);
     d.theta_tmp = reinterpret_cast<double*>(c + 2 * b_cdf);
@@ -1364,7 +1362,6 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
     c += b_ch + b_part + b_tot;
     d.init_units[0] = reinterpret_cast<BatchUnit*>(c);
     d.init_units[1] = reinterpret_cast<BatchUnit*>(c + b_i0);
-    d.move_grid = batch_move_grid();
     hipError_t e = hipMemset(p, 0, total);
     if (e == hipSuccess) e = hipMemcpy(d.runs, rd.data(), sizeof(BatchRun) * R, hipMemcpyHostToDevice);
     if (e == hipSuccess)

@@ -167,8 +167,8 @@ struct BatchRun {
 struct BatchChunk {
     int run, index;
 };
-constexpr int kBatchWaves = 8;          // waves per workgroup of the persistent batched move
-// Work unit of the persistent batched move: ntiles consecutive 64-particle
+constexpr int kBatchWaves = 8;          // waves per workgroup of the batched move
+// Work unit of the batched move: ntiles consecutive 64-particle
 // tiles of run `run` from tile0 on, each moved by `slices` waves (slices *
 // ntiles <= kBatchWaves).
 struct BatchUnit {
@@ -181,7 +181,6 @@ struct BatchDev {
     int n_units[2];
     BatchUnit* init_units[2];  // tiles of the first log-likelihood, longest slices first
     int n_init_units[2];
-    unsigned* work;            // work-queue counter, zero between launches
     StepState* state;          // [R]
     BatchChunk* chunks;        // [n_chunks] every run's chunks, run by run
     int n_chunks;
@@ -191,9 +190,7 @@ struct BatchDev {
     double* cdf_lo;            // [N_total]
     double* theta_tmp;         // [kd * N_total]
     double* l_tmp;             // [N_total]
-    int move_grid;             // persistent grid size
 };
-int batch_move_grid();
 // Every run's prior draw and log-likelihood, two launches. The units' slices and
 // tiles fill workgroups of kMaxSlices waves.
 hipError_t launch_batch_init(const BatchDev& b, const GmmDev& g, const float* y, double* theta,
