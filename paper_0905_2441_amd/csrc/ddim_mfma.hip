@@ -591,13 +591,13 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
     if (kg == 0 && p < N) part[static_cast<size_t>(slice) * N + p] = v;
 }
 
-__global__ void __launch_bounds__(256)
+// Adds the slices' partial sums: bound by latency, so they are requested at once and
+// a workgroup is one wave (k = 2, n = 1607, N = 4683: the whole call 22.1 -> 21.7 us).
+__global__ void __launch_bounds__(kWave)
 k_dd_finish(const double* part, int S, int N, int n, GmmDev g, double* out, int* status) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= N) return;
-    double acc = part[p];
-    for (int s = 1; s < S; ++s) acc += part[static_cast<size_t>(s) * N + p];
-    const double l = finish_loglik<SMC_PREC_FP32>(acc, n, g);
+    const double l = finish_loglik<SMC_PREC_FP32>(GroupSums(part, N, p, S).total(S), n, g);
     out[p] = l;
     if (l != l) atomicOr(status, kStatusNaN);
 }
@@ -687,7 +687,8 @@ hipError_t launch_dd_loglik(const GmmDev& g, const __bf16* A, int64_t n, const d
 #undef SMC_DD
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dd_finish, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_dd_finish, dim3(static_cast<unsigned>((N + kWave - 1) / kWave)),
+                       dim3(kWave), 0, s,
                        part, S, static_cast<int>(N), static_cast<int>(n), g, out, status);
     return hipGetLastError();
 }
@@ -742,7 +743,8 @@ hipError_t launch_dd64_loglik(const GmmDev& g, const float* y, int64_t n, const 
                               hipStream_t s) {
     const hipError_t e = launch_dd64_partial(g, y, n, theta, N, part, S, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dd_finish, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_dd_finish, dim3(static_cast<unsigned>((N + kWave - 1) / kWave)),
+                       dim3(kWave), 0, s,
                        static_cast<const double*>(part), S, static_cast<int>(N),
                        static_cast<int>(n), g, out, status);
     return hipGetLastError();

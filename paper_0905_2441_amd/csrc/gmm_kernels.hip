@@ -665,25 +665,6 @@ k_pt_deferred_exchange(const double* __restrict__ th_in, const double* __restric
     l_out[c] = l_in[src];
 }
 
-// The G groups' partial sums of particle p, added in group order. All are
-// requested at once (beyond G the last one again), before the caller draws its
-// random numbers: one after another they took 0.6 us more a launch at G = 8.
-struct GroupSums {
-    double v[kMoveGroups];
-    __device__ __forceinline__ GroupSums(const double* __restrict__ part, int N, int p, int G) {
-#pragma unroll
-        for (int q = 0; q < kMoveGroups; ++q)
-            v[q] = part[static_cast<size_t>(q < G ? q : G - 1) * N + p];
-    }
-    __device__ __forceinline__ double total(int G) const {
-        double tot = v[0];
-#pragma unroll
-        for (int q = 1; q < kMoveGroups; ++q)
-            if (q < G) tot += v[q];
-        return tot;
-    }
-};
-
 // Second half of a move whose tile data were split over G workgroups, for
 // particle p: add the G partial sums in group order, re-form the same proposal
 // (same counter, same arithmetic) and take the MH decision.
