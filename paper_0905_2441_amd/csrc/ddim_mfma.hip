@@ -139,10 +139,8 @@ __global__ void __launch_bounds__(256)
 k_dd_build(const double* __restrict__ theta, int N, int K, GmmDev g, double s2, MoveStep ms,
            double sd, uint64_t seed, StepSrc src, uint32_t move, __bf16* __restrict__ B,
            double* __restrict__ theta_prop) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N * K) return;
-    const int p = q / K;
-    const int i = q - p * K;
+    int p, i;
+    if (!dd_column(blockIdx.x * blockDim.x + threadIdx.x, N, K, p, i)) return;
     const double* th = theta;
     if constexpr (PROP) {
         const bool rs = ms.state != nullptr && ms.state->resampled != 0;
@@ -187,7 +185,7 @@ k_dd_build(const double* __restrict__ theta, int N, int K, GmmDev g, double s2, 
     s6[0] = one; s6[1] = one; s6[2] = one;
     s6[3] = ch; s6[4] = cm; s6[5] = cl;
     s6[6] = zero; s6[7] = zero;
-    bf16x8* dst = reinterpret_cast<bf16x8*>(B + static_cast<size_t>(q) * kRowElems);
+    bf16x8* dst = reinterpret_cast<bf16x8*>(B + (static_cast<size_t>(p) * K + i) * kRowElems);
     dst[0] = sh;   // slot 0: mu_hi
     dst[1] = sm;   // slot 1: mu_mid
     dst[2] = sh;   // slot 2: mu_hi
@@ -647,7 +645,9 @@ int dd_slices(int64_t n, int64_t N) {
     return dd_clamp_slices(n, (2048 + groups - 1) / groups);
 }
 
-bool dd64_takes(const GmmDev& g, int prec) { return prec == SMC_PREC_FP64 && dd_supported(g.k, g.d); }
+bool dd64_takes(const GmmDev& g, int prec, int64_t N) {
+    return prec == SMC_PREC_FP64 && dd_supported(g.k, g.d) && dd64_fits(g.k, N);
+}
 
 int dd64_slices(int64_t n, int64_t N, int64_t want, int64_t part_cap) {
     const int64_t tiles = dd_padded_rows(n) / kTileRows;

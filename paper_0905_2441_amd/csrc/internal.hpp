@@ -282,7 +282,22 @@ hipError_t launch_dd_rwmh(const GmmDev& g, const __bf16* A, int64_t n, double* t
 // particles (one slice may share the output array). The move writes its
 // proposals to theta_prop, which may be the output population of an out-of-place
 // move (theta itself).
-bool dd64_takes(const GmmDev& g, int prec);
+bool dd64_takes(const GmmDev& g, int prec, int64_t N);
+// Particle p and component i of thread q of a launch over N * K of them; false beyond
+// the last. Unsigned: N * K stays below 2^32 (dd64_fits; in BF16x3 by the columns'
+// memory, 1 KB a particle), not below 2^31.
+__host__ __device__ constexpr bool dd_column(unsigned q, int N, int K, int& p, int& i) {
+    if (q >= static_cast<unsigned>(N) * static_cast<unsigned>(K)) return false;
+    p = static_cast<int>(q / static_cast<unsigned>(K));
+    i = static_cast<int>(q % static_cast<unsigned>(K));
+    return true;
+}
+// The sizes of that form: a launch has fewer than 2^32 threads, and the proposals
+// take one per particle and component, the partial sums 256 per 64 particles.
+// Larger populations take the VALU form, 64 threads per 64 particles at one slice.
+constexpr bool dd64_fits(int k, int64_t N) {
+    return (N * k + 255) / 256 * 256 < (int64_t{1} << 32) && (N + 63) / 64 * 256 < (int64_t{1} << 32);
+}
 int dd64_slices(int64_t n, int64_t N, int64_t want, int64_t part_cap);
 hipError_t launch_dd64_loglik(const GmmDev& g, const float* y, int64_t n, const double* theta,
                               int64_t N, double* part, int S, double* out, int* status,

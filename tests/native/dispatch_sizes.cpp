@@ -1,0 +1,22 @@
+// Reads lines "fits k N" (whether the FP64 matrix form takes that population) and
+// "column q N k" (the particle and component of thread q of its proposals).
+#include <cstdio>
+#include <cstring>
+
+#include "internal.hpp"
+
+int main() {
+    char what[16];
+    while (std::scanf("%15s", what) == 1) {
+        long long a, b;
+        unsigned q;
+        int k, p = -1, i = -1;
+        if (std::strcmp(what, "fits") == 0 && std::scanf("%d %lld", &k, &a) == 2) {
+            std::printf("%d\n", smc::dd64_fits(k, a) ? 1 : 0);
+        } else if (std::scanf("%u %lld %d", &q, &b, &k) == 3) {
+            const bool in = smc::dd_column(q, static_cast<int>(b), k, p, i);
+            std::printf("%d %d %d\n", in ? 1 : 0, p, i);
+        }
+    }
+    return 0;
+}

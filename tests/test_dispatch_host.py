@@ -1,0 +1,50 @@
+"""Size rules of the dispatch that no GPU test can reach (populations of many GB),
+compiled for the host from the library's own header."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SRC = os.path.join(ROOT, "tests", "native", "dispatch_sizes.cpp")
+CSRC = os.path.join(ROOT, "paper_0905_2441_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def answers(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("native") / "dispatch_sizes")
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-I", CSRC,
+                    "-I", os.path.join(ROOT, "include"), "-o", exe, SRC],
+                   check=True, capture_output=True)
+
+    def ask(lines):
+        out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True,
+                             check=True).stdout
+        return [tuple(int(v) for v in line.split()) for line in out.strip().splitlines()]
+    return ask
+
+
+def test_fp64_matrix_form_leaves_sizes_beyond_its_launches_to_the_valu_form(answers):
+    """A grid has fewer than 2^32 threads: one per particle and component in the
+    proposals, four per particle (of whole tiles of 64) in the partial sums."""
+    cases = [(8, 1, 1), (8, 16384, 1), (8, 2 ** 28, 1), (8, 2 ** 29 - 32, 1), (8, 2 ** 29 - 31, 0),
+             (8, 2 ** 29, 0), (4, 2 ** 30 - 64, 1), (4, 2 ** 30, 0), (2, 2 ** 30 - 64, 1),
+             (2, 2 ** 30 - 63, 0), (1, 2 ** 30 - 64, 1), (1, 2 ** 30 - 63, 0), (1, 2 ** 31 - 1, 0)]
+    got = answers([f"fits {k} {N}" for k, N, _ in cases])
+    assert got == [(w,) for _, _, w in cases]
+
+
+def test_proposal_threads_are_numbered_beyond_2_31(answers):
+    """N * k = 2^31 and more (k = 8, N = 2^28): every thread has its particle and
+    component, and the first one past the end has none."""
+    cases = [(0, 2 ** 28, 8, (1, 0, 0)), (2 ** 31 - 1, 2 ** 28, 8, (1, 2 ** 28 - 1, 7)),
+             (2 ** 31, 2 ** 28, 8, (0, -1, -1)), (2 ** 31, 2 ** 28 + 1, 8, (1, 2 ** 28, 0)),
+             (2 ** 32 - 257, 2 ** 29 - 32, 8, (1, 2 ** 29 - 33, 7)),
+             (2 ** 32 - 256, 2 ** 29 - 32, 8, (0, -1, -1)), (14, 5, 3, (1, 4, 2)), (15, 5, 3, (0, -1, -1))]
+    got = answers([f"column {q} {N} {k}" for q, N, k, _ in cases])
+    assert got == [w for *_, w in cases]
