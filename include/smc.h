@@ -168,8 +168,10 @@ int smc_set_launch_table(smc_ctx ctx, const smc_launch_rule* rules, int32_t coun
  *   loglik[p] = sum_j log sum_i w_i N_d(y_j; mu_{p,i}, sigma2 I).
  * y: [n][d] FP32; theta: [k*d][N] FP64; loglik: [N] FP64 out.
  * prec FP64: for d = 1 the pivot form described below in FP64 (windows of 64
- * data, exponent differences up to 250, terms below 2^-58 of a factor left out,
- * one log per slice), windows it refuses in a max-shifted product form; for
+ * data, exponent differences up to 12, terms below 2^-58 of a factor left out,
+ * one log per slice); windows it refuses are halved or go in a max-shifted
+ * product form (which of them a wave takes may depend on the other particles of
+ * its 64, and changes a result by rounding only); for
  * d = 8 the quadratic forms as one FP64 matrix contraction about a centre of
  * the data (the population-MCMC calls and a move that cannot have its scratch
  * take an exp per term and a log per datum); relative error below 1e-12;

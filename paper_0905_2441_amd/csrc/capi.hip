@@ -155,7 +155,7 @@ int batch_slices(const smc_ctx_s* ctx, int k, int prec, int64_t n, int64_t N) {
 
 // Data slices per 64-particle tile: the explicit override, else the launch
 // table, else the built-in choice: enough waves to fill 256 CUs several times
-// over (about 8192), at least 32 observations per slice (24 in FP64), and a grid
+// over (about 8192), at least 32 observations per slice (fewer in FP64), and a grid
 // within 2^32 threads. More than kMaxSlices slices (small N, long data) are
 // spread over several workgroups per tile; only moves with N <= kSplitCap do
 // that, everything else stays within one workgroup.
@@ -178,13 +178,12 @@ Split choose_split(const smc_ctx_s* ctx, const GmmDev& g, int prec, int64_t n, i
     if (T <= 0) {
         T = (8192 + tiles - 1) / tiles;
         if (T > kMaxSlices * kMaxGroups) T = kMaxSlices * kMaxGroups;
-        // the FP64 pivot form has less fixed work per datum left to share: 24 data
-        // per slice, in whole multiples of the CU's four SIMDs from 4 on (the
-        // small sampler run, n = 100, N = 1024: 837 us at 4 slices, 893 at 3;
-        // n = 50, N = 262144: 840 us per ten steps at 2, 985 at 1)
+        // FP64 1-D: 12 data per slice up to 8 slices and 24 beyond, in whole multiples
+        // of the CU's four SIMDs from 4 on (the small sampler run, n = 100, N = 1024:
+        // 852 us at 8 slices, 920 at 4, 1006 at 3; n = 60, N = 30000: 433 us per 20
+        // steps at 4, 545 at 2; n = 300, N = 30000: 804 at 12, 1085 at 24)
         const bool f64 = prec == SMC_PREC_FP64 && g.d == 1;
-        const int64_t least = f64 ? 24 : 32;
-        while (T > 1 && n / T < least) --T;
+        while (T > 1 && n / T < (!f64 ? 32 : T > 8 ? 24 : 12)) --T;
         if (f64 && T > 4) T &= ~int64_t{3};
     }
     if (T > n) T = n;

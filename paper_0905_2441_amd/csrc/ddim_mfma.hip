@@ -68,7 +68,6 @@ constexpr int kStageRows = kStageTiles * kTileRows;
 constexpr int kStageBytes = kStageRows * kRowBytes;   // 16 KB
 constexpr int kDdBlock = 256;                          // 4 waves, 64 particles
 constexpr int kDdDim = 8;                              // coordinates per slot
-constexpr double kLog2e = 1.4426950408889634;
 
 __device__ __forceinline__ void split3(float x, __bf16& h, __bf16& m, __bf16& l) {
     h = static_cast<__bf16>(x);

@@ -1,0 +1,86 @@
+"""The FP64 likelihood's error against extended precision: no larger than that of a
+term-by-term FP64 evaluation (an exp per term, a log per datum, a running sum), over
+data orders, spreads and sizes. The device's forms regroup the terms (a pivot
+component per window, a matrix contraction about a centre), which must not cost
+precision where sigma2 is small, n is small or the data are unsorted."""
+
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import announce
+from workloads import make_mixture_data, theta_near_posterior, theta_prior_draws
+
+pytestmark = pytest.mark.gpu
+
+# The rms over particles of the relative error may exceed that of the term-by-term
+# evaluation by half (regrouped sums round differently, and the evaluation here
+# uses numpy's exp and log) and by the 2^-54 of rounding a result once more.
+FACTOR, EXTRA = 1.5, 2.0 ** -54
+
+
+def _term_by_term(theta, y, k, d, sigma2, slices, dtype):
+    """Log-likelihoods [N], terms and one running sum per data slice in `dtype`."""
+    th = theta.reshape(k, d, -1).astype(dtype)
+    yy = y.reshape(-1, d).astype(dtype)
+    inv2s2 = dtype(1.0 / (2.0 * sigma2))
+    lw = dtype(math.log(1.0 / k))
+    total = np.zeros(th.shape[2], dtype=dtype)
+    for rows in np.array_split(yy, slices):
+        acc = np.zeros(th.shape[2], dtype=dtype)
+        for row in rows:
+            a = np.stack([lw - sum((row[c] - th[i, c]) ** 2 for c in range(d)) * inv2s2
+                          for i in range(k)])
+            m = a.max(axis=0)
+            acc = acc + (m + np.log(np.exp(a - m).sum(axis=0)))
+        total = total + acc
+    return total + dtype(len(yy)) * dtype(-0.5 * d * math.log(2.0 * math.pi * sigma2))
+
+
+def _check(smc, y, theta, k, d, sigma2, slices):
+    ctx = smc.Context(0)
+    ctx.set_slices(slices)
+    g = smc.Gmm.equal_weights(k, d, sigma2)
+    got = smc.smc_loglik(ctx, g, torch.as_tensor(y).cuda(), torch.as_tensor(theta).cuda(), "fp64")
+    ctx.check()
+    ref = _term_by_term(theta, y, k, d, sigma2, 1, np.longdouble)
+    plain = _term_by_term(theta, y, k, d, sigma2, slices, np.float64)
+    assert np.finfo(np.longdouble).nmant >= 63
+
+    def rms(v):
+        return float(np.sqrt(np.mean((((v - ref) / ref).astype(np.float64)) ** 2)))
+    got_rms, plain_rms = rms(got.cpu().numpy().astype(np.longdouble)), rms(plain)
+    print(f"rms relative error {got_rms:.2e}, term by term {plain_rms:.2e}", flush=True)
+    assert got_rms <= FACTOR * plain_rms + EXTRA, (got_rms, plain_rms)
+
+
+@pytest.fixture(scope="module")
+def smc():
+    import paper_0905_2441_amd as smc
+    return smc
+
+
+@pytest.mark.parametrize("k,n,sigma2,order,start,slices", [
+    (4, 1000, 0.55, "sorted", "near", 4),
+    (4, 1000, 0.55, "unsorted", "near", 4),
+    (4, 1000, 0.55, "unsorted", "prior", 4),
+    (4, 50, 0.55, "sorted", "near", 2),
+    (4, 100, 0.03, "sorted", "near", 4),
+    (4, 1000, 0.03, "sorted", "near", 4),
+    (8, 200, 0.55, "unsorted", "near", 8),
+    (4, 600, 0.55, "shuffled_quarters", "near", 2),
+])
+def test_error_of_the_1d_forms(smc, k, n, sigma2, order, start, slices):
+    announce(f"fp64 error 1-D k={k} n={n} sigma2={sigma2} {order} {start}")
+    mu = -3.0 + 3.0 * np.arange(k, dtype=np.float64)
+    y = make_mixture_data(n, mu, sigma2, seed=71)
+    if order == "sorted":
+        y = np.sort(y)
+    elif order == "shuffled_quarters":
+        # windows that are refused whole and held in parts
+        y = np.concatenate([np.sort(q) for q in np.array_split(y, 40)])
+    th = (theta_near_posterior(512, mu, seed=72) if start == "near"
+          else theta_prior_draws(512, k, 1, seed=73))
+    _check(smc, y, th, k, 1, sigma2, slices)
