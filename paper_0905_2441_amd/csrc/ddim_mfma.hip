@@ -365,10 +365,17 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
 // 64 data spread over the array, the same in every workgroup) keeps Y_j small
 // for data far from the origin, and tiles holding a datum with Y_j above
 // kDd64MaxY, a datum that is not finite, or a particle with a mean that is not
-// finite take the difference form (no expansion, plain FP64). Waves with a
-// particle so far away that a datum's sum falls below 2^-1000 take each datum's
-// largest exponent out first.
-constexpr int kDd64Rows = 128;                         // data rows per LDS stage
+// finite take the difference form (no expansion, plain FP64): 8 subtractions and
+// 8 multiply-adds per component instead of the matrix unit's. A wave sets such
+// tiles aside and works them off after every block of 64, when the expansion's
+// operands are dead and their registers free, with the means from LDS: k = 8,
+// N = 16384, n = 8192 1.33 ms (the expansion 0.78), where two passes of rolled
+// loops over means and data in memory took 13.0 ms and the VALU form 4.1. Waves
+// with a particle so far away that a datum's sum falls below 2^-1000 take each
+// datum's largest exponent out first.
+constexpr int kDd64StageTiles = 8;                     // data rows per LDS stage
+constexpr int kDd64Rows = kDd64StageTiles * kTileRows;
+constexpr int kDd64Block = 8;                          // stages per block: 64 tiles, a bit each
 constexpr double kDd64MaxY = 4096.0;
 constexpr double kDd64MinC = -1.0e8;
 
@@ -381,12 +388,17 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
     __shared__ double su[2][kDd64Rows * kDdDim];
     __shared__ __align__(16) double sy[2][kDd64Rows];
     __shared__ double cen[kDdDim];
+    __shared__ double mean[K * kDdDim][64];          // the workgroup's particles' means
     const int lane = lane_id();
     const int w = wave_id();
     const int kg = lane >> 4;             // K element of the operands, row group of the results
     const int col = lane & 15;
     const int p = blockIdx.x * 64 + w * 16 + col;
-    const int pc = p < N ? p : N - 1;
+    const int mp = w * 16 + col;          // this lane's column of `mean`
+    for (int q = threadIdx.x; q < K * kDdDim * 64; q += kDdBlock) {
+        const int pq = blockIdx.x * 64 + (q & 63);
+        mean[q >> 6][q & 63] = th[static_cast<size_t>(q >> 6) * N + (pq < N ? pq : N - 1)];
+    }
     const int slice = blockIdx.y;
     const int ntiles = (n + kTileRows - 1) / kTileRows;
     const int t0 = static_cast<int>((static_cast<int64_t>(ntiles) * slice) / S);
@@ -403,24 +415,6 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
         }
     }
     __syncthreads();
-    // this lane's coordinates of its particle's means about the centre
-    double b1[K], b2[K], C[K];
-    bool fine = true;
-    {
-        const double c1 = cen[kg], c2 = cen[4 + kg];
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-            b1[i] = th[static_cast<size_t>(i * kDdDim + kg) * N + pc] - c1;
-            b2[i] = th[static_cast<size_t>(i * kDdDim + 4 + kg) * N + pc] - c2;
-            double q = fma(b2[i], b2[i], b1[i] * b1[i]);
-            q += __shfl_xor(q, 16, kWave);
-            q += __shfl_xor(q, 32, kWave);
-            C[i] = -s2 * q;
-            fine &= C[i] >= kDd64MinC;
-            C[i] += g.lw[i] * kLog2e;              // -inf: the component is skipped
-        }
-    }
-    fine = __all(fine);
 
     // stages: thread t brings half a data row, (t / 2, 4 coordinates)
     const int half = threadIdx.x & 1;
@@ -446,73 +440,98 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
         ys += __shfl_xor(ys, 1, kWave);
         if (half == 0) sy[buf][srow] = s2 * ys;
     };
-    const int nst = (t1 - t0 + kDd64Rows / kTileRows - 1) / (kDd64Rows / kTileRows);
+    const int nst = (t1 - t0 + kDd64StageTiles - 1) / kDd64StageTiles;
     if (nst > 0) {
         load_stage(0);
         store_stage(0);
     }
     __syncthreads();
 
-    double prod = 1.0, msum = 0.0;
+    double prod = 1.0, msum = 0.0, nsum = 0.0;       // nsum: in natural units
     int expo = 0;
-    bool direct = fine && g.unit_mass != 0;
+    bool direct = g.unit_mass != 0;
+    bool nan = false;                                // a mean of this lane's particle is NaN
     const int arow = 4 * (col & 3) + (col >> 2);
-    for (int st = 0; st < nst; ++st) {
-        const int buf = st & 1;
-        const bool more = st + 1 < nst;
-        if (more) load_stage(st + 1);
-        const int tile0 = t0 + st * (kDd64Rows / kTileRows);
-        const int tiles = min(kDd64Rows / kTileRows, t1 - tile0);
-        for (int tt = 0; tt < tiles; ++tt) {
-            const double* ur = &su[buf][(tt * kTileRows + arow) * kDdDim];
-            const double a1 = ur[kg], a2 = ur[4 + kg];
-            double Y[4];
+    for (int s0 = 0; s0 < nst; s0 += kDd64Block) {
+        const int s1 = min(nst, s0 + kDd64Block);
+        // this lane's coordinates of its particle's means about the centre: formed for
+        // every block of stages, so that they hold no registers in its difference form
+        // (the empty asm keeps them from being read once for all blocks)
+        double b1[K], b2[K], C[K];
+        bool fine = true;
+        {
+            int mq = mp;
+            asm volatile("" : "+v"(mq));
+            const double c1 = cen[kg], c2 = cen[4 + kg];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) Y[r] = sy[buf][tt * kTileRows + 4 * kg + r];
-            const int grow = (tile0 + tt) * kTileRows + 4 * kg;
-            const bool whole = (tile0 + tt + 1) * kTileRows <= n;
-            auto tile_exponents = [&](int i) {
-                f64x4 acc = {C[i] - Y[0], C[i] - Y[1], C[i] - Y[2], C[i] - Y[3]};
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1[i], acc, 0, 0, 0);
-                return __builtin_amdgcn_mfma_f64_16x16x4f64(a2, b2[i], acc, 0, 0, 0);
-            };
-            double e[4] = {0.0, 0.0, 0.0, 0.0};
-            const bool near =
-                __all(fmax(fmax(Y[0], Y[1]), fmax(Y[2], Y[3])) <= kDd64MaxY && Y[0] == Y[0] &&
-                      Y[1] == Y[1] && Y[2] == Y[2] && Y[3] == Y[3]);
-            bool done = false;
-            if (direct && near) {
-                // the next component's products are started before this one's
-                // exponentials; the fences keep the compiler from starting all K
-                f64x4 acc = tile_exponents(0);
-#pragma unroll
-                for (int i = 0; i < K; ++i) {
-                    f64x4 next = acc;
-                    if (i + 1 < K) next = tile_exponents(i + 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (g.lw[i] != -INFINITY) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) e[r] += exp2_fp64(acc[r]);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    acc = next;
-                }
-                if (!whole) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) e[r] = grow + r < n ? e[r] : 1.0;
-                }
-                done = __all(e[0] >= 0x1p-1000 && e[1] >= 0x1p-1000 && e[2] >= 0x1p-1000 &&
-                             e[3] >= 0x1p-1000);
-                direct = done;
+            for (int i = 0; i < K; ++i) {
+                b1[i] = mean[i * kDdDim + kg][mq] - c1;
+                b2[i] = mean[i * kDdDim + 4 + kg][mq] - c2;
+                double q = fma(b2[i], b2[i], b1[i] * b1[i]);
+                q += __shfl_xor(q, 16, kWave);
+                q += __shfl_xor(q, 32, kWave);
+                C[i] = -s2 * q;
+                nan |= C[i] != C[i];
+                fine &= C[i] >= kDd64MinC;
+                C[i] += g.lw[i] * kLog2e;          // -inf: the component is skipped
             }
-            if (!done) {
-                double m[4];
-                // the empty asm keeps this path's addresses and, across its two
-                // passes, its K results out of the direct path's registers
-                const double* thq = th;
-                int pq = pc;
-                asm volatile("" : "+s"(thq), "+v"(pq));
-                if (fine && near) {
+        }
+        fine = __all(fine);
+        unsigned long long far = 0;                  // the block's tiles left to the differences
+        for (int st = s0; st < s1; ++st) {
+            const int buf = st & 1;
+            const bool more = st + 1 < nst;
+            if (more) load_stage(st + 1);
+            const int tile0 = t0 + st * kDd64StageTiles;
+            const int tiles = min(kDd64StageTiles, t1 - tile0);
+            for (int tt = 0; tt < tiles; ++tt) {
+                const double* ur = &su[buf][(tt * kTileRows + arow) * kDdDim];
+                const double a1 = ur[kg], a2 = ur[4 + kg];
+                double Y[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) Y[r] = sy[buf][tt * kTileRows + 4 * kg + r];
+                const int grow = (tile0 + tt) * kTileRows + 4 * kg;
+                const bool whole = (tile0 + tt + 1) * kTileRows <= n;
+                const bool near =
+                    __all(fmax(fmax(Y[0], Y[1]), fmax(Y[2], Y[3])) <= kDd64MaxY && Y[0] == Y[0] &&
+                          Y[1] == Y[1] && Y[2] == Y[2] && Y[3] == Y[3]);
+                if (!(fine && near)) {
+                    far |= 1ull << ((st - s0) * kDd64StageTiles + tt);
+                    continue;
+                }
+                auto tile_exponents = [&](int i) {
+                    f64x4 acc = {C[i] - Y[0], C[i] - Y[1], C[i] - Y[2], C[i] - Y[3]};
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1[i], acc, 0, 0, 0);
+                    return __builtin_amdgcn_mfma_f64_16x16x4f64(a2, b2[i], acc, 0, 0, 0);
+                };
+                double e[4] = {0.0, 0.0, 0.0, 0.0};
+                if (direct) {
+                    // the next component's products are started before this one's
+                    // exponentials; the fences keep the compiler from starting all K
+                    f64x4 acc = tile_exponents(0);
+#pragma unroll
+                    for (int i = 0; i < K; ++i) {
+                        f64x4 next = acc;
+                        if (i + 1 < K) next = tile_exponents(i + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (g.lw[i] != -INFINITY) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) e[r] += exp2_fp64(acc[r]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        acc = next;
+                    }
+                    if (!whole) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) e[r] = grow + r < n ? e[r] : 1.0;
+                    }
+                    direct = __all(e[0] >= 0x1p-1000 && e[1] >= 0x1p-1000 && e[2] >= 0x1p-1000 &&
+                                   e[3] >= 0x1p-1000);
+                }
+                if (!direct) {
+                    // the empty asm keeps this path's K results, across its two passes,
+                    // out of the direct path's registers
+                    double m[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         m[r] = -INFINITY;
@@ -532,57 +551,84 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
                             }
                         }
                     }
-                } else {
-#pragma unroll 1
+#pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        // by differences, one component at a time
-                        const int j = grow + r < n ? grow + r : n - 1;
-                        const float* yj = y + static_cast<size_t>(j) * kDdDim;
-                        double mr = -INFINITY, er = 0.0;
-#pragma unroll 1
-                        for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll
-                            for (int i = 0; i < K; ++i) {
-                                double d2 = 0.0;
-#pragma unroll 1
-                                for (int c = 0; c < kDdDim; ++c) {
-                                    const double t =
-                                        static_cast<double>(yj[c]) -
-                                        thq[static_cast<size_t>(i * kDdDim + c) * N + pq];
-                                    d2 = fma(t, t, d2);
-                                }
-                                const double a = g.lw[i] * kLog2e - d2 * s2;
-                                const double t = a - mr;
-                                if (pass == 0) mr = fmax(mr, a);
-                                else er += exp2_fp64(t < -4000.0 ? -4000.0 : t);
-                            }
-                        }
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            m[q] = q == r ? mr : m[q];
-                            e[q] = q == r ? er : e[q];
-                        }
+                        const bool in = grow + r < n;
+                        msum += in ? m[r] : 0.0;
+                        e[r] = in ? e[r] : 1.0;
                     }
                 }
+                // each factor may reach down to 2^-1000: renormalise after every one
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const bool in = grow + r < n;
-                    msum += in ? m[r] : 0.0;
-                    e[r] = in ? e[r] : 1.0;
+                    const double q = prod * e[r];
+                    expo += __builtin_amdgcn_frexp_exp(q);
+                    prod = __builtin_amdgcn_frexp_mant(q);
                 }
             }
-            // each factor may reach down to 2^-1000: renormalise after every one
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double q = prod * e[r];
-                expo += __builtin_amdgcn_frexp_exp(q);
-                prod = __builtin_amdgcn_frexp_mant(q);
-            }
+            if (more) store_stage(buf ^ 1);
+            __syncthreads();
         }
-        if (more) store_stage(buf ^ 1);
-        __syncthreads();
+        // the tiles set aside: by differences, RB of a tile's rows of a lane at a time
+        // (more spill beside their K exponents; k = 4: 694 us at 2, 708 at 4; k = 2:
+        // 417 and 398), in natural units about each datum's largest exponent
+        constexpr int RB = K > 2 ? 2 : 4;
+        while (far != 0) {
+            const int tile = t0 + s0 * kDd64StageTiles + __builtin_ctzll(far);
+            far &= far - 1;
+#pragma unroll 1
+            for (int h = 0; h < 4; h += RB) {
+                const int grow = tile * kTileRows + 4 * kg + h;
+                int mq = mp;                         // as above: no means held between tiles
+                asm volatile("" : "+v"(mq));
+                double x[RB][kDdDim], a[RB][K], m[RB];
+#pragma unroll
+                for (int r = 0; r < RB; ++r) {
+                    m[r] = -INFINITY;
+                    const float* yr = y + static_cast<size_t>(min(grow + r, n - 1)) * kDdDim;
+#pragma unroll
+                    for (int c = 0; c < kDdDim; ++c) x[r][c] = static_cast<double>(yr[c]);
+                }
+#pragma unroll
+                for (int i = 0; i < K; ++i) {
+                    double q[RB];
+#pragma unroll
+                    for (int r = 0; r < RB; ++r) q[r] = 0.0;
+#pragma unroll
+                    for (int c = 0; c < kDdDim; ++c) {
+                        const double mu = mean[i * kDdDim + c][mq];
+#pragma unroll
+                        for (int r = 0; r < RB; ++r) {
+                            const double t = x[r][c] - mu;
+                            q[r] = fma(t, t, q[r]);
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < RB; ++r) {
+                        a[r][i] = fma(-q[r], g.inv2s2, g.lw[i]);
+                        m[r] = fmax(m[r], a[r][i]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int r = 0; r < RB; ++r) {
+                    double e = 0.0;
+#pragma unroll
+                    for (int i = 0; i < K; ++i)
+                        e += exp2_fp64(fmax((a[r][i] - m[r]) * kLog2e, -4000.0));
+                    const bool in = grow + r < n;
+                    nsum += in ? m[r] : 0.0;
+                    prod *= in ? e : 1.0;
+                }
+            }
+            expo += __builtin_amdgcn_frexp_exp(prod);
+            prod = __builtin_amdgcn_frexp_mant(prod);
+        }
     }
-    double v = msum + static_cast<double>(expo) + log2(prod);
+    double v = msum + static_cast<double>(expo) + log2(prod) + nsum * kLog2e;
+    // the differences' clamp passed over a NaN: a mean's, or that of a datum no
+    // component has a finite exponent for
+    if (nan || !(nsum > -INFINITY)) v = NAN;
     v += __shfl_xor(v, 16, kWave);
     v += __shfl_xor(v, 32, kWave);
     if (kg == 0 && p < N) part[static_cast<size_t>(slice) * N + p] = v;

@@ -1,0 +1,89 @@
+"""The FP64 likelihood and steps at d = 8 on the matrix cores: the tiles that go by
+differences, and the tempering step's buffers."""
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import announce, oracle_model, rel_err
+from oracle import gmm as ogmm
+from workloads import make_mixture_data, theta_near_posterior, theta_prior_draws
+
+pytestmark = pytest.mark.gpu
+
+FP64_TOL = 1e-12
+
+
+@pytest.fixture(scope="module")
+def smc():
+    import paper_0905_2441_amd as smc
+    return smc
+
+
+def _loglik(smc, ctx, g, y, th):
+    out = smc.smc_loglik(ctx, g, torch.as_tensor(y).cuda(), torch.as_tensor(th).cuda(), "fp64")
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("k", [1, 2, 4, 8])
+@pytest.mark.parametrize("case,n,N,slices", [
+    ("all", 1, 17, 0), ("all", 17, 70, 0), ("all", 1025, 65, 1), ("all", 2100, 33, 2),
+    ("mixed", 1025, 65, 1), ("mixed", 1040, 16, 1), ("mixed", 2100, 130, 3), ("last", 1025, 64, 1),
+    ("first", 130, 1, 1),
+])
+def test_tiles_by_differences(smc, k, case, n, N, slices):
+    """Every tile (means hundreds of standard deviations apart), every fifth one, or
+    only the first or last, with one slice of more than 64 tiles (the block after
+    which a wave works the tiles off), partial tiles and columns. Plain FP64 terms:
+    1e-12 as for every FP64 form."""
+    announce(f"ddim fp64 differences k={k} {case} n={n} N={N} slices={slices}")
+    rng = np.random.default_rng(65)
+    mu = 3.0 * rng.standard_normal((k, 8))
+    sigma2 = 0.003 if case == "all" else 1.0
+    y = make_mixture_data(n, mu, sigma2, seed=66)
+    th = theta_near_posterior(N, mu, seed=67)
+    tiles = np.arange(n) // 16
+    far = {"all": np.zeros(n, bool), "mixed": tiles % 5 == 3, "last": tiles == tiles[-1],
+           "first": tiles == 0}[case]
+    y[far, 2] += 500.0
+    g = smc.Gmm.equal_weights(k, 8, sigma2)
+    ctx = smc.Context(0)
+    ctx.set_slices(slices)
+    err = rel_err(_loglik(smc, ctx, g, y, th), ogmm.loglik(th, y, oracle_model(g)))
+    ctx.check()
+    assert err.max() <= FP64_TOL, float(err.max())
+
+
+@pytest.mark.parametrize("what", ["nan_mean", "inf_mean", "nan_datum", "inf_datum"])
+def test_values_that_are_not_finite(smc, what):
+    """A NaN mean makes its own particle NaN and no other; an infinite mean is a
+    component of zero density; a datum that is not finite makes every particle NaN."""
+    announce(f"ddim fp64 {what}")
+    rng = np.random.default_rng(68)
+    mu = 3.0 * rng.standard_normal((4, 8))
+    y = make_mixture_data(300, mu, 1.0, seed=69)
+    th = theta_near_posterior(70, mu, seed=70)
+    g = smc.Gmm.equal_weights(4, 8, 1.0)
+    clean = ogmm.loglik(th, y, oracle_model(g))
+    hit = np.zeros(70, bool)
+    if what == "nan_mean":
+        th[11, 21] = np.nan
+        hit[21] = True
+    elif what == "inf_mean":
+        th[8:16, 21] = np.inf
+        with np.errstate(invalid="ignore"):
+            clean[21] = ogmm.loglik(th[:, 21:22], y, oracle_model(g))[0]
+    else:
+        y[37, 3] = np.nan if what == "nan_datum" else np.inf
+        hit[:] = True
+    ctx = smc.Context(0)
+    got = _loglik(smc, ctx, g, y, th)
+    assert np.array_equal(np.isnan(got), hit)
+    if not hit.all():
+        assert rel_err(got[~hit], clean[~hit]).max() <= FP64_TOL
+    if hit.any():
+        with pytest.raises(Exception, match="NaN"):
+            ctx.check()
+    else:
+        ctx.check()
