@@ -343,8 +343,8 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
 //
 // The same contraction on the FP64 matrix instruction (v_mfma_f64_16x16x4_f64),
 // for the d-dimensional FP64 likelihood: with a centre c of the data,
-//   a_{j,i} = u_j . (mu_i - c) + (C_i - Y_j),  u_j = 2 s2 (y_j - c),
-//   C_i = log2 w_i - s2 ||mu_i - c||^2,  Y_j = s2 ||y_j - c||^2,
+//   a_{j,i} = u_j . v_i + (C_i - Y_j),  u_j = y_j - c,  v_i = 2 s2 (mu_i - c),
+//   C_i = log2 w_i - ||v_i||^2 / (4 s2),  Y_j = s2 ||u_j||^2,
 // two instructions of K = 4 per component, started from C_i - Y_j. Lane l holds
 // row (l mod 16) of A, column (l mod 16) of B at K element l / 16, and the four
 // results of rows (l / 16) + 4 r of its column; A row a carries data row
@@ -353,7 +353,7 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
 // next one's need a register, so a wave holds its particles' means (4 VGPRs per
 // component) where the VALU form keeps all k*d of a particle per lane: at
 // k = d = 8 those 128 VGPRs spilled, and the VALU form took 32.7 ms at
-// N = 16384, n = 65536 against 6.1 ms here.
+// N = 16384, n = 65536 against 6.2 ms here.
 //
 // Bound by FP64 issue: per (datum, particle) k = 8 components of 8 multiply-adds
 // on the matrix unit and 16 instructions of exp2, its start and its sum (5.7 ms
@@ -361,22 +361,24 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
 // 6.1 ms, against 6.6 at the 2 that the compiler's own choice of registers
 // allows and 7.6 at 4 (spills).
 //
-// The expansion loses 2^-53 of Y_j per datum, so the centre (the mean of up to
-// 64 data spread over the array, the same in every workgroup) keeps Y_j small
-// for data far from the origin, and tiles holding a datum with Y_j above
-// kDd64MaxY, a datum that is not finite, or a particle with a mean that is not
-// finite take the difference form (no expansion, plain FP64): 8 subtractions and
-// 8 multiply-adds per component instead of the matrix unit's. A wave sets such
-// tiles aside and works them off after every block of 64, when the expansion's
-// operands are dead and their registers free, with the means from LDS: k = 8,
-// N = 16384, n = 8192 1.33 ms (the expansion 0.78), where two passes of rolled
-// loops over means and data in memory took 13.0 ms and the VALU form 4.1. Waves
-// with a particle so far away that a datum's sum falls below 2^-1000 take each
-// datum's largest exponent out first.
+// An exponent is a sum of terms of the size of Y_j and C_i. What its rounding does
+// alike for every datum would not average out: the centre is an FP32 value (the
+// mean of up to 64 data spread over the array, the same in every workgroup), so
+// that u_j is exact; C_i is formed from the rounded v_i in two parts, so that the
+// exponents are those of one mean within 2^-54 of mu_i, and the low part is a
+// factor of the component's terms. What is left averages over the data: tiles
+// holding a datum with Y_j above dd64_max_y(n), a datum that is not finite, or a
+// particle with a mean that is not finite take the difference form (no expansion,
+// plain FP64): 8 subtractions and 8 multiply-adds per component instead of the
+// matrix unit's. A wave sets such tiles aside and works them off after every block
+// of 64, when the expansion's operands are dead and their registers free, with the
+// means from LDS: k = 8, N = 16384, n = 8192 1.34 ms (the expansion 0.81), where
+// two passes of rolled loops over means and data in memory took 13.0 ms and the
+// VALU form 4.1. Waves with a particle so far away that a datum's sum falls below
+// 2^-1000 take each datum's largest exponent out first.
 constexpr int kDd64StageTiles = 8;                     // data rows per LDS stage
 constexpr int kDd64Rows = kDd64StageTiles * kTileRows;
 constexpr int kDd64Block = 8;                          // stages per block: 64 tiles, a bit each
-constexpr double kDd64MaxY = 4096.0;
 constexpr double kDd64MinC = -1.0e8;
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -384,7 +386,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <int K>
 __global__ void __launch_bounds__(kDdBlock, 3)
 k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmDev g, double s2,
-               int S, double* part) {
+               double max_y, int S, double* part) {
     __shared__ double su[2][kDd64Rows * kDdDim];
     __shared__ __align__(16) double sy[2][kDd64Rows];
     __shared__ double cen[kDdDim];
@@ -411,7 +413,7 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
         for (int c = 0; c < kDdDim; ++c) {
             const float v = yr[c];
             const double sum = wave_sum(fabsf(v) < 1.0e18f ? static_cast<double>(v) : 0.0);
-            if (threadIdx.x == 0) cen[c] = sum * (1.0 / kWave);
+            if (threadIdx.x == 0) cen[c] = static_cast<double>(static_cast<float>(sum * (1.0 / kWave)));
         }
     }
     __syncthreads();
@@ -435,11 +437,13 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
         for (int q = 0; q < 4; ++q) {
             const double d = static_cast<double>(yv[q]) - hc[q];
             ys = fma(d, d, ys);
-            su[buf][srow * kDdDim + half * 4 + q] = 2.0 * s2 * d;
+            su[buf][srow * kDdDim + half * 4 + q] = d;
         }
         ys += __shfl_xor(ys, 1, kWave);
         if (half == 0) sy[buf][srow] = s2 * ys;
     };
+    const double quarter = 0.25 / s2;                // 1 / (4 s2) in two parts
+    const double quarter_lo = fma(-quarter, 4.0 * s2, 1.0) * quarter;
     const int nst = (t1 - t0 + kDd64StageTiles - 1) / kDd64StageTiles;
     if (nst > 0) {
         load_stage(0);
@@ -458,6 +462,7 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
         // every block of stages, so that they hold no registers in its difference form
         // (the empty asm keeps them from being read once for all blocks)
         double b1[K], b2[K], C[K];
+        float cl[K];                                 // 2^(low part of C) - 1
         bool fine = true;
         {
             int mq = mp;
@@ -465,15 +470,22 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
             const double c1 = cen[kg], c2 = cen[4 + kg];
 #pragma unroll
             for (int i = 0; i < K; ++i) {
-                b1[i] = mean[i * kDdDim + kg][mq] - c1;
-                b2[i] = mean[i * kDdDim + 4 + kg][mq] - c2;
-                double q = fma(b2[i], b2[i], b1[i] * b1[i]);
-                q += __shfl_xor(q, 16, kWave);
-                q += __shfl_xor(q, 32, kWave);
-                C[i] = -s2 * q;
-                nan |= C[i] != C[i];
-                fine &= C[i] >= kDd64MinC;
-                C[i] += g.lw[i] * kLog2e;          // -inf: the component is skipped
+                b1[i] = 2.0 * s2 * (mean[i * kDdDim + kg][mq] - c1);
+                b2[i] = 2.0 * s2 * (mean[i * kDdDim + 4 + kg][mq] - c2);
+                // C_i in two parts from the rounded operands, so that the exponents are
+                // those of one (slightly moved) mean whatever the datum
+                const double p1 = b1[i] * b1[i], p2 = b2[i] * b2[i];
+                dd q = two_sum(p1, p2);
+                q.lo += fma(b1[i], b1[i], -p1) + fma(b2[i], b2[i], -p2);
+                q = dd_add(q, dd{__shfl_xor(q.hi, 16, kWave), __shfl_xor(q.lo, 16, kWave)});
+                q = dd_add(q, dd{__shfl_xor(q.hi, 32, kWave), __shfl_xor(q.lo, 32, kWave)});
+                const double h = -q.hi * quarter;
+                const double low = fma(-q.hi, quarter, -h) - q.hi * quarter_lo - q.lo * quarter;
+                nan |= b1[i] != b1[i] || b2[i] != b2[i];
+                fine &= h >= kDd64MinC;                        // false for NaN
+                const dd t = two_sum(h, g.lw[i] * kLog2e);     // -inf: the component is skipped
+                C[i] = t.hi;
+                cl[i] = static_cast<float>((t.lo + low) * kLn2);
             }
         }
         fine = __all(fine);
@@ -493,7 +505,7 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
                 const int grow = (tile0 + tt) * kTileRows + 4 * kg;
                 const bool whole = (tile0 + tt + 1) * kTileRows <= n;
                 const bool near =
-                    __all(fmax(fmax(Y[0], Y[1]), fmax(Y[2], Y[3])) <= kDd64MaxY && Y[0] == Y[0] &&
+                    __all(fmax(fmax(Y[0], Y[1]), fmax(Y[2], Y[3])) <= max_y && Y[0] == Y[0] &&
                           Y[1] == Y[1] && Y[2] == Y[2] && Y[3] == Y[3]);
                 if (!(fine && near)) {
                     far |= 1ull << ((st - s0) * kDd64StageTiles + tt);
@@ -515,8 +527,9 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
                         if (i + 1 < K) next = tile_exponents(i + 1);
                         __builtin_amdgcn_sched_barrier(0);
                         if (g.lw[i] != -INFINITY) {
+                            const double wl = 1.0 + static_cast<double>(cl[i]);
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) e[r] += exp2_fp64(acc[r]);
+                            for (int r = 0; r < 4; ++r) e[r] = fma(exp2_fp64(acc[r]), wl, e[r]);
                         }
                         __builtin_amdgcn_sched_barrier(0);
                         acc = next;
@@ -544,10 +557,11 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
                         for (int i = 0; i < K; ++i) {
                             if (g.lw[i] == -INFINITY) continue;
                             const f64x4 acc = tile_exponents(i);
+                            const double wl = 1.0 + static_cast<double>(cl[i]);
 #pragma unroll
                             for (int r = 0; r < 4; ++r) {
                                 if (pass == 0) m[r] = fmax(m[r], acc[r]);
-                                else e[r] += exp2_fp64(fmax(acc[r] - m[r], -4000.0));
+                                else e[r] = fma(exp2_fp64(fmax(acc[r] - m[r], -4000.0)), wl, e[r]);
                             }
                         }
                     }
@@ -690,6 +704,18 @@ int dd_slices(int64_t n, int64_t N) {
     return dd_clamp_slices(n, (2048 + groups - 1) / groups);
 }
 
+// Largest Y_j of a tile in the expansion over n data. A datum's exponent carries
+// about ten roundings of 2^-53 Y; they average over the data, and the largest that
+// leaves a log-likelihood's error at or below that of an exp per term and a log per
+// datum was found against extended precision (k = 8, sigma2 = 1 and 0.3, means of
+// spread 3, rms over particles, expansion and difference form against term by term:
+// n = 600 1.5 and 0.9 against 0.9e-16, n = 2000 1.2 and 0.9 against 1.6, sigma2 =
+// 0.3 n = 2000 4.0 and 1.3 against 2.2, n = 20000 3.7 and 1.5 against 6.3).
+double dd64_max_y(int64_t n) {
+    const double m = std::min(static_cast<double>(n) / 16.0, 3.0 * std::sqrt(static_cast<double>(n)));
+    return std::min(m, 4096.0);
+}
+
 bool dd64_takes(const GmmDev& g, int prec, int64_t N) {
     return prec == SMC_PREC_FP64 && dd_supported(g.k, g.d) && dd64_fits(g.k, N);
 }
@@ -775,7 +801,8 @@ hipError_t launch_dd64_partial(const GmmDev& g, const float* y, int64_t n, const
 #define SMC_DD(KK)                                                                              \
     if (g.k == KK)                                                                              \
         hipLaunchKernelGGL((k_dd64_partial<KK>), grid, dim3(kDdBlock), 0, s, y,                  \
-                           static_cast<int>(n), theta, static_cast<int>(N), g, s2_of(g), S, part);
+                           static_cast<int>(n), theta, static_cast<int>(N), g, s2_of(g),           \
+                           dd64_max_y(n), S, part);
     SMC_DD(1) SMC_DD(2) SMC_DD(4) SMC_DD(8)
 #undef SMC_DD
     return hipGetLastError();

@@ -31,8 +31,7 @@ def _term_by_term(theta, y, k, d, sigma2, slices, dtype):
     for rows in np.array_split(yy, slices):
         acc = np.zeros(th.shape[2], dtype=dtype)
         for row in rows:
-            a = np.stack([lw - sum((row[c] - th[i, c]) ** 2 for c in range(d)) * inv2s2
-                          for i in range(k)])
+            a = lw - ((row[None, :, None] - th) ** 2).sum(axis=1) * inv2s2
             m = a.max(axis=0)
             acc = acc + (m + np.log(np.exp(a - m).sum(axis=0)))
         total = total + acc
@@ -84,3 +83,23 @@ def test_error_of_the_1d_forms(smc, k, n, sigma2, order, start, slices):
     th = (theta_near_posterior(512, mu, seed=72) if start == "near"
           else theta_prior_draws(512, k, 1, seed=73))
     _check(smc, y, th, k, 1, sigma2, slices)
+
+
+@pytest.mark.parametrize("k,n,sigma2,start,slices", [
+    (8, 400, 1.0, "near", 1),
+    (8, 1100, 1.0, "near", 2),
+    (2, 1100, 1.0, "near", 2),
+    (4, 2000, 1.0, "prior", 4),
+    (8, 600, 0.3, "near", 1),
+    (8, 2000, 0.3, "near", 4),
+    (4, 2000, 0.1, "near", 4),
+    (8, 6000, 0.3, "near", 4),
+    (1, 2000, 0.03, "near", 4),
+])
+def test_error_of_the_matrix_form(smc, k, n, sigma2, start, slices):
+    announce(f"fp64 error d=8 k={k} n={n} sigma2={sigma2} {start}")
+    mu = 3.0 * np.random.default_rng(74).standard_normal((k, 8))
+    y = make_mixture_data(n, mu, sigma2, seed=75)
+    th = (theta_near_posterior(128, mu, seed=76) if start == "near"
+          else theta_prior_draws(128, k, 8, seed=77))
+    _check(smc, y, th, k, 8, sigma2, slices)
