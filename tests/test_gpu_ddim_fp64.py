@@ -7,7 +7,8 @@ import torch
 
 from gpu_common import announce, oracle_model, rel_err
 from oracle import gmm as ogmm
-from workloads import make_mixture_data, theta_near_posterior, theta_prior_draws
+from oracle import smc as osmc
+from workloads import make_mixture_data, theta_near_posterior
 
 pytestmark = pytest.mark.gpu
 
@@ -87,3 +88,56 @@ def test_values_that_are_not_finite(smc, what):
             ctx.check()
     else:
         ctx.check()
+
+
+@pytest.mark.parametrize("k,n,N", [(1, 60, 65), (2, 200, 130), (8, 150, 70)])
+@pytest.mark.parametrize("moves,ess_frac,slices,steps_per_call", [
+    (1, 0.5, 1, 1), (3, 1.0, 1, 1), (3, 0.0, 3, 1), (1, 1.0, 3, 3), (3, 0.5, 1, 3), (0, 0.5, 0, 1)])
+def test_tempering_steps_match_oracle(smc, k, n, N, moves, ess_frac, slices, steps_per_call):
+    """smc_step and smc_steps at d = 8: the first move writes its proposals into the
+    output population and, with one slice, its partial sums into the output
+    log-likelihoods; later moves use the gather's buffers; resampling never, at every
+    step (ESS below N) and by its test. Every decision, population, weight and
+    count as the oracle's, eager and replayed."""
+    announce(f"ddim fp64 steps k={k} n={n} N={N} moves={moves} ess={ess_frac} slices={slices}")
+    mu = 3.0 * np.random.default_rng(78).standard_normal((k, 8))
+    y = make_mixture_data(n, mu, 1.0, seed=79)
+    betas = np.linspace(0.0, 0.01, 7)
+    g = smc.Gmm.equal_weights(k, 8, 1.0)
+    ref = osmc.smc_run(y, oracle_model(g), betas, N, 0.4, moves, 81, ess_frac=ess_frac,
+                       resample=ess_frac > 0.0)
+    for graph in (False, True):
+        ctx = smc.Context(0)
+        ctx.set_slices(slices)
+        s = smc.SMCSampler(ctx, g, y, N, betas, 0.4, moves, 81, ess_frac=ess_frac, prec="fp64")
+        r = s.run(graph=graph, steps_per_graph=steps_per_call)
+        assert r["resamples"] == int(np.sum(ref["trace"]["resampled"]))
+        assert r["accepted"] == int(np.sum(ref["trace"]["accepted"]))
+        assert abs(r["logZ"] - ref["logZ"]) <= 1e-9 * max(1.0, abs(ref["logZ"]))
+        assert np.max(np.abs(r["theta"] - ref["theta"])) <= 1e-9
+        assert rel_err(r["l"], ref["l"]).max() <= 1e-10
+        assert np.max(np.abs(r["W"] - ref["W"])) <= 1e-12
+        assert np.max(np.abs(r["logw"] - ref["logw"])) <= 1e-8
+
+
+@pytest.mark.parametrize("k,slices", [(1, 1), (4, 1), (8, 1), (8, 2)])
+def test_single_move_with_one_slice(smc, k, slices):
+    """A standalone move whose partial sums, of one slice, share a scratch array."""
+    announce(f"ddim fp64 move k={k} slices={slices}")
+    mu = 3.0 * np.random.default_rng(82).standard_normal((k, 8))
+    y = make_mixture_data(90, mu, 1.0, seed=83)
+    g = smc.Gmm.equal_weights(k, 8, 1.0)
+    om = oracle_model(g)
+    th = theta_near_posterior(130, mu, seed=84)
+    l = ogmm.loglik(th, y, om)
+    ctx = smc.Context(0)
+    ctx.set_slices(slices)
+    t, ll = torch.as_tensor(th).cuda(), torch.as_tensor(l).cuda()
+    for move in (0, 1):
+        rt, rl, _ = osmc.rwmh_move(th, l, y, om, 0.2, 0.1, 9, 4, move)
+        smc.smc_rwmh_move(ctx, g, torch.as_tensor(y).cuda(), t, ll, 0.2, 0.1, 9, 4, move=move,
+                          prec="fp64")
+        th, l = rt, rl
+    ctx.check()
+    assert np.max(np.abs(t.cpu().numpy() - th)) <= 1e-11
+    assert rel_err(ll.cpu().numpy(), l).max() <= FP64_TOL
