@@ -914,6 +914,48 @@ __host__ __device__ constexpr int ancestor_lds_doubles(int nchunks) {
     return nchunks > 0 ? 3 * nchunks + kCdfWin : 0;
 }
 
+// LDS bytes of the pivot forms' staging rows of `slices` waves (d = 1).
+constexpr size_t rows_lds_bytes(int slices, bool rows) {
+    return rows ? sizeof(float) * kPivotRow * slices : 0;
+}
+
+constexpr size_t larger(size_t a, size_t b) { return a > b ? a : b; }
+
+// Dynamic LDS bytes of one k_rwmh workgroup (the layout at the top of k_rwmh): the
+// ancestor search's buffer, which grows with N, lies over what the move uses after
+// it. Beside it, a CU held 16 one-slice waves where it holds 20 at N = 262144 and 4
+// for 6 from 2^21 on (k = 4, n = 1000, N = 2^20: 7054 us per ten steps, 5374 now).
+constexpr size_t rwmh_dyn_lds_bytes(int slices, int nchunks, bool rows, int kd) {
+    return larger(sizeof(double) * kWave * (kd + (kd <= 16 ? kd : 0) + 2 + slices) +
+                      rows_lds_bytes(slices, rows),
+                  sizeof(double) * ancestor_lds_doubles(nchunks));
+}
+
+// Dynamic LDS bytes of one k_rwmh_multi workgroup (the layout at its top).
+constexpr size_t multi_dyn_lds_bytes(int slices, int nchunks, bool rows, int kd, int batch) {
+    return larger(sizeof(double) * kWave * (kd + 1 + batch * (kd + 1) + slices) +
+                      rows_lds_bytes(slices, rows),
+                  sizeof(double) * ancestor_lds_doubles(nchunks));
+}
+
+// Moves whose random numbers a k_rwmh_multi workgroup holds at once: two with
+// drawing waves, else as many as leave LDS for the 16 waves a CU that its registers
+// admit, at most 13 KB of them (k*d = 4: five moves, two with one slice). Ten moves
+// a step, k = 4, n = 100, N = 262144: 6945 us per 20 steps at five moves, 5356 at
+// two.
+constexpr int kMultiWavesPerCu = 16;
+constexpr size_t kCuLds = 156 * 1024;
+constexpr int multi_batch(int kd, int slices, bool rows, int n_moves, bool drawers) {
+    if (drawers) return 2;
+    const size_t fixed = multi_dyn_lds_bytes(slices, 0, rows, kd, 0);
+    const size_t one = sizeof(double) * kWave * (kd + 1);
+    int fit = 1;
+    while (fit < n_moves && (fit + 1) * one <= size_t{13 * 1024} &&
+           fixed + (fit + 1) * one <= kCuLds * slices / kMultiWavesPerCu)
+        ++fit;
+    return fit;
+}
+
 // Ancestors of the 64 particles of this workgroup after resampling
 // (cooperative: every thread of the block must call it). Wave 0 forms the chunk
 // offsets and ends in LDS (exclusive double-double scan of the chunk totals; buf

@@ -139,21 +139,21 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
     constexpr bool kRows = D == 1;
     // the current state held in LDS for the decision (small k*d)
     constexpr bool kHold = KD <= 16;
-    __shared__ double red[kMaxSlices][kWave];
     __shared__ int anc[kWave];
-    __shared__ double prs[KD][kWave];
-    __shared__ double hold[kHold ? KD : 1][kWave];
-    __shared__ double hold_l[kWave];
-    __shared__ double lus[kWave];
-    // LDS sized by the launch (rwmh_dyn_lds_bytes): for 1-D data the
-    // waves' staging rows [S][kPivotRow] floats, then fused_ancestors' buffer when
-    // the move can resample
+    // LDS sized by the launch (rwmh_dyn_lds_bytes): rows of 64 doubles, the proposals'
+    // pairs [KD], the held state [KD] and its log-likelihood, log u, the slices'
+    // sums [S] and for 1-D data the waves' staging rows [S]. fused_ancestors' buffer
+    // lies over all of them: a barrier parts the two uses.
     extern __shared__ __align__(16) double lds[];
     const int S = wave_uniform(blockDim.x / kWave);
-    double* anc_lds = lds + (kRows ? S * (kPivotRow / 2) : 0);
+    double (*prs)[kWave] = reinterpret_cast<double (*)[kWave]>(lds);
+    double (*hold)[kWave] = prs + KD;
+    double* hold_l = *(hold + (kHold ? KD : 0));
+    double* lus = hold_l + kWave;
+    double (*red)[kWave] = reinterpret_cast<double (*)[kWave]>(lus + kWave);
     const int lane = lane_id();
     const int w = wave_uniform(threadIdx.x / kWave);
-    float* row = kRows ? reinterpret_cast<float*>(lds) + w * kPivotRow : nullptr;
+    float* row = kRows ? reinterpret_cast<float*>(red + S) + w * kPivotRow : nullptr;
     const int tile = static_cast<int>(blockIdx.x) / G;
     const int grp = static_cast<int>(blockIdx.x) - tile * G;
     const int p = tile * kWave + lane;
@@ -170,7 +170,7 @@ k_rwmh(const float* __restrict__ y, int n, double* theta, double* l, int N,
     if (ms.t_out != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
         *ms.t_out = static_cast<int>(step);
     const bool fused = (ms.cdf_hi != nullptr) && (ms.state != nullptr) && (ms.state->resampled != 0);
-    if (fused) fused_ancestors(ms, N, step, pc, anc, anc_lds);
+    if (fused) fused_ancestors(ms, N, step, pc, anc, lds);
     const MoveSource srcs = move_source(ms, theta, l);
     const int a = fused ? anc[lane] : pc;
 
@@ -240,28 +240,28 @@ k_rwmh_multi(const float* __restrict__ y, int n, double* theta, double* l, int N
     constexpr int KD = K * D;
     constexpr int NP = (KD + 1) / 2;            // Box-Muller pairs per particle
     constexpr bool kRows = D == 1;
-    __shared__ double red[kMaxSlices][kWave];
     __shared__ int anc[kWave];
-    __shared__ double cur[KD][kWave];
-    __shared__ double lcur[kWave];
-    // LDS sized by the launch (multi_dyn_lds_bytes): the staging rows and
-    // fused_ancestors' buffer as in k_rwmh, then the random numbers [batch][KD + 1][64]
+    // LDS sized by the launch (multi_dyn_lds_bytes): rows of 64 doubles, the current
+    // state [KD] and its log-likelihood, the random numbers [batch][KD + 1], the
+    // slices' sums [S] and for 1-D data the staging rows [S]; fused_ancestors'
+    // buffer over them as in k_rwmh
     extern __shared__ __align__(16) double lds[];
     S = wave_uniform(S);
     const int nw = wave_uniform(blockDim.x / kWave);
-    const int nch = ms.cdf_hi != nullptr ? ms.nchunks : 0;
-    double* anc_lds = lds + (kRows ? S * (kPivotRow / 2) : 0);
-    double* rnd = anc_lds + ancestor_lds_doubles(nch);
+    double (*cur)[kWave] = reinterpret_cast<double (*)[kWave]>(lds);
+    double* lcur = *(cur + KD);
+    double* rnd = lcur + kWave;
+    double (*red)[kWave] = reinterpret_cast<double (*)[kWave]>(rnd + batch * (KD + 1) * kWave);
     const int lane = lane_id();
     const int w = wave_uniform(threadIdx.x / kWave);
-    float* row = kRows && w < S ? reinterpret_cast<float*>(lds) + w * kPivotRow : nullptr;
+    float* row = kRows && w < S ? reinterpret_cast<float*>(red + S) + w * kPivotRow : nullptr;
     const int p = static_cast<int>(blockIdx.x) * kWave + lane;
     const int pc = p < N ? p : N - 1;
     int j0, j1;
     slice_bounds(n, w < S ? w : 0, S, j0, j1);
     const uint32_t step = static_cast<uint32_t>(step_index(src));
     const bool fused = (ms.cdf_hi != nullptr) && (ms.state != nullptr) && (ms.state->resampled != 0);
-    if (fused) fused_ancestors(ms, N, step, pc, anc, anc_lds);
+    if (fused) fused_ancestors(ms, N, step, pc, anc, lds);
     const MoveSource srcs = move_source(ms, theta, l);
     if (w == 0) {
         const int a = fused ? anc[lane] : pc;
@@ -811,38 +811,8 @@ __global__ void k_prior(int N, uint64_t seed, GmmDev g, double* __restrict__ the
 
 namespace {
 
-// Largest dynamic LDS a k_rwmh launch asks for (its static part is at most
-// 8 KB + 64 KB + 1280 B).
-constexpr size_t kMaxRwmhLds = 34 * 1024;
-
-// Moves whose random numbers a k_rwmh_multi workgroup holds at once: two with
-// drawing waves, else 13 KB of them (five moves at k*d = 4), so that LDS admits as
-// many workgroups per CU as registers do.
-constexpr size_t kMultiRandomBytes = 18 * 1024;
-
-int multi_batch(int kd, int n_moves, bool drawers) {
-    const int fit = static_cast<int>(size_t{13 * 1024} / (sizeof(double) * kWave * (kd + 1)));
-    return drawers ? 2 : std::max(1, std::min(n_moves, fit));
-}
-
-// LDS bytes of the pivot forms' staging rows of `slices` waves (d = 1).
-size_t rows_lds_bytes(int slices, bool rows) {
-    return rows ? sizeof(float) * slices * kPivotRow : 0;
-}
-
-// Dynamic LDS bytes of one k_rwmh workgroup (the layout at the top of k_rwmh).
-size_t rwmh_dyn_lds_bytes(int slices, int nchunks, bool rows) {
-    return rows_lds_bytes(slices, rows) +
-           sizeof(double) * static_cast<size_t>(ancestor_lds_doubles(nchunks));
-}
-
-// Dynamic LDS bytes of one k_rwmh_multi workgroup: k_rwmh's, then the random
-// numbers of `batch` moves.
-constexpr size_t kMaxMultiLds = kMaxRwmhLds + kMultiRandomBytes;
-size_t multi_dyn_lds_bytes(int slices, int nchunks, bool rows, int kd, int batch) {
-    return rwmh_dyn_lds_bytes(slices, nchunks, rows) +
-           sizeof(double) * kWave * static_cast<size_t>(kd + 1) * static_cast<size_t>(batch);
-}
+// Largest dynamic LDS a move's launch asks for.
+constexpr size_t kMaxMoveLds = 64 * 1024;
 
 }  // namespace
 
@@ -903,8 +873,8 @@ hipError_t launch_move_partials(const float* y, int64_t n, double* theta, double
     const dim3 block(static_cast<unsigned>(kWave * sp.slices));
     const int nch = ms.cdf_hi != nullptr ? ms.nchunks : 0;
     if (nch < 0 || nch > kMaxChunks) return hipErrorInvalidValue;
-    const size_t lds = rwmh_dyn_lds_bytes(sp.slices, nch, D == 1);
-    if (lds > kMaxRwmhLds) return hipErrorInvalidValue;
+    const size_t lds = rwmh_dyn_lds_bytes(sp.slices, nch, D == 1, K * D);
+    if (lds > kMaxMoveLds) return hipErrorInvalidValue;
     const SliceMap sm = slice_map(static_cast<int>(n), sp.total);
     if (ms.lw_next != nullptr)
         hipLaunchKernelGGL((k_rwmh<K, D, P, true>), grid, block, lds, s, y, static_cast<int>(n),
@@ -990,9 +960,9 @@ hipError_t launch_rwmh_moves(const GmmDev& g, const float* y, int64_t n, double*
     if (nch < 0 || nch > kMaxChunks) return hipErrorInvalidValue;
 #define SMC_MULTI(K, D, P)                                                                     \
     do {                                                                                       \
-        const int batch = multi_batch(K * D, n_moves, waves > sp.slices);                      \
+        const int batch = multi_batch(K * D, sp.slices, D == 1, n_moves, waves > sp.slices);   \
         const size_t lds = multi_dyn_lds_bytes(sp.slices, nch, D == 1, K * D, batch);          \
-        if (lds > kMaxMultiLds) return hipErrorInvalidValue;                                   \
+        if (lds > kMaxMoveLds) return hipErrorInvalidValue;                                    \
         if (ms.lw_next != nullptr)                                                             \
             hipLaunchKernelGGL((k_rwmh_multi<K, D, P, true>), grid, block, lds, s, y,          \
                                static_cast<int>(n), theta, l, static_cast<int>(N), src, sd,    \

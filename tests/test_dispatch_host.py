@@ -48,3 +48,22 @@ def test_proposal_threads_are_numbered_beyond_2_31(answers):
              (2 ** 32 - 256, 2 ** 29 - 32, 8, (0, -1, -1)), (14, 5, 3, (1, 4, 2)), (15, 5, 3, (0, -1, -1))]
     got = answers([f"column {q} {N} {k}" for q, N, k, _ in cases])
     assert got == [w for *_, w in cases]
+
+
+@pytest.mark.parametrize("kd", [1, 2, 4, 8])
+@pytest.mark.parametrize("slices", [1, 2, 4, 16])
+def test_move_lds_leaves_a_cu_its_waves(answers, kd, slices):
+    """At any N (up to 1024 CDF chunks) a move's workgroup takes no more LDS than the
+    ancestor search and the move need one after the other, and the random numbers of
+    several moves leave room for the 16 waves a CU that the registers admit (or one
+    move's numbers, the least)."""
+    chunks = [0, 1, 128, 256, 512, 1024]
+    got = answers([f"lds {slices} {c} {kd} 10" for c in chunks])
+    for c, (one, many, batch) in zip(chunks, got):
+        search = 8 * (3 * c + 256) if c else 0
+        row = 512 * slices                           # 64 doubles, a row of a wave each
+        assert one == max(512 * (2 * kd + 2) + 2 * row, search)
+        work = 512 * (kd + 1) * (batch + 1) + 2 * row
+        assert many == max(work, search) and one < 65536 and many < 65536
+        assert 1 <= batch <= 10
+        assert batch == 1 or (160 * 1024) // work * slices >= 16
