@@ -235,30 +235,38 @@ k_cdf_chunks(WeightSrc w, int N, Scratch sc, ResamplePred pred) {
 }
 
 // Exclusive double-double scan of the nchunks chunk totals into res_off. Workgroup
-// b writes the offsets of chunks [256 b, 256 b + 256) and sums the totals before
+// b writes the offsets of its `pieces` runs of 256 chunks and sums the totals before
 // them itself, with coalesced independent loads, so no workgroup waits on another
-// (one workgroup for all of them took 29 us at 16384 chunks).
+// (one workgroup for all of them took 29 us at 16384 chunks). At most kOffsetBlocks
+// workgroups, so that what they read before their own grows with the chunks and not
+// with their square (N = 2^28, 2^30: 99 and 485 us; with a workgroup for every 256
+// chunks 104 and 2084, with 64 workgroups 124 at 2^28).
+constexpr int kOffsetBlocks = 256;
 __global__ void __launch_bounds__(kRedBlock)
-k_cdf_offsets(int nchunks, Scratch sc, ResamplePred pred) {
+k_cdf_offsets(int nchunks, int pieces, Scratch sc, ResamplePred pred) {
     if (!should_fire(pred)) return;
     const double2* tot = reinterpret_cast<const double2*>(sc.res_tot);
     double2* off = reinterpret_cast<double2*>(sc.res_off);
     const int t = threadIdx.x;
-    const int c0 = blockIdx.x * kRedBlock;
+    const int c0 = blockIdx.x * pieces * kRedBlock;
+    const int c1 = min(nchunks, c0 + pieces * kRedBlock);
     dd before = dd_zero();
 #pragma unroll 8
     for (int c = t; c < c0; c += kRedBlock) {
         const double2 v = tot[c];
         before = dd_add(before, dd{v.x, v.y});
     }
-    const int c = c0 + t;
-    const double2 v = c < nchunks ? tot[c] : double2{0.0, 0.0};
-    dd total, own;
-    (void)block_dd_exclusive_scan(before, total);
-    const dd excl = block_dd_exclusive_scan(dd{v.x, v.y}, own);
-    if (c < nchunks) {
-        const dd o = dd_add(total, excl);
-        off[c] = double2{o.hi, o.lo};
+    dd lead, own;
+    (void)block_dd_exclusive_scan(before, lead);
+    for (int p0 = c0; p0 < c1; p0 += kRedBlock) {
+        const int c = p0 + t;
+        const double2 v = c < c1 ? tot[c] : double2{0.0, 0.0};
+        const dd excl = block_dd_exclusive_scan(dd{v.x, v.y}, own);
+        if (c < c1) {
+            const dd o = dd_add(lead, excl);
+            off[c] = double2{o.hi, o.lo};
+        }
+        lead = dd_add(lead, own);
     }
 }
 
@@ -784,8 +792,10 @@ hipError_t launch_resample(const Scratch& sc, WeightSrc w, int64_t N, int scheme
     if (e != hipSuccess) return e;
     const bool lds_off = nchunks <= kLdsChunks;
     if (!lds_off) {
-        hipLaunchKernelGGL(k_cdf_offsets, dim3((nchunks + kRedBlock - 1) / kRedBlock),
-                           dim3(kRedBlock), 0, s, nchunks, sc, pred);
+        const int runs = (nchunks + kRedBlock - 1) / kRedBlock;
+        const int pieces = (runs + kOffsetBlocks - 1) / kOffsetBlocks;
+        hipLaunchKernelGGL(k_cdf_offsets, dim3((runs + pieces - 1) / pieces), dim3(kRedBlock), 0,
+                           s, nchunks, pieces, sc, pred);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

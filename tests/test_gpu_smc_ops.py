@@ -914,3 +914,23 @@ def test_rwmh_move_ddim_matches_oracle(smc, ctx, prec):
     assert np.max(np.abs(got_th[:, same] - th_ref[:, same])) <= 1e-12
     tol = 1e-12 if prec == "fp64" else 1e-6
     assert rel_err(got_l[same], l_ref[same]).max() <= tol
+
+
+def test_resample_offsets_over_several_runs_of_chunks(smc, ctx):
+    """Past 2^26 particles a workgroup of the chunk offsets takes several runs of 256
+    chunks (here two, the last workgroup one and a ragged one): weights m_j 2^-40 with
+    whole m_j, so every prefix sum is exact in FP64 and the indices follow from it."""
+    N = (1 << 26) + 3 * (1 << 18) + 321
+    announce(f"resample offsets N={N}")
+    rng = np.random.default_rng(91)
+    m = rng.integers(0, 1 << 14, size=N, dtype=np.int64)
+    m[rng.random(N) < 0.4] = 0
+    m[-1000:] = 0
+    m[5] += (1 << 40) - int(m.sum())                 # total mass 1
+    assert m[5] > 0
+    C = np.cumsum(m).astype(np.float64) * 2.0 ** -40
+    U = osmc.resample_points(N, "systematic", 17, 3)
+    idx = torch.empty(N, dtype=torch.int32).cuda()
+    smc.smc_resample(ctx, _cuda(m.astype(np.float64) * 2.0 ** -40), "systematic", 17, 3, idx=idx)
+    ref = np.minimum(np.searchsorted(C, U, side="right"), np.searchsorted(C, C[-1], side="left"))
+    assert np.array_equal(idx.cpu().numpy(), ref)
