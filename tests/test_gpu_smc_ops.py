@@ -934,3 +934,26 @@ def test_resample_offsets_over_several_runs_of_chunks(smc, ctx):
     smc.smc_resample(ctx, _cuda(m.astype(np.float64) * 2.0 ** -40), "systematic", 17, 3, idx=idx)
     ref = np.minimum(np.searchsorted(C, U, side="right"), np.searchsorted(C, C[-1], side="left"))
     assert np.array_equal(idx.cpu().numpy(), ref)
+
+
+def test_weights_exponential_to_the_last_bit(smc, ctx):
+    """One particle at log-weight 0 and the others below -47, whose sum vanishes beside
+    it: S = 1 and every other weight is the exponential itself. Only a final rounding
+    (2^-53) and the rounding of the remainder (2^-55) are left: 1.3e-16 = 1.17 2^-53.
+    At the end of the range a weight is within half the smallest number, then zero."""
+    announce("weights' exponential")
+    N = 4096
+    rng = np.random.default_rng(92)
+    x = -47.0 - 653.0 * rng.random(N)
+    x[0] = 0.0
+    x[1:6] = (-np.inf, -745.0, -746.5, -1e300, -708.3)
+    W = torch.empty(N, dtype=torch.float64).cuda()
+    smc.smc_reweight(ctx, _cuda(x), _cuda(np.zeros(N)), 0.0, W=W)
+    ctx.check()
+    got = W.cpu().numpy()
+    want = np.exp(x.astype(np.longdouble))
+    assert got[0] == 1.0 and got[1] == 0.0 and got[3] == 0.0 and got[4] == 0.0
+    assert abs(got[2] - want[2]) <= np.longdouble(2.0) ** -1075   # (zero as a float)
+    rest = np.r_[5:N]
+    err = np.abs((got[rest] - want[rest]) / want[rest]).astype(np.float64)
+    assert err.max() <= 1.3e-16, float(err.max())
