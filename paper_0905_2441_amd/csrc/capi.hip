@@ -25,6 +25,7 @@ struct smc_ctx_s {
     void* fixed = nullptr;       // partials, chunk totals, status, state
     void* grow = nullptr;        // cdf, dd partials, l_tmp, theta_tmp
     int64_t grow_kd = 0;
+    int64_t refused = 0;         // N * kd of an optional scratch that could not be had
     void* mm = nullptr;          // MFMA form: data rows, columns, proposals, partials
     double* fsv_mom = nullptr;   // particle filter: per-block moment sums (in `fixed`)
     // Scratch superseded by a larger allocation. Graphs captured earlier hold
@@ -236,17 +237,18 @@ int ensure_scratch(smc_ctx ctx, int64_t N, int64_t kd, hipStream_t s) {
     const size_t b_th = align_up(sizeof(double) * cap * kdc);
     const size_t b_res = align_up(sizeof(double) * 2 * res_chunks(cap));
     SMC_CHECK_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-    SMC_CHECK_HIP(hipDeviceSynchronize(), "hipDeviceSynchronize before scratch growth");
-    if (ctx->grow) {
-        ctx->retired.push_back(ctx->grow);
-        ctx->grow = nullptr;
-    }
+    // the scratch in use stays in use where the larger one cannot be had
     void* p = nullptr;
     if (hipMalloc(&p, 2 * b_cdf + b_l + b_th + 2 * b_res) != hipSuccess) {
-        ctx->sc.cap = 0;
-        ctx->grow_kd = 0;
+        (void)hipGetLastError();
         return fail(SMC_ERR_NOMEM, "device allocation of context scratch failed");
     }
+    const hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) {
+        (void)hipFree(p);
+        return hip_fail(e, "hipDeviceSynchronize before scratch growth");
+    }
+    if (ctx->grow) ctx->retired.push_back(ctx->grow);
     char* c = static_cast<char*>(p);
     ctx->grow = p;
     ctx->sc.cdf_hi = reinterpret_cast<double*>(c);
@@ -257,16 +259,20 @@ int ensure_scratch(smc_ctx ctx, int64_t N, int64_t kd, hipStream_t s) {
     ctx->sc.res_off = reinterpret_cast<double*>(c + 2 * b_cdf + b_l + b_th + b_res);
     ctx->sc.cap = cap;
     ctx->grow_kd = kdc;
+    ctx->refused = 0;
     return SMC_OK;
 }
 
 // Whether the scratch of N particles of kd parameters is there or could be had
-// (no growth inside a capture); leaves no error behind.
+// (no growth inside a capture); leaves no error behind, and what a size was refused
+// once it is not asked for again before some scratch has grown.
 bool have_scratch(smc_ctx ctx, int64_t N, int64_t kd, hipStream_t s) {
     if (ctx->sc.cap >= N && ctx->grow_kd >= kd) return true;
-    if (capturing(s)) return false;
+    if (capturing(s) || (ctx->refused > 0 && N * kd >= ctx->refused)) return false;
+    const std::string before = g_last_error;
     if (ensure_scratch(ctx, N, kd, s) == SMC_OK) return true;
-    (void)hipGetLastError();
+    ctx->refused = N * kd;
+    g_last_error = before;
     return false;
 }
 
@@ -284,17 +290,17 @@ int ensure_mm_scratch(smc_ctx ctx, int64_t n, int64_t N, hipStream_t s) {
     const size_t b_prop = align_up(sizeof(double) * nc * SMC_KDMAX);
     const size_t b_part = align_up(sizeof(double) * nc * kMaxSlices);
     SMC_CHECK_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-    SMC_CHECK_HIP(hipDeviceSynchronize(), "hipDeviceSynchronize before scratch growth");
-    if (ctx->mm) {
-        ctx->retired.push_back(ctx->mm);
-        ctx->mm = nullptr;
-    }
     void* p = nullptr;
     if (hipMalloc(&p, b_rows + b_cols + b_prop + b_part) != hipSuccess) {
-        ctx->sc.mm_rows_cap = 0;
-        ctx->sc.mm_n_cap = 0;
+        (void)hipGetLastError();
         return fail(SMC_ERR_NOMEM, "device allocation of MFMA scratch failed");
     }
+    const hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) {
+        (void)hipFree(p);
+        return hip_fail(e, "hipDeviceSynchronize before scratch growth");
+    }
+    if (ctx->mm) ctx->retired.push_back(ctx->mm);
     char* c = static_cast<char*>(p);
     ctx->mm = p;
     ctx->sc.mm_rows = reinterpret_cast<__bf16*>(c);

@@ -957,3 +957,27 @@ def test_weights_exponential_to_the_last_bit(smc, ctx):
     rest = np.r_[5:N]
     err = np.abs((got[rest] - want[rest]) / want[rest]).astype(np.float64)
     assert err.max() <= 1.3e-16, float(err.max())
+
+
+def test_a_reservation_that_fails_keeps_the_scratch_in_use(smc):
+    """A reservation beyond the card's memory is refused and leaves the former one:
+    a capture that fitted before still fits (it may not allocate)."""
+    announce("reservation refused")
+    from paper_0905_2441_amd.api import Graph
+    c = smc.Context(0)
+    N = 3000
+    c.reserve(N, 4, 200)
+    with pytest.raises(smc.SmcError, match="allocation"):
+        c.reserve(2 ** 31 - 1, 64)
+    W = osmc.normalise(lognormal_logw(N, seed=93, spread=2.0))
+    Wd, s = _cuda(W), torch.cuda.Stream()
+    idx = torch.empty(N, dtype=torch.int32).cuda()
+    torch.cuda.synchronize()
+    graph = Graph(c, s)
+    with graph:
+        smc.smc_resample(c, Wd, "systematic", 5, 2, idx=idx, stream=s)
+    for _ in range(2):
+        graph.launch()
+    s.synchronize()
+    graph.close()
+    assert np.array_equal(idx.cpu().numpy(), osmc.resample_indices(W, "systematic", 5, 2))
