@@ -1230,14 +1230,10 @@ int smc_rng_normals(uint64_t seed, int64_t count, int32_t per_index, uint32_t st
 
 // ---------------------------------------------------------------- batched runs
 
-// Data slices of every run's log-likelihood, as a call for the run alone would
-// choose them.
-std::vector<int> init_slices(const smc_ctx_s* ctx, const GmmDev& g, int prec,
-                             const std::vector<smc_run_desc>& runs) {
-    std::vector<int> S(runs.size());
-    for (size_t i = 0; i < runs.size(); ++i)
-        S[i] = choose_slices(ctx, g, prec, runs[i].n, runs[i].N);
-    return S;
+// Data slices of a run's log-likelihood, as a call for the run alone would choose
+// them.
+int init_slices(const smc_ctx_s* ctx, const GmmDev& g, int prec, const smc_run_desc& run) {
+    return choose_slices(ctx, g, prec, run.n, run.N);
 }
 
 struct smc_batch_s {
@@ -1298,7 +1294,9 @@ int smc_batch_create(smc_ctx ctx, const smc_run_desc* runs, int32_t R, int32_t k
     std::vector<int> slices[2];
     std::vector<BatchUnit> iunits[2];
     for (int pi = 0; pi < 2; ++pi) {
-        slices[pi] = init_slices(ctx, shape, pi == 1 ? SMC_PREC_FP32 : SMC_PREC_FP64, descs);
+        for (const smc_run_desc& d : descs)
+            slices[pi].push_back(
+                init_slices(ctx, shape, pi == 1 ? SMC_PREC_FP32 : SMC_PREC_FP64, d));
         std::vector<int> by(order);
         std::stable_sort(by.begin(), by.end(), [&](int a, int b) {
             return runs[a].n / slices[pi][a] > runs[b].n / slices[pi][b];
@@ -1415,7 +1413,11 @@ int smc_batch_init(smc_ctx ctx, smc_batch b, const smc_gmm* model, const float* 
     if (!y || !theta || !loglik) return fail(SMC_ERR_INVALID_ARG, "NULL array");
     const hipStream_t s = as_stream(stream);
     // other slices in force now than at the batch's creation: a launch per run
-    if (init_slices(ctx, g, prec, b->runs) != b->slices[prec == SMC_PREC_FP32 ? 1 : 0]) {
+    const std::vector<int>& made = b->slices[prec == SMC_PREC_FP32 ? 1 : 0];
+    bool same = true;
+    for (size_t i = 0; i < b->runs.size(); ++i)
+        same = same && init_slices(ctx, g, prec, b->runs[i]) == made[i];
+    if (!same) {
         for (const smc_run_desc& d : b->runs) {
             double* th = theta + static_cast<int64_t>(b->kd) * d.p_off;
             if ((r = smc_prior_init(ctx, model, d.N, d.seed, th, stream))) return r;
