@@ -476,10 +476,12 @@ k_pt_local(const float* __restrict__ y, int n, double* theta, double* l, int M,
         double pr[KD], cu[KD], lc = 0.0;
         Half half{};
         if (worker) {
-            lc = lcur[col];
+            // lanes past the last chain follow it through its exchanges: the forms that
+            // a wave takes depend on all its lanes
+            lc = lcur[cc];
 #pragma unroll
             for (int c = 0; c < KD; ++c) {
-                cu[c] = cur[c][col];
+                cu[c] = cur[c][cc];
                 pr[c] = cu[c] + sd * zs[AHEAD ? buf : 0][c][col];
             }
             // the same per-datum forms as the one-launch-per-iteration path, so the

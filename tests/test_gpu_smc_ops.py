@@ -981,3 +981,37 @@ def test_a_reservation_that_fails_keeps_the_scratch_in_use(smc):
     s.synchronize()
     graph.close()
     assert np.array_equal(idx.cpu().numpy(), osmc.resample_indices(W, "systematic", 5, 2))
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("M,slices,ordered", [(129, 3, False), (129, 3, True), (33, 4, True),
+                                              (70, 2, True), (100, 1, True), (65, 8, False)])
+def test_pt_iterations_with_a_ragged_last_tile(smc, ctx, prec, M, slices, ordered):
+    """The lanes past the last chain take part in their wave's choice of per-datum
+    forms: in the single-workgroup form too they hold the last chain's state after its
+    exchanges, so many iterations equal single ones bit for bit."""
+    announce(f"pt ragged tile {prec} M={M} slices={slices} ordered={ordered}")
+    mu = np.linspace(-3.0, 6.0, 4)
+    y = make_mixture_data(700, mu, 0.55, seed=94)
+    y = _cuda(np.sort(y) if ordered else y, torch.float32)
+    g = smc.Gmm.equal_weights(4, 1, 0.55)
+    th = theta_prior_draws(M, 4, 1, seed=95)
+    l = ogmm.loglik(th, y.cpu().numpy(), oracle_model(g))
+    bd, outs = _cuda(pt_betas(M, 4)), []
+    ctx.set_slices(slices)
+    ctx.set_pt_single_workgroup(1)
+    try:
+        for fused in (True, False):
+            tt, lt = _cuda(th), _cuda(l)
+            it = torch.full((1,), 5, dtype=torch.int32).cuda()
+            for _ in range(1 if fused else 40):
+                if fused:
+                    smc.pt_iterations(ctx, g, y, tt, lt, bd, it, 40, 0.5, 41, 1, True, prec)
+                else:
+                    smc.pt_iteration(ctx, g, y, tt, lt, bd, it, 0.5, 41, 1, True, prec)
+            ctx.check()
+            outs.append((tt.cpu().numpy(), lt.cpu().numpy()))
+    finally:
+        ctx.set_slices(0)
+        ctx.set_pt_single_workgroup(0)
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
