@@ -477,7 +477,7 @@ int smc_loglik(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n,
         if (e != hipSuccess) return hip_fail(e, "MFMA loglik launch");
         return SMC_OK;
     }
-    if (dd64_takes(g, prec, N)) {
+    if (dd64_takes(g, prec, n, N, false)) {
         const int S = choose_dd64_slices(ctx, g, n, N);
         const hipError_t e = launch_dd64_loglik(g, y, n, theta, N, S == 1 ? loglik : ctx->sc.mv_part,
                                                 S, loglik, ctx->sc.status, s);
@@ -535,7 +535,7 @@ int smc_rwmh_move(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n,
     }
     // the FP64 matrix form keeps the proposals in the context scratch: a call that
     // cannot have it (a capture before it was reserved, no memory) takes the VALU form
-    if (dd64_takes(g, prec, N) && have_scratch(ctx, N, g.k * g.d, as_stream(stream))) {
+    if (dd64_takes(g, prec, n, N, true) && have_scratch(ctx, N, g.k * g.d, as_stream(stream))) {
         const int S = choose_dd64_slices(ctx, g, n, N);
         const hipError_t e = launch_dd64_rwmh(
             g, y, n, theta, loglik, N, beta_vec, host_src(static_cast<int>(step), beta, 0.0),
@@ -711,7 +711,7 @@ int smc_step(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n, int64
     }
     int chunk, nchunks;
     cdf_layout(N, &chunk, &nchunks);
-    const bool mfma64 = dd64_takes(g, prec, N);
+    const bool mfma64 = dd64_takes(g, prec, n, N, true);
     if (mfma || mfma64) {
         e = launch_search_gather(ctx->sc, N, ctx->scheme, seed, later, ctx->sc.state, theta_in,
                                  ctx->sc.theta_tmp, kd, loglik_in, ctx->sc.l_tmp, logw, 0, s);
@@ -785,7 +785,7 @@ int smc_steps(smc_ctx ctx, const smc_gmm* model, const float* y, int64_t n, int6
     constexpr int64_t kFusedTiles = static_cast<int64_t>(sizeof(double)) * kMaxGroups * kSplitCap /
                                     static_cast<int64_t>(sizeof(RwPartial));
     const Split sp = choose_split(ctx, g, prec, n, N, true);
-    const bool fuse = prec != SMC_PREC_BF16X3 && !dd64_takes(g, prec, N) &&
+    const bool fuse = prec != SMC_PREC_BF16X3 && !dd64_takes(g, prec, n, N, true) &&
                       rwmh_moves_chainable(g, n_moves, sp) &&
                       n_steps >= 2 && tiles <= kFusedTiles;
     if (!fuse) {

@@ -716,8 +716,9 @@ double dd64_max_y(int64_t n) {
     return std::min(m, 4096.0);
 }
 
-bool dd64_takes(const GmmDev& g, int prec, int64_t N) {
-    return prec == SMC_PREC_FP64 && dd_supported(g.k, g.d) && dd64_fits(g.k, N);
+bool dd64_takes(const GmmDev& g, int prec, int64_t n, int64_t N, bool move) {
+    return prec == SMC_PREC_FP64 && dd_supported(g.k, g.d) && dd64_fits(g.k, N) &&
+           dd64_pays(g.k, n, N, move);
 }
 
 int dd64_slices(int64_t n, int64_t N, int64_t want, int64_t part_cap) {

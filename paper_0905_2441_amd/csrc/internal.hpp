@@ -282,7 +282,7 @@ hipError_t launch_dd_rwmh(const GmmDev& g, const __bf16* A, int64_t n, double* t
 // particles (one slice may share the output array). The move writes its
 // proposals to theta_prop, which may be the output population of an out-of-place
 // move (theta itself).
-bool dd64_takes(const GmmDev& g, int prec, int64_t N);
+bool dd64_takes(const GmmDev& g, int prec, int64_t n, int64_t N, bool move);
 // Particle p and component i of thread q of a launch over N * K of them; false beyond
 // the last. Unsigned: N * K stays below 2^32 (dd64_fits; in BF16x3 by the columns'
 // memory, 1 KB a particle), not below 2^31.
@@ -297,6 +297,19 @@ __host__ __device__ constexpr bool dd_column(unsigned q, int N, int K, int& p, i
 // Larger populations take the VALU form, 64 threads per 64 particles at one slice.
 constexpr bool dd64_fits(int k, int64_t N) {
     return (N * k + 255) / 256 * 256 < (int64_t{1} << 32) && (N + 63) / 64 * 256 < (int64_t{1} << 32);
+}
+// Whether that form pays against the VALU form. Its fixed work (the proposals' and the
+// decision's own launches, the setup of a wave) wants data: ten moves a step at
+// N = 65536, us for five steps, VALU and matrix form: k = 2 n = 50 1588 and 3051,
+// n = 130 2971 and 4010, n = 160 6192 and 4057 (N = 16384 1552 and 2118), n = 200 6842
+// and 4518; k = 4 n = 50 3461 and 4058; k = 8 n = 50 18433 and 7874. One
+// log-likelihood at N = 262144: k = 4 n = 50 113 and 124, n = 100 238 and 183, n = 20
+// 49 and 86; k = 8 n = 10 109 and 145. Few particles leave the VALU form few waves: at
+// N = 4096 it takes 35 against 13 us (k = 4, n = 50).
+constexpr bool dd64_pays(int k, int64_t n, int64_t N, bool move) {
+    const bool many = N > 8192;
+    if (move) return k <= 2 ? n >= 192 : k == 4 ? n >= 64 || !many : true;
+    return k == 8 ? n >= 16 || !many : n >= (many ? 64 : 32);
 }
 int dd64_slices(int64_t n, int64_t N, int64_t want, int64_t part_cap);
 hipError_t launch_dd64_loglik(const GmmDev& g, const float* y, int64_t n, const double* theta,

@@ -67,3 +67,14 @@ def test_move_lds_leaves_a_cu_its_waves(answers, kd, slices):
         assert many == max(work, search) and one < 65536 and many < 65536
         assert 1 <= batch <= 10
         assert batch == 1 or (160 * 1024) // work * slices >= 16
+
+
+def test_fp64_matrix_form_leaves_short_data_to_the_valu_form(answers):
+    """Short data, where the VALU form's single launches (several moves in one, the
+    chain of steps) are faster."""
+    cases = [(1, 191, 64, 1, 0), (1, 192, 64, 1, 1), (2, 50, 65536, 1, 0), (2, 192, 65536, 1, 1),
+             (4, 63, 8193, 1, 0), (4, 63, 8192, 1, 1), (4, 64, 65536, 1, 1), (8, 1, 65536, 1, 1),
+             (2, 63, 8193, 0, 0), (2, 64, 8193, 0, 1), (4, 31, 8192, 0, 0), (4, 32, 8192, 0, 1),
+             (8, 15, 8193, 0, 0), (8, 15, 8192, 0, 1), (8, 16, 8193, 0, 1)]
+    got = answers([f"pays {k} {n} {N} {m}" for k, n, N, m, _ in cases])
+    assert got == [(w,) for *_, w in cases]

@@ -141,3 +141,37 @@ def test_single_move_with_one_slice(smc, k, slices):
     ctx.check()
     assert np.max(np.abs(t.cpu().numpy() - th)) <= 1e-11
     assert rel_err(ll.cpu().numpy(), l).max() <= FP64_TOL
+
+
+@pytest.mark.parametrize("k,n,N", [(1, 31, 70), (1, 32, 70), (2, 63, 8193), (2, 64, 8193),
+                                   (4, 63, 8192), (4, 63, 8193), (8, 15, 8193), (8, 16, 8193)])
+def test_loglik_on_both_sides_of_the_short_data_rule(smc, k, n, N):
+    """The VALU form below, the matrix form from there on, both as exact."""
+    announce(f"ddim fp64 short data k={k} n={n} N={N}")
+    mu = 3.0 * np.random.default_rng(85).standard_normal((k, 8))
+    y = make_mixture_data(n, mu, 1.0, seed=86)
+    th = theta_near_posterior(N, mu, seed=87)
+    g = smc.Gmm.equal_weights(k, 8, 1.0)
+    ctx = smc.Context(0)
+    err = rel_err(_loglik(smc, ctx, g, y, th), ogmm.loglik(th, y, oracle_model(g)))
+    ctx.check()
+    assert err.max() <= FP64_TOL, float(err.max())
+
+
+@pytest.mark.parametrize("k,n", [(1, 191), (1, 192), (2, 191), (2, 192), (4, 63), (4, 64)])
+@pytest.mark.parametrize("moves,steps_per_call", [(1, 1), (3, 4)])
+def test_steps_on_both_sides_of_the_short_data_rule(smc, k, n, moves, steps_per_call):
+    """Single steps and chains of them, one and several moves, with either form."""
+    announce(f"ddim fp64 short data steps k={k} n={n} moves={moves}")
+    N = 130
+    mu = 3.0 * np.random.default_rng(88).standard_normal((k, 8))
+    y = make_mixture_data(n, mu, 1.0, seed=89)
+    betas = np.linspace(0.0, 0.01, 9)
+    g = smc.Gmm.equal_weights(k, 8, 1.0)
+    ref = osmc.smc_run(y, oracle_model(g), betas, N, 0.4, moves, 90)
+    s = smc.SMCSampler(smc.Context(0), g, y, N, betas, 0.4, moves, 90, prec="fp64")
+    r = s.run(graph=True, steps_per_graph=steps_per_call)
+    assert r["accepted"] == int(np.sum(ref["trace"]["accepted"]))
+    assert r["resamples"] == int(np.sum(ref["trace"]["resampled"]))
+    assert np.max(np.abs(r["theta"] - ref["theta"])) <= 1e-9
+    assert rel_err(r["l"], ref["l"]).max() <= 1e-10
