@@ -109,7 +109,12 @@ int check_model(const smc_gmm* m, GmmDev* out) {
     g.prior = m->prior;
     g.pa = m->prior_a;
     g.pb = m->prior_b;
-    g.inv2pb2 = m->prior == SMC_PRIOR_GAUSS ? 1.0 / (2.0 * m->prior_b * m->prior_b) : 0.0;
+    if (m->prior == SMC_PRIOR_GAUSS) {
+        int e = 0;
+        const double b = frexp(m->prior_b, &e);
+        g.pexp = -e;
+        g.inv2pb2 = 1.0 / (2.0 * b * b);
+    }
     *out = g;
     return SMC_OK;
 }

@@ -1019,8 +1019,10 @@ __device__ __forceinline__ double rwmh_log_alpha(int p, PropAt pr_at, CurAt cur_
         double sq_cur = 0.0, sq_prop = 0.0;
 #pragma unroll
         for (int c = 0; c < KD; ++c) {
-            const double zc = cur_at(c) - g.pa;
-            const double zp = pr_at(c) - g.pa;
+            // theta - pa, scaled (exactly) so that no square leaves the FP64 range
+            // where the ratio does not
+            const double zc = __builtin_amdgcn_ldexp(cur_at(c) - g.pa, g.pexp);
+            const double zp = __builtin_amdgcn_ldexp(pr_at(c) - g.pa, g.pexp);
             sq_cur = fma(zc, zc, sq_cur);
             sq_prop = fma(zp, zp, sq_prop);
         }

@@ -28,8 +28,9 @@ struct GmmDev {
     double inv2s2;             // 1 / (2 sigma2)
     double cst;                // per-datum constant -(d/2) ln(2 pi sigma2)
     int prior;                 // SMC_PRIOR_GAUSS or SMC_PRIOR_BOX
+    int pexp;                  // Gaussian prior: 2^pexp brings pb to [1/2, 1)
     double pa, pb;
-    double inv2pb2;            // Gaussian prior: 1 / (2 pb^2)
+    double inv2pb2;            // Gaussian prior: 1 / (2 (2^pexp pb)^2)
     int unit_mass;             // sum_i w_i <= 1 (+1e-6): the FP32 form may skip the max shift
 };
 

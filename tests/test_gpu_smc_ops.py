@@ -1015,3 +1015,30 @@ def test_pt_iterations_with_a_ragged_last_tile(smc, ctx, prec, M, slices, ordere
         ctx.set_slices(0)
         ctx.set_pt_single_workgroup(0)
     assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+
+
+@pytest.mark.parametrize("scale", [1e-156, 1e-120, 1.0, 1e120])
+def test_rwmh_prior_ratio_at_the_ends_of_its_range(smc, ctx, scale):
+    """A Gaussian prior so narrow that 1 / (2 b^2) is beyond the FP64 range (its
+    squares, still above the smallest number, give the oracle's ratio to 2^-38), or
+    so wide that nothing but the prior decides: at beta = 0 the decisions are the
+    oracle's."""
+    announce(f"prior ratio at scale {scale}")
+    N, y = 500, make_mixture_data(40, np.linspace(-3.0, 6.0, 4), 0.55, seed=96)
+    g = smc.Gmm.equal_weights(4, 1, 0.55, prior="gauss", prior_a=0.0, prior_b=scale)
+    om = oracle_model(g)
+    rng = np.random.default_rng(97)
+    th = scale * rng.standard_normal((4, N))
+    l = np.zeros(N)
+    t, ll = _cuda(th), _cuda(l)
+    acc = torch.zeros(1, dtype=torch.int64).cuda()
+    for move in range(3):
+        prop_l, before = l, th
+        th, l, _ = osmc.rwmh_move(before, prop_l, y, om, 0.0, scale, 23, 7, move)
+        smc.smc_rwmh_move(ctx, g, _cuda(y, torch.float32), t, ll, 0.0, scale, 23, 7, move=move,
+                          prec="fp64", n_accept=acc)
+        moved = (th != before).any(axis=0)
+        assert 0 < moved.sum() < N
+        assert np.array_equal(t.cpu().numpy() != before, np.tile(moved, (4, 1)))
+        assert np.max(np.abs(t.cpu().numpy() - th)) <= 1e-12 * scale * 10.0
+        th, l = t.cpu().numpy(), ll.cpu().numpy()
