@@ -11,7 +11,7 @@ device memory), so ten consecutive steps are captured in one hipGraph and
 replayed; inputs are resident in HBM.
 
 value = particle x datum log-likelihood evaluations per second over whole
-steps (FP32 path). The same run times the plain FP64 GPU form and reports the
+steps (FP32 path). The same run times the FP64 GPU form and reports the
 FP32/FP64 step-time ratio, the dominant kernel's roofline position (its
 average launch time from HIP events on its own stream) and the FP64 CPU
 oracle on a bounded sample of the same workload.
@@ -88,7 +88,7 @@ MOVE_COUNTERS = {
 
 # the files the move kernel is compiled from (with the compiler flags of build.py)
 MOVE_SOURCES = ("gmm_kernels.hip", "gmm_common.hpp", "exchange.hpp", "internal.hpp",
-                "philox.hpp", "wave.hpp", "dd.hpp", "cdf_search.hpp", "reduce.hpp",
+                "philox.hpp", "wave.hpp", "dd.hpp", "fp64.hpp", "cdf_search.hpp", "reduce.hpp",
                 "../../include/smc.h")
 
 
@@ -732,7 +732,7 @@ def time_batched(smc, torch, ctx, prec, steps, warmup, R=256, keep_state=False,
     betas = beta_schedule(BATCHED["T"], BATCHED["schedule"])
     table = None
     if tune_batch:
-        # per range of n, the waves per tile of the persistent move (untimed)
+        # per range of n, the waves per tile of the batched move (untimed)
         from paper_0905_2441_amd import autotune
         table = autotune.tune_batched(ctx, g, datas, [r.N for r in runs],
                                       [r.run_seed for r in runs], betas, BATCHED["step_sd"],

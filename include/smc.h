@@ -127,9 +127,9 @@ const char* smc_last_error(void);
  * and N <= 32768 spreads them over up to 16 workgroups of 4 or 8 waves per 64
  * particles and completes in a second, per-particle kernel. Other kernels use
  * min(slices, 16).
- * Results depend on the slicing only through the order of FP64 additions and,
- * in FP32, through which of the equivalent per-datum forms (see smc_loglik) a
- * wave's slice takes and, in the pivot form, through its windows. */
+ * Results depend on the slicing only through the order of FP64 additions and
+ * through which of the equivalent per-datum forms (see smc_loglik; FP64 at d = 1
+ * too) a wave's slice takes and, in the pivot forms, through its windows. */
 int smc_set_slices(smc_ctx ctx, int32_t slices);
 
 /* Which launches a rule of the launch table shapes. */
@@ -173,8 +173,13 @@ int smc_set_launch_table(smc_ctx ctx, const smc_launch_rule* rules, int32_t coun
  * product form (which of them a wave takes may depend on the other particles of
  * its 64, and changes a result by rounding only); for
  * d = 8 the quadratic forms as one FP64 matrix contraction about a centre of
- * the data (the population-MCMC calls and a move that cannot have its scratch
- * take an exp per term and a log per datum); relative error below 1e-12;
+ * the data, or by differences for data far from it (short data, the
+ * population-MCMC calls and a move that cannot have its scratch take an exp per
+ * term and a log per datum). The error against 64 bits is no larger than that of
+ * an exp per term and a log per datum; relative error below 1e-12. The matrix
+ * forms (BF16X3, FP64 at d = 8) keep partial sums and a move's proposals in the
+ * context's scratch, which an FP64 move at d = 8 grows on its first call outside
+ * a capture: like every call that uses it they must not overlap on one context;
  * FP32: FP32 arithmetic in base 2 with hardware exp2, no per-datum log: each
  * datum's mixture sum is multiplied into a running FP32 product that is
  * renormalised by frexp after every block of 8 or 16 data, its exponents added
@@ -432,8 +437,8 @@ int smc_batch_init(smc_ctx ctx, smc_batch b, const smc_gmm* model, const float* 
  *   (>= 1) RW-MH moves, one launch each over the work list, a workgroup a
  *   unit. run_stats: device FP64 [R][4] = {log Z (accumulated), last ESS,
  *   resample count, unused}. prec: FP32 or FP64. A run's results depend on its
- *   S only through the order of its FP64 slice sums and, in FP32, through which
- *   of the per-datum forms a wave takes and its data centre (see smc_loglik). */
+ *   S only through the order of its FP64 slice sums and through which of the
+ *   per-datum forms a wave takes (see smc_loglik). */
 int smc_step_batched(smc_ctx ctx, smc_batch b, const smc_gmm* model, const float* y,
                      double* theta, double* loglik, double* logw, double* W, const double* beta,
                      int32_t T, int32_t* t_dev, double step_sd, int32_t n_moves, double ess_frac,

@@ -230,7 +230,9 @@ k_b_loglik(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ unit
 // workgroups to a CU; as a persistent loop over a work counter it took 127, since
 // the loop's invariants were held through the likelihood (64 runs of up to 65536
 // particles and 100000 data, k = 4: 5.02 ms so, 4.95 with a workgroup a unit at 91
-// registers, 4.65 at 80, 4.51 at 64).
+// registers, 4.65 at 80, 4.51 at 64; three steps and the first likelihood at 64, 80
+// and 96 registers, k = 1: 2.01, 2.07 and 2.28 ms, k = 2: 9.00, 9.19 and 9.64, k = 3:
+// 14.5, 15.1 and 15.6).
 template <int K, int PREC>
 __global__ void __launch_bounds__(kBatchBlock, PREC == SMC_PREC_FP32 && K <= 4 ? 8 : 4)
 k_b_move(const BatchRun* __restrict__ runs, const BatchUnit* __restrict__ units,

@@ -8,11 +8,10 @@ namespace smc {
 // Inclusive prefixes (double-double) of the piece [piece, piece + kRedBlock*PER)
 // clipped to `end`, offset by `carry`, stored rounded in two halves to
 // out_hi/out_lo; returns the prefix stored for the piece's last element. Each
-// thread scans PER
-// consecutive elements, but the weights are read and the prefixes written
-// striped across the block (element e*256 + t by thread t: every wave access
-// is 512 contiguous bytes) through LDS, whose rows are padded by one double per
-// PER elements so that the per-thread runs do not fall on the same banks.
+// thread scans PER consecutive elements, but the weights are read and the prefixes
+// written striped across the block (element e*256 + t by thread t: every wave
+// access is 512 contiguous bytes) through LDS, whose rows are padded by one double
+// per PER elements so that the per-thread runs do not fall on the same banks.
 template <int PER, class WeightAt>
 __device__ __forceinline__ dd scan_piece(int piece, int end, dd carry, double* out_hi,
                                          double* out_lo, WeightAt weight) {

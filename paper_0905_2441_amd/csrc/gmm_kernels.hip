@@ -35,9 +35,9 @@
 // log-likelihood stays below 1e-6 for n up to 10^5.
 //
 // FP64 forms: the same decomposition. For 1-D data the pivot form in FP64
-// (pivot_fp64); the headline move (N = 131072, n = 1000, 4 slices, mean of 20 steps) takes 231 us
-// where an exp per term and a log per datum of the device library took 782 us.
-// For d > 1 the latter.
+// (pivot_fp64; 20 tempering steps at N = 131072, n = 1000 take 4.40 ms where an exp per
+// term and a log per datum of the device library took 15.5). For d > 1 the latter, where
+// the matrix form (k_dd64_partial) does not take the call: population MCMC, short data.
 #include <algorithm>
 #include <vector>
 
@@ -1038,7 +1038,7 @@ hipError_t launch_pt_local(const GmmDev& g, const float* y, int64_t n, double* t
     if (S * tiles > kMaxSlices) S = kMaxSlices / tiles;
     if (S > n) S = static_cast<int>(n);
     if (S < 1) S = 1;
-    // waves that only draw: one per tile and random item, as far as 16 waves go
+    // waves that only draw: one per tile and random item, as far as kPtAheadWaves go
     const bool ahead = M <= kPtAheadChains && tiles * S < kPtAheadWaves;
     const int items = tiles * ((kd + 1) / 2 + 2);
     const int drawers = ahead ? std::min(kPtAheadWaves - tiles * S, items) : 0;

@@ -140,8 +140,9 @@ struct MoveStep {
 
 // Launch shape of a VALU move for one 64-particle tile: the observations are
 // split into `total` contiguous slices, one per wave of `groups` workgroups of
-// `slices` waves; the last group's waves beyond `total` hold none. With groups > 1 each workgroup writes its partial sums to scratch and a
-// per-particle kernel completes the move.
+// `slices` waves; the last group's waves beyond `total` hold none. With groups > 1 each
+// workgroup writes its partial sums to scratch and a per-particle kernel completes the
+// move.
 struct Split {
     int slices;
     int groups;

@@ -18,8 +18,8 @@
 // of the weights, sampled N times) builds the CDF with a double-double scan:
 // each chunk's workgroup stores within-chunk inclusive prefixes and the chunk
 // total; the search forms the chunk offsets once per workgroup in LDS, or reads
-// those of a launch of their own beyond kLdsChunks chunks, and rounds offset + prefix once, so every C_j is the correctly rounded
-// prefix sum (up to double-double error, about 2^-104 relative). Both kernels
+// those of a launch of their own beyond kLdsChunks chunks, and rounds offset +
+// prefix once, so every C_j is the correctly rounded prefix sum (up to double-double error, about 2^-104 relative). Both kernels
 // can be predicated on the device-side ESS test.
 #include "internal.hpp"
 #include "philox.hpp"
