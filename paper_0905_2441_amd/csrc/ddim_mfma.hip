@@ -366,27 +366,35 @@ k_dd_partial(const __bf16* __restrict__ A, int n, int n_pad, const __bf16* __res
 // mean of up to 64 data spread over the array, the same in every workgroup), so
 // that u_j is exact; C_i is formed from the rounded v_i in two parts, so that the
 // exponents are those of one mean within 2^-54 of mu_i, and the low part is a
-// factor of the component's terms. What is left averages over the data: tiles
-// holding a datum with Y_j above dd64_max_y(n), a datum that is not finite, or a
-// particle with a mean that is not finite take the difference form (no expansion,
-// plain FP64): 8 subtractions and 8 multiply-adds per component instead of the
-// matrix unit's. A wave sets such tiles aside and works them off after every block
-// of 64, when the expansion's operands are dead and their registers free, with the
-// means from LDS: k = 8, N = 16384, n = 8192 1.34 ms (the expansion 0.81), where
-// two passes of rolled loops over means and data in memory took 13.0 ms and the
-// VALU form 4.1. Waves with a particle so far away that a datum's sum falls below
-// 2^-1000 take each datum's largest exponent out first.
+// factor of the component's terms; s2, log2 w_i and ln 2 enter in two parts; and
+// Y_j is summed as (s2 u) u, because a square of the few bits of a u ends in 0, 1
+// or 4 of 8 and sums of them round one way. (With s2 in one part and Y_j = s2
+// sum u^2 the relative error at n = 20000, near the modes, was 5.5e-16 at k = 8,
+// sigma2 = 0.3 and 17.5e-16 at k = 2, 0.15, nearly all of it alike for every
+// particle; it is 1.0e-16 and 1.5e-16, term by term 1.7e-16 and 2.8e-16.) What is
+// left averages over the data: tiles holding a datum with Y_j above dd64_max_y(n), a
+// datum that is not finite, or a particle with a mean that is not finite take the
+// difference form (no expansion, plain FP64): 8 subtractions and 8 multiply-adds per
+// component instead of the matrix unit's. A wave sets such tiles aside and works
+// them off after every block of 64, when the expansion's operands are dead and their
+// registers free, with the means from LDS: k = 8, N = 16384, n = 8192 1.34 ms (the
+// expansion 0.81), where two passes of rolled loops over means and data in memory
+// took 13.0 ms and the VALU form 4.1. Waves with a particle so far away that a
+// datum's sum falls below 2^-1000 take each datum's largest exponent out first.
 constexpr int kDd64StageTiles = 8;                     // data rows per LDS stage
 constexpr int kDd64Rows = kDd64StageTiles * kTileRows;
 constexpr int kDd64Block = 8;                          // stages per block: 64 tiles, a bit each
 constexpr double kDd64MinC = -1.0e8;
+
+constexpr double kLn2Tail = 2.3190468138462996e-17;    // ln 2 - kLn2
+constexpr double kLog2eTail = 2.0355273740931033e-17;  // log2 e - kLog2e
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 template <int K>
 __global__ void __launch_bounds__(kDdBlock, 3)
 k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmDev g, double s2,
-               double max_y, int S, double* part) {
+               double s2_lo, double max_y, int S, double* part) {
     __shared__ double su[2][kDd64Rows * kDdDim];
     __shared__ __align__(16) double sy[2][kDd64Rows];
     __shared__ double cen[kDdDim];
@@ -432,18 +440,18 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
             yv[q] = row < n ? y[static_cast<size_t>(row) * kDdDim + half * 4 + q] : 0.0f;
     };
     auto store_stage = [&](int buf) {
-        double ys = 0.0;
+        double ys = 0.0;                             // (s2 d) d, not s2 (d d): see above
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const double d = static_cast<double>(yv[q]) - hc[q];
-            ys = fma(d, d, ys);
+            ys = fma(fma(s2, d, s2_lo * d), d, ys);
             su[buf][srow * kDdDim + half * 4 + q] = d;
         }
         ys += __shfl_xor(ys, 1, kWave);
-        if (half == 0) sy[buf][srow] = s2 * ys;
+        if (half == 0) sy[buf][srow] = ys;
     };
     const double quarter = 0.25 / s2;                // 1 / (4 s2) in two parts
-    const double quarter_lo = fma(-quarter, 4.0 * s2, 1.0) * quarter;
+    const double quarter_lo = fma(-quarter, 4.0 * s2_lo, fma(-quarter, 4.0 * s2, 1.0)) * quarter;
     const int nst = (t1 - t0 + kDd64StageTiles - 1) / kDd64StageTiles;
     if (nst > 0) {
         load_stage(0);
@@ -454,7 +462,6 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
     double prod = 1.0, msum = 0.0, nsum = 0.0;       // nsum: in natural units
     int expo = 0;
     bool direct = g.unit_mass != 0;
-    bool nan = false;                                // a mean of this lane's particle is NaN
     const int arow = 4 * (col & 3) + (col >> 2);
     for (int s0 = 0; s0 < nst; s0 += kDd64Block) {
         const int s1 = min(nst, s0 + kDd64Block);
@@ -470,8 +477,10 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
             const double c1 = cen[kg], c2 = cen[4 + kg];
 #pragma unroll
             for (int i = 0; i < K; ++i) {
-                b1[i] = 2.0 * s2 * (mean[i * kDdDim + kg][mq] - c1);
-                b2[i] = 2.0 * s2 * (mean[i * kDdDim + 4 + kg][mq] - c2);
+                const double m1 = mean[i * kDdDim + kg][mq] - c1;
+                const double m2 = mean[i * kDdDim + 4 + kg][mq] - c2;
+                b1[i] = fma(2.0 * s2, m1, 2.0 * s2_lo * m1);
+                b2[i] = fma(2.0 * s2, m2, 2.0 * s2_lo * m2);
                 // C_i in two parts from the rounded operands, so that the exponents are
                 // those of one (slightly moved) mean whatever the datum
                 const double p1 = b1[i] * b1[i], p2 = b2[i] * b2[i];
@@ -481,11 +490,12 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
                 q = dd_add(q, dd{__shfl_xor(q.hi, 32, kWave), __shfl_xor(q.lo, 32, kWave)});
                 const double h = -q.hi * quarter;
                 const double low = fma(-q.hi, quarter, -h) - q.hi * quarter_lo - q.lo * quarter;
-                nan |= b1[i] != b1[i] || b2[i] != b2[i];
                 fine &= h >= kDd64MinC;                        // false for NaN
-                const dd t = two_sum(h, g.lw[i] * kLog2e);     // -inf: the component is skipped
+                const double lw = g.lw[i] * kLog2e;            // -inf: the component is skipped
+                const double lw_lo = fma(g.lw[i], kLog2e, -lw) + g.lw[i] * kLog2eTail;
+                const dd t = two_sum(h, lw);
                 C[i] = t.hi;
-                cl[i] = static_cast<float>((t.lo + low) * kLn2);
+                cl[i] = static_cast<float>((t.lo + low + lw_lo) * kLn2);
             }
         }
         fine = __all(fine);
@@ -639,10 +649,14 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
             prod = __builtin_amdgcn_frexp_mant(prod);
         }
     }
-    double v = msum + static_cast<double>(expo) + log2(prod) + nsum * kLog2e;
+    const double bits = msum + static_cast<double>(expo) + log2(prod);
+    double v = nsum + fma(bits, kLn2, bits * kLn2Tail);
     // the differences' clamp passed over a NaN: a mean's, or that of a datum no
     // component has a finite exponent for
-    if (nan || !(nsum > -INFINITY)) v = NAN;
+    bool nan = !(nsum > -INFINITY);
+#pragma unroll 1
+    for (int c = kg; c < K * kDdDim; c += 4) nan |= mean[c][mp] != mean[c][mp];
+    if (nan) v = NAN;
     v += __shfl_xor(v, 16, kWave);
     v += __shfl_xor(v, 32, kWave);
     if (kg == 0 && p < N) part[static_cast<size_t>(slice) * N + p] = v;
@@ -650,16 +664,17 @@ k_dd64_partial(const float* __restrict__ y, int n, const double* th, int N, GmmD
 
 // Adds the slices' partial sums: bound by latency, so they are requested at once and
 // a workgroup is one wave (k = 2, n = 1607, N = 4683: the whole call 22.1 -> 21.7 us).
+template <int PREC>
 __global__ void __launch_bounds__(kWave)
 k_dd_finish(const double* part, int S, int N, int n, GmmDev g, double* out, int* status) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= N) return;
-    const double l = finish_loglik<SMC_PREC_FP32>(GroupSums(part, N, p, S).total(S), n, g);
+    const double l = finish_loglik<PREC>(GroupSums(part, N, p, S).total(S), n, g);
     out[p] = l;
     if (l != l) atomicOr(status, kStatusNaN);
 }
 
-template <int K>
+template <int K, int PREC>
 __global__ void __launch_bounds__(256)
 k_dd_accept(const double* part, int S, int N, int n, const double* theta_prop, double* theta,
             double* l,
@@ -674,7 +689,7 @@ k_dd_accept(const double* part, int S, int N, int n, const double* theta_prop, d
     if (p < N) {
         double tot = part[p];
         for (int s = 1; s < S; ++s) tot += part[static_cast<size_t>(s) * N + p];
-        const double l_prop = finish_loglik<SMC_PREC_FP32>(tot, n, g);
+        const double l_prop = finish_loglik<PREC>(tot, n, g);
         const MoveSource srcs = move_source(ms, theta, l);
         acc = rwmh_accept<KD>(
             p, p, N, [&](int c) { return theta_prop[static_cast<size_t>(c) * N + p]; }, l_prop,
@@ -708,7 +723,8 @@ int dd_slices(int64_t n, int64_t N) {
 // about ten roundings of 2^-53 Y; they average over the data, and the largest that
 // leaves a log-likelihood's error at or below that of an exp per term and a log per
 // datum was found against extended precision (k = 8, sigma2 = 1 and 0.3, means of
-// spread 3, rms over particles, expansion and difference form against term by term:
+// spread 3, rms over particles, expansion and difference form against term by term,
+// s2 in one part:
 // n = 600 1.5 and 0.9 against 0.9e-16, n = 2000 1.2 and 0.9 against 1.6, sigma2 =
 // 0.3 n = 2000 4.0 and 1.3 against 2.2, n = 20000 3.7 and 1.5 against 6.3).
 double dd64_max_y(int64_t n) {
@@ -759,8 +775,8 @@ hipError_t launch_dd_loglik(const GmmDev& g, const __bf16* A, int64_t n, const d
 #undef SMC_DD
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dd_finish, dim3(static_cast<unsigned>((N + kWave - 1) / kWave)),
-                       dim3(kWave), 0, s,
+    hipLaunchKernelGGL(k_dd_finish<SMC_PREC_FP32>,
+                       dim3(static_cast<unsigned>((N + kWave - 1) / kWave)), dim3(kWave), 0, s,
                        part, S, static_cast<int>(N), static_cast<int>(n), g, out, status);
     return hipGetLastError();
 }
@@ -784,9 +800,9 @@ hipError_t launch_dd_rwmh(const GmmDev& g, const __bf16* A, int64_t n, double* t
                            static_cast<int>(np), B, static_cast<int>(N), S, g.unit_mass, part);              \
         e = hipGetLastError();                                                                  \
         if (e != hipSuccess) return e;                                                          \
-        hipLaunchKernelGGL((k_dd_accept<KK>), g1, dim3(256), 0, s, part, S, static_cast<int>(N), \
-                           static_cast<int>(n), theta_prop, theta, l, beta_vec, src, seed, move, \
-                           g, n_accept, status, ms);                                            \
+        hipLaunchKernelGGL((k_dd_accept<KK, SMC_PREC_FP32>), g1, dim3(256), 0, s, part, S,       \
+                           static_cast<int>(N), static_cast<int>(n), theta_prop, theta, l,      \
+                           beta_vec, src, seed, move, g, n_accept, status, ms);                 \
         return hipGetLastError();                                                               \
     }
     SMC_DD(1) SMC_DD(2) SMC_DD(4) SMC_DD(8)
@@ -799,10 +815,12 @@ namespace {
 hipError_t launch_dd64_partial(const GmmDev& g, const float* y, int64_t n, const double* theta,
                                int64_t N, double* part, int S, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>((N + 63) / 64), static_cast<unsigned>(S));
+    const double s2 = s2_of(g);
+    const double s2_lo = std::fma(g.inv2s2, kLog2e, -s2) + g.inv2s2 * kLog2eTail;
 #define SMC_DD(KK)                                                                              \
     if (g.k == KK)                                                                              \
         hipLaunchKernelGGL((k_dd64_partial<KK>), grid, dim3(kDdBlock), 0, s, y,                  \
-                           static_cast<int>(n), theta, static_cast<int>(N), g, s2_of(g),           \
+                           static_cast<int>(n), theta, static_cast<int>(N), g, s2, s2_lo,          \
                            dd64_max_y(n), S, part);
     SMC_DD(1) SMC_DD(2) SMC_DD(4) SMC_DD(8)
 #undef SMC_DD
@@ -816,8 +834,8 @@ hipError_t launch_dd64_loglik(const GmmDev& g, const float* y, int64_t n, const 
                               hipStream_t s) {
     const hipError_t e = launch_dd64_partial(g, y, n, theta, N, part, S, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dd_finish, dim3(static_cast<unsigned>((N + kWave - 1) / kWave)),
-                       dim3(kWave), 0, s,
+    hipLaunchKernelGGL(k_dd_finish<SMC_PREC_FP64>,
+                       dim3(static_cast<unsigned>((N + kWave - 1) / kWave)), dim3(kWave), 0, s,
                        static_cast<const double*>(part), S, static_cast<int>(N),
                        static_cast<int>(n), g, out, status);
     return hipGetLastError();
@@ -837,8 +855,9 @@ hipError_t launch_dd64_rwmh(const GmmDev& g, const float* y, int64_t n, double* 
     if (e != hipSuccess) return e;
 #define SMC_DD(KK)                                                                              \
     if (g.k == KK)                                                                              \
-        hipLaunchKernelGGL((k_dd_accept<KK>), dim3(static_cast<unsigned>((N + 255) / 256)),      \
-                           dim3(256), 0, s, static_cast<const double*>(part), S,                 \
+        hipLaunchKernelGGL((k_dd_accept<KK, SMC_PREC_FP64>),                                     \
+                           dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s,        \
+                           static_cast<const double*>(part), S,                                  \
                            static_cast<int>(N), static_cast<int>(n),                             \
                            static_cast<const double*>(theta_prop), theta, l, beta_vec, src,      \
                            seed, move, g, n_accept, status, ms);

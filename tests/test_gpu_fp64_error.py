@@ -103,3 +103,19 @@ def test_error_of_the_matrix_form(smc, k, n, sigma2, start, slices):
     th = (theta_near_posterior(128, mu, seed=76) if start == "near"
           else theta_prior_draws(128, k, 8, seed=77))
     _check(smc, y, th, k, 8, sigma2, slices)
+
+
+@pytest.mark.parametrize("k,n,sigma2,slices", [
+    (2, 20000, 0.15, 16),
+    (8, 20000, 0.3, 16),
+    (2, 1500, 0.9, 16),
+])
+def test_matrix_form_rounds_no_datum_alike(smc, k, n, sigma2, slices):
+    """Roundings alike for every datum (of s2 = log2 e / (2 sigma2), of sums of squares
+    of FP32 differences) would grow with n where a running sum's average out."""
+    announce(f"fp64 error d=8 k={k} n={n} sigma2={sigma2} long data")
+    g = np.random.default_rng(50)
+    mu = 3.0 * g.standard_normal((k, 8))
+    y = (mu[g.integers(0, k, n)] + math.sqrt(sigma2) * g.standard_normal((n, 8)))
+    th = mu.reshape(-1, 1) + 0.05 * g.standard_normal((k * 8, 64))
+    _check(smc, y.astype(np.float32), th, k, 8, sigma2, slices)
